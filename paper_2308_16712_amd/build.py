@@ -22,7 +22,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libls_ed.so")
 SOURCES = ["api.cpp", "group.cpp", "terms.cpp", "basis.hip", "matvec.hip", "batch.hip", "lanczos.hip", "stored.hip"]
-HEADERS = ["ls_internal.hpp", "orbit.hpp", "matvec_impl.hpp", "dispatch.hpp"]
+HEADERS = ["ls_internal.hpp", "orbit.hpp", "enumerate.hpp", "matvec_impl.hpp", "dispatch.hpp"]
 
 ARCH = "gfx950"
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", INCLUDE, "-I", CSRC,

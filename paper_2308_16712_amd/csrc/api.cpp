@@ -106,6 +106,7 @@ void free_basis(ls_basis *b) {
     b->used.drain();
     ls::dev_free(b->d_reps);
     ls::dev_free(b->d_stab);
+    ls::dev_free(b->d_skip);
     ls::dev_free(b->d_buckets);
     ls::dev_free(b->d_table);
     ls::dev_free(b->d_binom);

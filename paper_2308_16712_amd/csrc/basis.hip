@@ -6,13 +6,14 @@
 // survivors with a histogram -> cumulative sum -> offsets scheme (Section
 // 5.1 "Block to hashed", Section 5.2).  On one GPU the same scheme becomes
 // an order-preserving stream compaction:
-//   pass 1  every lane filters 64 consecutive candidates (Gosper's
-//           next-combination step between them) and keeps a 64-bit mark
-//           word; a workgroup reduction gives per-chunk counts;
+//   pass 1  every lane walks a run of consecutive candidates (enumerate.hpp:
+//           jumps over those one test rules out together) and counts its
+//           members; a workgroup reduction gives per-chunk counts;
 //   scan    an exclusive scan of the chunk counts gives chunk offsets;
-//   pass 2  a workgroup scan of the lanes' mark popcounts gives each lane's
-//           offset; the lane regenerates its candidates and writes the
-//           marked ones.  No atomics; the output is sorted by construction.
+//   pass 2  a workgroup scan of the lanes' counts gives each lane's offset;
+//           the lane walks its run again and writes its members and their
+//           stabilizer sizes.  No atomics; the output is sorted by
+//           construction.
 // The "condition" kept by the filter: s is the minimum of its orbit, and P
 // does not annihilate it (every stabilizer element has character 1).
 
@@ -22,14 +23,13 @@
 #include <mutex>
 #include <string>
 
-#include "orbit.hpp"
+#include "enumerate.hpp"
 
 namespace ls {
 
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kCandPerLane = 64;
 
 __device__ uint64_t unrank_colex(uint64_t rank, uint32_t n, int32_t w, const uint64_t *tab) {
     uint64_t s = 0;
@@ -43,104 +43,6 @@ __device__ uint64_t unrank_colex(uint64_t rank, uint32_t n, int32_t w, const uin
         }
     }
     return s;
-}
-
-template <typename W>
-__device__ __forceinline__ W next_combination(W x) {
-    const W c = x & (~x + 1);
-    const W r = x + c;
-    const int z = sizeof(W) == 4 ? __builtin_ctz(static_cast<uint32_t>(x))
-                                 : __builtin_ctzll(static_cast<uint64_t>(x));
-    return (((r ^ x) >> 2) >> z) | r;
-}
-
-// Membership of cnt consecutive candidates s, next(s), ...: s is kept iff no
-// group image is smaller and every image equal to s has chi == 1.  hit(q)
-// is called for every kept candidate q.
-//
-// Most candidates are rejected after one or two images, while a member (about
-// one candidate in |G|) needs every image.  A loop over candidates with the
-// group walk inside would run each wave at the pace of its slowest lane for
-// every candidate; here one iteration checks one image (with its spin-flipped
-// partner) of the lane's current candidate, and a lane moves on to its next
-// candidate as soon as the current one is decided, so a wave's time is the
-// largest per-lane total over the run rather than the sum of per-candidate
-// maxima.  Group order as in for_each_image: coset p, y-shift b, x-shift a.
-template <typename W, int KIND, typename Hit>
-__device__ __forceinline__ void walk_members(const PlanDev &P, W s, uint32_t cnt, bool gosper, Hit &&hit) {
-    const W full = static_cast<W>(P.full);
-    const bool pf = P.pair_flip != 0;
-    const uint32_t nz = pf ? 2u : 1u;
-    const uint32_t n = P.n_sites, lx = P.lx, ly = P.ly, nc = P.n_cosets, nt = P.n_trans;
-    uint32_t q = 0, a = 0, b = 0, p = 0;
-    // cosets[0] is the identity: the walk of every candidate starts at s
-    W ub = s, v = s;
-    uint32_t lo = 0, hi = 0;   // ring32: the coset image doubled into 64 bits
-    if constexpr (KIND == kOrbitRing32) {
-        const uint64_t uu = static_cast<uint64_t>(s) | (static_cast<uint64_t>(s) << n);
-        lo = static_cast<uint32_t>(uu);
-        hi = static_cast<uint32_t>(uu >> 32);
-    }
-    for (;;) {
-        const W vf = static_cast<W>(v ^ full);
-        bool out = v < s || (pf && vf < s);
-        if (!out && (v == s || (pf && vf == s))) {
-            uint32_t code;
-            if constexpr (KIND == kOrbitRing32) code = (p * n + (a == 0 ? 0u : n - a)) * nz;
-            else code = (p * nt + a + lx * b) * nz;
-            if (v == s && !chi_is_one(P, code)) out = true;
-            if (pf && vf == s && !chi_is_one(P, code + 1)) out = true;
-        }
-        bool end = false;
-        if constexpr (KIND == kOrbitRing32) {
-            // a counts right rotations here
-            if (++a < n) {
-                v = static_cast<W>(__builtin_amdgcn_alignbit(hi, lo, a)) & full;
-            } else {
-                a = 0;
-                if (++p < nc) {
-                    const W u = apply_coset<W>(P.cosets[p], s, P);
-                    const uint64_t uu = static_cast<uint64_t>(u) | (static_cast<uint64_t>(u) << n);
-                    lo = static_cast<uint32_t>(uu);
-                    hi = static_cast<uint32_t>(uu >> 32);
-                    v = u;
-                } else {
-                    end = true;
-                }
-            }
-        } else {
-            if (++a < lx) {
-                v = xrot<W>(v, P);
-            } else {
-                a = 0;
-                if (++b < ly) {
-                    ub = yrot<W>(ub, P);
-                    v = ub;
-                } else {
-                    b = 0;
-                    if (++p < nc) {
-                        ub = apply_coset<W>(P.cosets[p], s, P);
-                        v = ub;
-                    } else {
-                        end = true;
-                    }
-                }
-            }
-        }
-        if (out || end) {
-            if (!out) hit(q);
-            if (++q >= cnt) break;
-            if (gosper) s = next_combination<W>(s);
-            else s = static_cast<W>(s + 1);
-            a = b = p = 0;
-            ub = v = s;
-            if constexpr (KIND == kOrbitRing32) {
-                const uint64_t uu = static_cast<uint64_t>(s) | (static_cast<uint64_t>(s) << n);
-                lo = static_cast<uint32_t>(uu);
-                hi = static_cast<uint32_t>(uu >> 32);
-            }
-        }
-    }
 }
 
 __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t *sh) {
@@ -175,76 +77,96 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *s
 struct EnumArgs {
     PlanDev plan;
     const uint64_t *binom;
-    uint64_t total;        // candidates
+    uint64_t begin, total;    // candidate ranks [begin, total)
+    uint32_t per_lane;        // consecutive candidates of a lane
     uint32_t n_sites;
     int32_t weight;
-    uint64_t *marks;       // [lanes]
-    uint32_t *counts;      // [blocks]
+    uint32_t *lane_counts;    // [lanes]
+    uint32_t *counts;         // [blocks]
     const uint64_t *offsets;  // [blocks], pass 2
-    uint64_t *reps;        // pass 2
+    uint64_t *reps;           // pass 2
+    uint16_t *stab;           // pass 2
 };
 
 template <typename W>
-__device__ __forceinline__ W first_candidate(const EnumArgs &a, uint64_t start) {
-    return a.weight >= 0 ? static_cast<W>(unrank_colex(start, a.n_sites, a.weight, a.binom))
-                         : static_cast<W>(start);
+__device__ __forceinline__ W candidate(const EnumArgs &a, uint64_t rank) {
+    return a.weight >= 0 ? static_cast<W>(unrank_colex(rank, a.n_sites, a.weight, a.binom)) : static_cast<W>(rank);
 }
 
-template <typename W>
-__device__ __forceinline__ W next_candidate(const EnumArgs &a, W s) {
-    return a.weight >= 0 ? next_combination<W>(s) : static_cast<W>(s + 1);
+// Walks the lane's candidates; hit(s, stab) for every member in order.  A
+// lane's range ends where its neighbour's starts: one unranking a lane.
+template <typename W, int WALK, typename Hit>
+__device__ __forceinline__ void walk_lane(const EnumArgs &a, uint64_t *sh, Hit &&hit) {
+    const uint64_t lane0 = static_cast<uint64_t>(blockIdx.x) * kBlock;
+    const uint64_t start = a.begin + (lane0 + threadIdx.x) * a.per_lane;
+    const bool live = start < a.total;
+    const W s = live ? candidate<W>(a, start) : static_cast<W>(0);
+    sh[threadIdx.x] = live ? static_cast<uint64_t>(s) : ~0ULL;
+    if (threadIdx.x == 0) {
+        const uint64_t stop = a.begin + (lane0 + kBlock) * a.per_lane;
+        sh[kBlock] = stop < a.total ? static_cast<uint64_t>(candidate<W>(a, stop)) : ~0ULL;
+    }
+    __syncthreads();
+    uint64_t end = sh[threadIdx.x + 1];
+    __syncthreads();
+    if (!live) return;
+    CandRange<W> R;
+    R.gosper = a.weight >= 0;
+    const W full = static_cast<W>(a.plan.full);
+    // the sector's greatest candidate: all its up spins on top
+    R.last = full;
+    if (R.gosper && a.weight < static_cast<int32_t>(a.n_sites)) R.last = static_cast<W>(full & ~(full >> a.weight));
+    // a range that ends before the sector does, without a neighbour lane
+    if (end == ~0ULL && start + a.per_lane >= a.total) {
+        const W stop = candidate<W>(a, a.total - 1);
+        if (stop < R.last) end = static_cast<uint64_t>(stop) + 1;
+    }
+    R.end = end;
+    if constexpr (WALK == kWalkRing) walk_ring<W>(a.plan, s, R, hit);
+    else if constexpr (WALK == kWalkTorus) walk_torus<W>(a.plan, s, R, hit);
+    else walk_images<W>(a.plan, s, R, hit);
 }
 
-template <typename W, int KIND>
+// Pass 1 of the build.
+template <typename W, int WALK>
 __global__ void __launch_bounds__(kBlock) k_enum_mark(EnumArgs a) {
+    __shared__ uint64_t ends[kBlock + 1];
     __shared__ uint32_t sh[kBlock];
+    uint32_t c = 0;
+    walk_lane<W, WALK>(a, ends, [&](W, uint32_t) { ++c; });
     const uint64_t lane = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    const uint64_t start = lane * kCandPerLane;
-    uint64_t mask = 0;
-    if (start < a.total) {
-        const uint32_t cnt = static_cast<uint32_t>(min<uint64_t>(kCandPerLane, a.total - start));
-        walk_members<W, KIND>(a.plan, first_candidate<W>(a, start), cnt, a.weight >= 0,
-                              [&](uint32_t q) { mask |= 1ULL << q; });
-        a.marks[lane] = mask;
-    }
-    const uint32_t c = block_sum(static_cast<uint32_t>(__builtin_popcountll(mask)), sh);
-    if (threadIdx.x == 0) a.counts[blockIdx.x] = c;
+    a.lane_counts[lane] = c;
+    const uint32_t t = block_sum(c, sh);
+    if (threadIdx.x == 0) a.counts[blockIdx.x] = t;
 }
 
-// Count-only pass over candidates [begin, end): each lane takes per_lane
-// consecutive candidates; block totals are added into *acc (integer atomic
-// adds: the total does not depend on their order), so launches on one stream
-// over consecutive ranges accumulate.
-template <typename W, int KIND>
-__global__ void __launch_bounds__(kBlock) k_enum_count(EnumArgs a, uint64_t begin, uint64_t end, uint32_t per_lane,
-                                                       unsigned long long *acc) {
+// Count only: block totals are added into *acc (integer atomic adds: the
+// total does not depend on their order), so launches on one stream over
+// consecutive ranges accumulate.
+template <typename W, int WALK>
+__global__ void __launch_bounds__(kBlock) k_enum_count(EnumArgs a, unsigned long long *acc) {
+    __shared__ uint64_t ends[kBlock + 1];
     __shared__ uint32_t sh[kBlock];
-    const uint64_t lane = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    const uint64_t start = begin + lane * per_lane;
     uint32_t c = 0;
-    if (start < end) {
-        const uint32_t cnt = static_cast<uint32_t>(min<uint64_t>(per_lane, end - start));
-        walk_members<W, KIND>(a.plan, first_candidate<W>(a, start), cnt, a.weight >= 0, [&](uint32_t) { ++c; });
-    }
+    walk_lane<W, WALK>(a, ends, [&](W, uint32_t) { ++c; });
     const uint32_t t = block_sum(c, sh);
     if (threadIdx.x == 0 && t != 0) atomicAdd(acc, static_cast<unsigned long long>(t));
 }
 
-template <typename W>
+// Pass 2 of the build.
+template <typename W, int WALK>
 __global__ void __launch_bounds__(kBlock) k_enum_write(EnumArgs a) {
+    __shared__ uint64_t ends[kBlock + 1];
     __shared__ uint32_t sh[kBlock];
+    if (a.counts[blockIdx.x] == 0) return;
     const uint64_t lane = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    const uint64_t start = lane * kCandPerLane;
-    uint64_t mask = start < a.total ? a.marks[lane] : 0ULL;
-    const uint32_t local = block_exclusive_scan(static_cast<uint32_t>(__builtin_popcountll(mask)), sh);
-    if (mask == 0) return;
+    const uint32_t local = block_exclusive_scan(a.lane_counts[lane], sh);
     uint64_t pos = a.offsets[blockIdx.x] + local;
-    const uint32_t cnt = static_cast<uint32_t>(min<uint64_t>(kCandPerLane, a.total - start));
-    W s = first_candidate<W>(a, start);
-    for (uint32_t q = 0; q < cnt; ++q) {
-        if ((mask >> q) & 1ULL) a.reps[pos++] = static_cast<uint64_t>(s);
-        if (q + 1 < cnt) s = next_candidate<W>(a, s);
-    }
+    walk_lane<W, WALK>(a, ends, [&](W s, uint32_t st) {
+        a.reps[pos] = static_cast<uint64_t>(s);
+        a.stab[pos] = static_cast<uint16_t>(st);
+        ++pos;
+    });
 }
 
 // Single-workgroup exclusive scan of n counts (n up to a few million).
@@ -270,19 +192,6 @@ __global__ void __launch_bounds__(1024) k_scan_counts(const uint32_t *counts, ui
         run += counts[i];
     }
     if (t == 1023) *total = sh[1023];
-}
-
-template <typename W, int KIND>
-__global__ void __launch_bounds__(kBlock) k_stab(PlanDev P, const uint64_t *reps, uint64_t d, uint16_t *stab) {
-    const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (i >= d) return;
-    const W r = static_cast<W>(reps[i]);
-    uint32_t cnt = 0;
-    for_each_image<W, KIND>(P, r, [&](W v, uint32_t) {
-        cnt += v == r ? 1u : 0u;
-        return true;
-    });
-    stab[i] = static_cast<uint16_t>(cnt);
 }
 
 // buckets[k] = first index whose key reaches bucket k (k = 0 .. nb; entry
@@ -414,67 +323,63 @@ struct StreamBuf {
     }
 };
 
-template <typename W>
-void enumerate_impl(ls_basis *b, hipStream_t st, uint64_t total, uint64_t **out_reps, uint64_t *out_dim) {
-    const GroupPlan &gp = b->plan;
-    const uint64_t lanes = (total + kCandPerLane - 1) / kCandPerLane;
-    const uint64_t blocks = grid_for(lanes);
-    StreamBuf marks_b(std::max<uint64_t>(lanes, 1) * sizeof(uint64_t), st);
-    StreamBuf counts_b(std::max<uint64_t>(blocks, 1) * sizeof(uint32_t), st);
-    StreamBuf offsets_b(std::max<uint64_t>(blocks, 1) * sizeof(uint64_t), st);
-    StreamBuf total_b(sizeof(uint64_t), st);
-    uint64_t *marks = marks_b.as<uint64_t>(), *offsets = offsets_b.as<uint64_t>(), *d_total = total_b.as<uint64_t>();
-    uint32_t *counts = counts_b.as<uint32_t>();
+// Candidates of a lane.  The members crowd at the low ranks, so few candidates
+// a lane balance the walk; but a lane pays about a thousand instructions to
+// unrank its first one.  Rings: 3.4e10 candidates of the 40-spin chain take
+// 22.4 ms at 512 a lane, 24.8 at 256, 28.8 at 128, 50.6 at 32.  Members of the
+// other groups cost more each: a 6x6 build takes 45.6 ms at 512, 36.5 at 128,
+// 38.0 at 64, 43.4 at 32.
+uint32_t cand_per_lane(uint64_t candidates, int walk) {
+    const uint64_t most = walk == kWalkRing ? 512 : 128;
+    return static_cast<uint32_t>(std::min<uint64_t>(most, std::max<uint64_t>(4, candidates >> 20)));
+}
+
+// Sorted representatives and their stabilizer sizes.
+template <typename W, int WALK>
+void enumerate_impl(ls_basis *b, hipStream_t st, uint64_t total) {
     EnumArgs a{};
     a.plan = b->plan_dev;
     a.binom = b->d_binom;
+    a.begin = 0;
     a.total = total;
-    a.n_sites = gp.n_sites;
+    a.per_lane = cand_per_lane(total, WALK);
+    a.n_sites = b->plan.n_sites;
     a.weight = b->weight;
-    a.marks = marks;
-    a.counts = counts;
-    a.offsets = offsets;
-    const int kind = orbit_kind<W>(gp);
-    if (blocks > 0) {
-        if (kind == kOrbitRing32)
-            hipLaunchKernelGGL((k_enum_mark<W, kOrbitRing32>), dim3(blocks), dim3(kBlock), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_enum_mark<W, kOrbitGeneric>), dim3(blocks), dim3(kBlock), 0, st, a);
-        LS_HIP_CHECK(hipGetLastError());
-        hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, st, counts, blocks, offsets, d_total);
-        LS_HIP_CHECK(hipGetLastError());
-    }
+    const uint64_t lanes = (total + a.per_lane - 1) / a.per_lane;
+    const uint64_t blocks = grid_for(lanes);
+    StreamBuf lanes_b(std::max<uint64_t>(blocks, 1) * kBlock * sizeof(uint32_t), st);
+    StreamBuf counts_b(std::max<uint64_t>(blocks, 1) * sizeof(uint32_t), st);
+    StreamBuf offsets_b(std::max<uint64_t>(blocks, 1) * sizeof(uint64_t), st);
+    StreamBuf total_b(sizeof(uint64_t), st);
+    a.lane_counts = lanes_b.as<uint32_t>();
+    a.counts = counts_b.as<uint32_t>();
+    a.offsets = offsets_b.as<uint64_t>();
     uint64_t dim = 0;
     if (blocks > 0) {
-        LS_HIP_CHECK(hipMemcpyAsync(&dim, d_total, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
+        hipLaunchKernelGGL((k_enum_mark<W, WALK>), dim3(blocks), dim3(kBlock), 0, st, a);
+        LS_HIP_CHECK(hipGetLastError());
+        hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, st, a.counts, blocks, offsets_b.as<uint64_t>(),
+                           total_b.as<uint64_t>());
+        LS_HIP_CHECK(hipGetLastError());
+        LS_HIP_CHECK(hipMemcpyAsync(&dim, total_b.p, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
         LS_HIP_CHECK(hipStreamSynchronize(st));
     }
-    uint64_t *reps = dev_alloc_n<uint64_t>(std::max<uint64_t>(dim, 1), st);
-    a.reps = reps;
-    hipError_t e = hipSuccess;
+    if (dim >= 0xFFFFFFFFull) throw Error{LS_EINVAL, "basis dimension must be below 2^32 - 1"};
+    b->d_reps = dev_alloc_n<uint64_t>(std::max<uint64_t>(dim, 1), st);
+    b->d_stab = dev_alloc_n<uint16_t>(std::max<uint64_t>(dim, 1), st);
+    a.reps = b->d_reps;
+    a.stab = b->d_stab;
     if (dim > 0) {
-        hipLaunchKernelGGL((k_enum_write<W>), dim3(blocks), dim3(kBlock), 0, st, a);
-        e = hipGetLastError();
+        hipLaunchKernelGGL((k_enum_write<W, WALK>), dim3(blocks), dim3(kBlock), 0, st, a);
+        LS_HIP_CHECK(hipGetLastError());
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) {
-        dev_free(reps, st);
-        LS_HIP_CHECK(e);
-    }
-    *out_reps = reps;
-    *out_dim = dim;
+    b->dim = dim;
 }
 
-template <typename W>
-void stab_impl(ls_basis *b, hipStream_t st) {
-    if (b->dim == 0) return;
-    if (orbit_kind<W>(b->plan) == kOrbitRing32)
-        hipLaunchKernelGGL((k_stab<W, kOrbitRing32>), dim3(grid_for(b->dim)), dim3(kBlock), 0, st, b->plan_dev,
-                           b->d_reps, b->dim, b->d_stab);
-    else
-        hipLaunchKernelGGL((k_stab<W, kOrbitGeneric>), dim3(grid_for(b->dim)), dim3(kBlock), 0, st, b->plan_dev,
-                           b->d_reps, b->dim, b->d_stab);
-    LS_HIP_CHECK(hipGetLastError());
+template <int WALK>
+void enumerate_words(ls_basis *b, hipStream_t st, uint64_t total) {
+    if (b->plan.n_sites <= 32) enumerate_impl<uint32_t, WALK>(b, st, total);
+    else enumerate_impl<uint64_t, WALK>(b, st, total);
 }
 
 uint64_t host_binom(uint32_t n, uint32_t k) {
@@ -538,6 +443,7 @@ void fill_plan_dev(const GroupPlan &gp, PlanDev &pd) {
     pd.full = gp.full;
     pd.col0 = gp.col0;
     pd.pair_lut = nullptr;
+    pd.skip = nullptr;
     for (int a = 0; a < 8; ++a) pd.col_ge[a] = gp.col_ge[a];
     pd.n_stab_cls = 0;
     pd.stab_cls = nullptr;
@@ -579,6 +485,8 @@ void upload_plan(ls_basis *b, hipStream_t st) {
     LS_HIP_CHECK(hipMemcpyAsync(b->d_cosets, gp.cosets.data(), ncos * sizeof(CosetRep), hipMemcpyHostToDevice, st));
     b->d_chi = dev_alloc_n<double2>(gp.n_elements, st);
     LS_HIP_CHECK(hipMemcpyAsync(b->d_chi, gp.chi.data(), gp.n_elements * sizeof(double2), hipMemcpyHostToDevice, st));
+    b->d_skip = dev_alloc_n<uint8_t>(gp.skip.size(), st);
+    LS_HIP_CHECK(hipMemcpyAsync(b->d_skip, gp.skip.data(), gp.skip.size(), hipMemcpyHostToDevice, st));
     b->d_chi_one = dev_alloc_n<uint32_t>(gp.chi_one.size(), st);
     LS_HIP_CHECK(hipMemcpyAsync(b->d_chi_one, gp.chi_one.data(), gp.chi_one.size() * sizeof(uint32_t),
                                 hipMemcpyHostToDevice, st));
@@ -587,6 +495,7 @@ void upload_plan(ls_basis *b, hipStream_t st) {
     pd.cosets = b->d_cosets;
     pd.chi = b->d_chi;
     pd.chi_one = b->d_chi_one;
+    pd.skip = b->d_skip;
     if (gp.torus) {
         b->d_pair_lut = dev_alloc_n<uint32_t>(gp.pair_lut.size(), st);
         LS_HIP_CHECK(hipMemcpyAsync(b->d_pair_lut, gp.pair_lut.data(), gp.pair_lut.size() * sizeof(uint32_t),
@@ -623,30 +532,33 @@ __global__ void k_clear_u64(unsigned long long *p) { *p = 0ull; }
 template <typename W>
 uint64_t count_impl(const GroupPlan &gp, const PlanDev &pd, const uint64_t *binom, int32_t weight, uint64_t begin,
                     uint64_t end, unsigned long long *acc, hipStream_t st) {
-    // 64 candidates per lane as in the mark pass; a launch covers up to 2^20
-    // workgroups (1.7e10 candidates, a fraction of a second)
-    constexpr uint32_t kPerLane = kCandPerLane;
-    constexpr uint64_t kSpan = (1ull << 20) * kBlock * kPerLane;
+    // a launch covers up to 2^20 workgroups (at most 1.4e11 candidates)
+    constexpr uint64_t kSpanBlocks = 1ull << 20;
     unsigned long long total = 0;
     hipLaunchKernelGGL(k_clear_u64, dim3(1), dim3(1), 0, st, acc);
     LS_HIP_CHECK(hipGetLastError());
     EnumArgs a{};
     a.plan = pd;
     a.binom = binom;
-    a.total = end;
+    a.per_lane = cand_per_lane(end - begin, walk_kind(gp));
     a.n_sites = gp.n_sites;
     a.weight = weight;
-    const int kind = orbit_kind<W>(gp);
+    const uint64_t span = kSpanBlocks * kBlock * a.per_lane;
     for (uint64_t lo = begin; lo < end;) {
-        const uint64_t hi = end - lo > kSpan ? lo + kSpan : end;
-        const uint64_t lanes = (hi - lo + kPerLane - 1) / kPerLane;
-        const uint32_t blocks = static_cast<uint32_t>((lanes + kBlock - 1) / kBlock);
-        if (kind == kOrbitRing32)
-            hipLaunchKernelGGL((k_enum_count<W, kOrbitRing32>), dim3(blocks), dim3(kBlock), 0, st, a, lo, hi,
-                               kPerLane, acc);
-        else
-            hipLaunchKernelGGL((k_enum_count<W, kOrbitGeneric>), dim3(blocks), dim3(kBlock), 0, st, a, lo, hi,
-                               kPerLane, acc);
+        const uint64_t hi = end - lo > span ? lo + span : end;
+        a.begin = lo;
+        a.total = hi;
+        const uint64_t lanes = (hi - lo + a.per_lane - 1) / a.per_lane;
+        const uint32_t blocks = static_cast<uint32_t>(grid_for(lanes));
+        switch (walk_kind(gp)) {
+            case kWalkRing:
+                hipLaunchKernelGGL((k_enum_count<W, kWalkRing>), dim3(blocks), dim3(kBlock), 0, st, a, acc);
+                break;
+            case kWalkTorus:
+                hipLaunchKernelGGL((k_enum_count<W, kWalkTorus>), dim3(blocks), dim3(kBlock), 0, st, a, acc);
+                break;
+            default: hipLaunchKernelGGL((k_enum_count<W, kWalkImages>), dim3(blocks), dim3(kBlock), 0, st, a, acc);
+        }
         LS_HIP_CHECK(hipGetLastError());
         lo = hi;
     }
@@ -687,7 +599,9 @@ uint64_t count_members(ls_basis *b, uint64_t begin, uint64_t end, hipStream_t st
 // several processes on one GPU use separate arrays.
 
 constexpr size_t kCountScratchBytes = 256 * 1024;
-static __device__ __align__(256) unsigned char scratch[kCountScratchBytes];
+// the skip table of the walk lies after them: at most 4096 images of 64 bits
+constexpr size_t kSkipBytes = 4096 * 64;
+static __device__ __align__(256) unsigned char scratch[kCountScratchBytes + kSkipBytes];
 
 namespace {
 
@@ -739,11 +653,13 @@ uint64_t count_members_noalloc(const GroupPlan &gp, int32_t weight, uint64_t beg
     put(o_cos, gp.cosets.data(), gp.cosets.size() * sizeof(CosetRep));
     put(o_chi, gp.chi.data(), gp.chi.size() * sizeof(double));
     put(o_one, gp.chi_one.data(), gp.chi_one.size() * sizeof(uint32_t));
+    put(kCountScratchBytes, gp.skip.data(), gp.skip.size());
     PlanDev pd{};
     fill_plan_dev(gp, pd);
     pd.cosets = reinterpret_cast<const CosetRep *>(base + o_cos);
     pd.chi = reinterpret_cast<const double2 *>(base + o_chi);
     pd.chi_one = reinterpret_cast<const uint32_t *>(base + o_one);
+    pd.skip = base + kCountScratchBytes;
     if (gp.torus) {
         put(o_lut, gp.pair_lut.data(), gp.pair_lut.size() * sizeof(uint32_t));
         pd.pair_lut = reinterpret_cast<const uint32_t *>(base + o_lut);
@@ -759,15 +675,12 @@ void build_basis(ls_basis *b, hipStream_t st) {
     const uint32_t n = gp.n_sites;
     upload_plan(b, st);
 
-    // candidates
     const uint64_t total = candidate_count(b);
-    if (n <= 32) enumerate_impl<uint32_t>(b, st, total, &b->d_reps, &b->dim);
-    else enumerate_impl<uint64_t>(b, st, total, &b->d_reps, &b->dim);
-    if (b->dim >= 0xFFFFFFFFull) throw Error{LS_EINVAL, "basis dimension must be below 2^32 - 1"};
-
-    b->d_stab = dev_alloc_n<uint16_t>(std::max<uint64_t>(b->dim, 1), st);
-    if (n <= 32) stab_impl<uint32_t>(b, st);
-    else stab_impl<uint64_t>(b, st);
+    switch (walk_kind(gp)) {
+        case kWalkRing: enumerate_words<kWalkRing>(b, st, total); break;
+        case kWalkTorus: enumerate_words<kWalkTorus>(b, st, total); break;
+        default: enumerate_words<kWalkImages>(b, st, total);
+    }
 
     // search layout
     SearchDev &S = b->search_dev;

@@ -287,6 +287,7 @@ GroupPlan compile_group(const ls_sector_desc &d) {
     P.chi.assign(2 * ng, 0.0);
     P.chi_one.assign((ng + 31) / 32, 0u);
     P.code_to_index.assign(ng, -1);
+    P.skip.assign(static_cast<size_t>(P.cosets.size()) * nt * n, 0);
     std::vector<char> hit(ng, 0);
     bool trivial = true, real = true;
     for (uint32_t p = 0; p < P.cosets.size(); ++p) {
@@ -295,6 +296,13 @@ GroupPlan compile_group(const ls_sector_desc &d) {
             auto tp = trans_perm(P.lx, P.ly, t % P.lx, t / P.lx);
             std::vector<uint16_t> c(n);
             for (uint32_t i = 0; i < n; ++i) c[i] = tp[pp[i]];
+            std::vector<uint16_t> from(n);
+            for (uint32_t i = 0; i < n; ++i) from[c[i]] = static_cast<uint16_t>(i);
+            uint32_t lowest = n;
+            for (uint32_t d = n; d-- > 0;) {
+                lowest = std::min<uint32_t>(lowest, from[d]);
+                P.skip[(static_cast<size_t>(p) * nt + t) * n + d] = static_cast<uint8_t>(std::min(lowest, d));
+            }
             for (uint32_t f = 0; f < nz; ++f) {
                 const uint32_t code = (p * nt + t) * nz + f;
                 const int e = find_elem(c, static_cast<uint8_t>(d.flip[reps[p]] ^ f));

@@ -111,6 +111,9 @@ struct GroupPlan {
     std::vector<double> chi;        // [n_elements][2] by code
     std::vector<uint32_t> chi_one;  // bitset by code: chi == 1
     std::vector<int32_t> code_to_index;  // code -> index in the user's list
+    // Enumeration: for image p * |T| + t and bit d, the lowest of d and the
+    // positions the image moves to bit d or above, [n_elements / |Z|][N].
+    std::vector<uint8_t> skip;
     // Pruned torus search (lx <= 6, ly >= 2): for every pair of rows
     // q = (top << lx | second) the smallest x-rotation of the pair, as
     // entry = key << 4 | ambiguous << 3 | argmin_a, stored as
@@ -140,6 +143,7 @@ struct PlanDev {
     const double2 *chi;         // device, by code
     const uint32_t *chi_one;    // device bitset, by code
     const uint32_t *pair_lut;   // device, torus pruning table (or null)
+    const uint8_t *skip;        // device, by image and bit (enumeration only; else null)
     uint64_t col_ge[8];
     // Stabilizer-ratio table (0 classes = none): stab_cls[s] is the class of
     // the divisor s of |G|, stab_ratio[a * n_stab_cls + b] the correctly
@@ -217,6 +221,7 @@ struct ls_basis {
     double2 *d_chi = nullptr;
     uint32_t *d_chi_one = nullptr;
     uint32_t *d_pair_lut = nullptr;
+    uint8_t *d_skip = nullptr;
     void *d_stab_tab = nullptr;
     ls::PlanDev plan_dev{};
     ls::SearchDev search_dev{};

@@ -152,3 +152,37 @@ def test_table2_build_n40(golden_dir):
         assert np.array_equal(r, sample) and np.all(norm > 0)
     finally:
         b.close()
+
+
+def _walk_sector(lx, ly, w, point, k, inv):
+    """A ring (ly = 1) or torus sector: momentum k along x, mirrors with
+    character `point` (0: translations only), spin inversion `inv`."""
+    n = lx * ly
+    g = lattice.ring_group(n, k, point, inv) if ly == 1 else lattice.torus_group(
+        lx, ly, k, 0, "full" if point else "none", {"mx": point, "my": point} if point else None, inv)
+    return configs.sector_from_arrays(f"walk{lx}x{ly}_w{w}", n, w, g.perm, g.flip, g.chi,
+                                      terms.heisenberg_terms([(0, 1, 1.0)]))
+
+
+@pytest.mark.parametrize("lx,ly,w,point,k,inv", [
+    (2, 1, 1, 0, 0, 1), (3, 1, 0, 1, 0, 0), (3, 1, 3, 1, 0, 0), (11, 1, -1, 1, 0, 1), (12, 1, -1, 0, 5, 0),
+    (13, 1, 6, 1, 0, 0), (16, 1, 8, -1, 0, -1), (17, 1, 8, 0, 3, 0), (20, 1, 10, 1, 10, 1), (31, 1, 3, 1, 0, 0),
+    (32, 1, 4, 0, 16, 0), (33, 1, 4, 1, 0, 0), (63, 1, 3, 1, 0, 0), (64, 1, 3, 0, 1, 0), (2, 8, 8, 0, 1, 1),
+    (3, 5, 7, 1, 0, 0), (3, 4, -1, 1, 0, -1), (4, 4, 8, 1, 0, 1), (4, 5, 10, 0, 2, 1), (6, 3, 9, -1, 0, 1),
+    (8, 2, 8, 1, 0, 1), (6, 6, 5, 1, 0, 0), (7, 5, 4, 1, 0, 0)])
+def test_walks_match_oracle(lx, ly, w, point, k, inv):
+    """The jumping walks (rings, tori with a pair table, any group) against the
+    oracle: representatives and stabilizer sizes bit for bit, and the counts
+    of rank ranges that cut the members at odd places."""
+    sec = _walk_sector(lx, ly, w, point, k, inv)
+    _say(f"[walk] {sec.name}")
+    reps, stab = oracle.enumerate_basis(oracle.Problem(sec))
+    b = ls.ls_basis_build(sec)
+    got, gstab = b.copy()
+    assert np.array_equal(got.cpu().numpy().view(np.uint64), reps)
+    assert np.array_equal(gstab.cpu().numpy().view(np.uint16), stab)
+    b.close()
+    total = _candidates(sec)
+    ranks = np.array([_rank(sec, s) for s in reps], dtype=np.int64)
+    for lo, hi in ((0, total), (total // 7, total // 3), (total // 3, total // 3 + 1), (max(0, total - 5), total + 9)):
+        assert ls.ls_sector_count(sec, lo, hi)[0] == int(((ranks >= lo) & (ranks < hi)).sum()), (lo, hi)
