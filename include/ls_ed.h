@@ -105,12 +105,13 @@ typedef struct {
  * order, kept iff it is its orbit's minimum and P does not annihilate it).
  * The handle owns reps (uint64 [dim], strictly increasing), their
  * stabilizer sizes and the search layout used by ls_index_lookup and the
- * products (stateToIndex, Section 5.3): a hash index of 16-byte slots
- * (key, index, stabilizer size; linear probing from the key's Fibonacci
- * hash, the top bits of key * 0x9E3779B97F4A7C15; load factor at most 1/8
- * while the table fits 8 GiB, else 1/4 within 64 GiB, else 1/2 or 3/4
- * within 128 GiB), or, where it would pass 128 GiB or the
- * environment variable LS_ED_SEARCH is "buckets" at build time, a bucket
+ * products (stateToIndex, Section 5.3): a hash index over blocks of
+ * consecutive keys (16 bytes a block: a bit for every key the block can
+ * hold, and the position of the first; eight blocks to a 128-byte line,
+ * linear probing over lines from the Fibonacci hash of the block group,
+ * the top bits of group * 0x9E3779B97F4A7C15; load at most 1/4, in sparse
+ * sectors 1/2 or 3/4), or, where it would pass 128 GiB or the environment
+ * variable LS_ED_SEARCH is "buckets" at build time, a bucket
  * table over the keys' high bits with binary search in reps.  A group of
  * one element needs neither (colex rank, or the state itself).
  * Blocks until the build on `stream` has finished.  Indices are 32-bit:
@@ -183,7 +184,7 @@ void ls_basis_destroy(ls_basis *basis);
  * changed for good: use it on a basis built for the purpose.  Blocks until
  * done on `stream`.
  * Errors: LS_EINVAL (NULL basis, index >= dim, a search layout other than
- * the hash index, or no unused key value above the representatives).      */
+ * the hash index, or 1023 keys dropped before).                           */
 ls_status ls_basis_test_drop_key(ls_basis *basis, uint64_t index, void *stream);
 
 /* Per state: its representative (orbit minimum), the character chi(g*) of

@@ -107,6 +107,8 @@ void free_basis(ls_basis *b) {
     ls::dev_free(b->d_reps);
     ls::dev_free(b->d_stab);
     ls::dev_free(b->d_skip);
+    ls::dev_free(b->d_low_rank);
+    ls::dev_free(b->d_dropped);
     ls::dev_free(b->d_buckets);
     ls::dev_free(b->d_table);
     ls::dev_free(b->d_binom);

@@ -213,42 +213,77 @@ __global__ void __launch_bounds__(kBlock) k_buckets(const uint64_t *reps, uint64
     buckets[k] = static_cast<uint32_t>(lo);
 }
 
-// Hash index insert: keys are distinct, so each claims the first free slot
-// of its probe sequence with a compare-and-swap; the table has more slots
-// than keys, so every sequence ends.
-__global__ void __launch_bounds__(kBlock) k_hash_insert(const uint64_t *reps, const uint16_t *stab, uint64_t d,
-                                                        HashSlot *table, uint64_t mask, uint32_t shift) {
+__global__ void k_clear_u64(unsigned long long *p) { *p = 0ull; }
+
+// Groups of the hash index among the sorted representatives (integer atomic
+// adds: the total does not depend on their order).
+__global__ void __launch_bounds__(kBlock) k_count_groups(const uint64_t *reps, uint64_t d, uint32_t shift,
+                                                         unsigned long long *total) {
+    __shared__ uint32_t sh[kBlock];
     const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (i >= d) return;
-    const uint64_t key = reps[i];
-    uint64_t s = slot_of(key, shift);
+    const bool head = i < d && (i == 0 || (reps[i] >> shift) != (reps[i - 1] >> shift));
+    const uint32_t c = block_sum(head ? 1u : 0u, sh);
+    if (threadIdx.x == 0 && c != 0) atomicAdd(total, static_cast<unsigned long long>(c));
+}
+
+// Hash index: the first representative of every group claims the first free
+// line of the group's probe sequence with a compare-and-swap (groups are
+// distinct and the table has more lines than groups, so every sequence ends)
+// and fills its eight blocks.
+__global__ void __launch_bounds__(kBlock) k_index_fill(SearchDev S, IndexBlock *table) {
+    const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    if (i >= S.dim) return;
+    const uint32_t shift = S.low_bits + kGroupBits;
+    uint64_t key = S.reps[i];
+    const uint64_t g = key >> shift;
+    if (i > 0 && (S.reps[i - 1] >> shift) == g) return;
+    const uint32_t tag = static_cast<uint32_t>(g);
+    uint64_t line = line_of(g, S.hash_shift);
     for (;;) {
-        const unsigned long long prev =
-            atomicCAS(reinterpret_cast<unsigned long long *>(&table[s].key), static_cast<unsigned long long>(kEmptyKey),
-                      static_cast<unsigned long long>(key));
-        if (prev == kEmptyKey) {
-            table[s].idx = static_cast<uint32_t>(i);
-            table[s].stab = stab[i];
-            return;
+        // tag and position of the line's first block: ~0 while it is free
+        unsigned long long *w = reinterpret_cast<unsigned long long *>(&table[line << kGroupBits].base);
+        const unsigned long long mine = static_cast<unsigned long long>(tag) << 32 | static_cast<uint32_t>(i);
+        if (atomicCAS(w, ~0ull, mine) == ~0ull) break;
+        line = (line + 1) & S.hash_mask;
+    }
+    const uint64_t hi = (g >> 32) << kBlockTagHi;
+    uint64_t j = i;
+    for (uint32_t b = 0; b < (1u << kGroupBits); ++b) {
+        uint64_t bits = hi, stab = 0;
+        const uint32_t base = static_cast<uint32_t>(j);
+        bool one = true;
+        for (; j < S.dim; ++j) {
+            key = S.reps[j];
+            if ((key >> shift) != g || ((key >> S.low_bits) & ((1u << kGroupBits) - 1)) != b) break;
+            bits |= 1ull << low_rank(S, key);
+            const uint64_t st = S.stab[j];
+            if (stab == 0) stab = st;
+            one = one && st == stab;
         }
-        s = (s + 1) & mask;
+        if (one) bits |= stab << kBlockKeys;
+        IndexBlock &B = table[line << kGroupBits | b];
+        B.bits = bits;
+        B.base = base;
+        B.tag = tag;
     }
 }
 
-// Test hook: the slot holding `key` gets `repl`, a key above every
-// representative (lookups above kmax stop before probing), so the slot stays
-// occupied, the probe sequences through it still end, and `key` misses.
-// One thread; the walk is bounded by the table size.
-__global__ void k_drop_key(HashSlot *table, uint64_t mask, uint32_t shift, uint64_t key, uint64_t repl) {
-    uint64_t s = slot_of(key, shift);
-    for (uint64_t n = 0; n <= mask; ++n) {
-        const uint64_t k = table[s].key;
-        if (k == key) {
-            table[s].key = repl;
+// Test hook: `key` joins the dropped keys and its block gets the mark that
+// makes lookups compare with them.  One thread; the walk is bounded by the
+// table size.
+__global__ void k_drop_key(SearchDev S, IndexBlock *table, uint64_t *dropped, uint64_t key) {
+    const uint64_t g = key >> (S.low_bits + kGroupBits);
+    const uint64_t blk = (key >> S.low_bits) & ((1u << kGroupBits) - 1);
+    uint64_t line = line_of(g, S.hash_shift);
+    for (uint64_t n = 0; n <= S.hash_mask; ++n) {
+        IndexBlock &B = table[line << kGroupBits | blk];
+        if (B.tag == static_cast<uint32_t>(g) && (B.bits >> kBlockTagHi) == (g >> 32)) {
+            dropped[++dropped[0]] = key;
+            B.bits &= ~(((1ull << kBlockStabBits) - 1) << kBlockKeys);
+            B.bits |= 1ull << kBlockDropped;
             return;
         }
-        if (k == kEmptyKey) return;
-        s = (s + 1) & mask;
+        line = (line + 1) & S.hash_mask;
     }
 }
 
@@ -391,23 +426,31 @@ uint64_t host_binom(uint32_t n, uint32_t k) {
 
 }  // namespace
 
-// Binomial table and the compiled group in device memory (PlanDev).
-// Slots of the hash index, a power of two: load factor at most 1/8 while the
-// table fits 8 GiB, else 1/4 within 64 GiB, else 1/2 or 3/4 within 128 GiB;
-// 0 above that.  A sparse table makes a second probe (a second dependent
-// memory round trip) rare: load 1/2 -> 1/8 took the 6x6 product from 40.0 to
-// 36.7 ms, load 0.4 -> 0.2 the 40-spin chain product from 442 to 421 ms, and
-// load 0.75 -> 0.37 (a 128 GiB table) the 42-spin chain product from 2425
-// to 1756 ms.
-uint64_t hash_capacity(uint64_t dim) {
+// Lines of the hash index, a power of two: load at most 1/4, or 1/2 or 3/4
+// where that would pass the bytes a table of one 16-byte slot a key takes at
+// load 1/8 within 8 GiB, 1/4 within 64 GiB and 3/4 within 128 GiB (dense
+// sectors hold about 20 keys a line and stay far below; the admission of the
+// serving loop reserves those bytes); 0: over 128 GiB.
+uint64_t index_lines(uint64_t dim, uint64_t groups) {
     struct Tier {
         uint64_t num, den, limit;   // slots >= dim * num / den while slots * 16 <= limit
     };
     const Tier tiers[] = {{8, 1, 8ULL << 30}, {4, 1, 64ULL << 30}, {2, 1, 128ULL << 30}, {4, 3, 128ULL << 30}};
+    uint64_t room = 128ULL << 30;
     for (const Tier &t : tiers) {
         uint64_t cap = 1024;
         while (cap * t.den < t.num * dim) cap <<= 1;
-        if (cap * sizeof(HashSlot) <= t.limit) return cap;
+        if (cap * 16 <= t.limit) {
+            room = cap * 16;
+            break;
+        }
+    }
+    constexpr uint64_t line = sizeof(IndexBlock) << kGroupBits;
+    const uint64_t load[3][2] = {{4, 1}, {2, 1}, {4, 3}};
+    for (int k = 0; k < 3; ++k) {
+        uint64_t lines = 8;
+        while (lines * load[k][1] < load[k][0] * groups) lines <<= 1;
+        if (lines * line <= (k < 2 ? room : 128ULL << 30)) return lines;
     }
     return 0;
 }
@@ -523,8 +566,6 @@ uint64_t candidate_count(const ls_basis *b) {
 }
 
 namespace {
-
-__global__ void k_clear_u64(unsigned long long *p) { *p = 0ull; }
 
 // Members among the candidates of rank [begin, end) (end within range),
 // accumulated into *acc (device, 8 bytes; cleared here by a fill kernel);
@@ -702,23 +743,49 @@ void build_basis(ls_basis *b, hipStream_t st) {
         }
         S.kmin = kmin;
         S.kmax = kmax;
-        // Hash index (hash_capacity); when it would pass 128 GiB, or when asked
+        // Hash index (index_lines); when it would pass 128 GiB, or when asked
         // for, the bucket search.
         const char *env = std::getenv("LS_ED_SEARCH");
         const bool want_buckets = env != nullptr && std::string(env) == "buckets";
-        const uint64_t cap = hash_capacity(b->dim);
-        if (!want_buckets && cap != 0 && kmax != kEmptyKey) {
-            S.mode = kLookupHash;
-            S.hash_mask = cap - 1;
-            S.hash_shift = 64;
-            for (uint64_t c = cap; c > 1; c >>= 1) --S.hash_shift;
-            b->d_table = dev_alloc_n<HashSlot>(cap, st);
-            LS_HIP_CHECK(hipMemsetAsync(b->d_table, 0xFF, cap * sizeof(HashSlot), st));
+        S.low_bits = b->weight >= 0 ? 7 : 5;
+        const uint32_t shift = S.low_bits + kGroupBits;
+        uint64_t lines = 0;
+        if (!want_buckets && kmax != kEmptyKey && (kmax >> shift) <= kMaxGroup) {
+            StreamBuf groups_b(sizeof(uint64_t), st);
+            unsigned long long *d_groups = groups_b.as<unsigned long long>(), groups = 0;
+            hipLaunchKernelGGL(k_clear_u64, dim3(1), dim3(1), 0, st, d_groups);
             if (b->dim > 0)
-                hipLaunchKernelGGL(k_hash_insert, dim3(grid_for(b->dim)), dim3(kBlock), 0, st, b->d_reps, b->d_stab,
-                                   b->dim, b->d_table, S.hash_mask, S.hash_shift);
+                hipLaunchKernelGGL(k_count_groups, dim3(grid_for(b->dim)), dim3(kBlock), 0, st, b->d_reps, b->dim,
+                                   shift, d_groups);
             LS_HIP_CHECK(hipGetLastError());
+            LS_HIP_CHECK(hipMemcpyAsync(&groups, d_groups, sizeof(groups), hipMemcpyDeviceToHost, st));
+            LS_HIP_CHECK(hipStreamSynchronize(st));
+            lines = index_lines(b->dim, groups);
+        }
+        if (lines != 0) {
+            S.mode = kLookupHash;
+            S.hash_mask = lines - 1;
+            S.hash_shift = 64;
+            for (uint64_t c = lines; c > 1; c >>= 1) --S.hash_shift;
+            // a key's number in its block: its low bits, or their rank among
+            // those of their popcount
+            uint8_t rank[128] = {}, next[8] = {};
+            for (uint32_t v = 0; v < (1u << S.low_bits); ++v)
+                rank[v] = b->weight >= 0 ? next[__builtin_popcount(v)]++ : static_cast<uint8_t>(v);
+            b->d_low_rank = dev_alloc_n<uint8_t>(sizeof(rank), st);
+            LS_HIP_CHECK(hipMemcpyAsync(b->d_low_rank, rank, sizeof(rank), hipMemcpyHostToDevice, st));
+            b->d_dropped = dev_alloc_n<uint64_t>(1 + kMaxDropped, st);
+            hipLaunchKernelGGL(k_clear_u64, dim3(1), dim3(1), 0, st,
+                               reinterpret_cast<unsigned long long *>(b->d_dropped));
+            b->d_table = dev_alloc_n<IndexBlock>(lines << kGroupBits, st);
+            LS_HIP_CHECK(hipMemsetAsync(b->d_table, 0xFF, (lines << kGroupBits) * sizeof(IndexBlock), st));
             S.table = b->d_table;
+            S.low_rank = b->d_low_rank;
+            S.stab = b->d_stab;
+            S.dropped = b->d_dropped;
+            if (b->dim > 0)
+                hipLaunchKernelGGL(k_index_fill, dim3(grid_for(b->dim)), dim3(kBlock), 0, st, S, b->d_table);
+            LS_HIP_CHECK(hipGetLastError());
             LS_HIP_CHECK(hipStreamSynchronize(st));
             return;
         }
@@ -744,11 +811,12 @@ void build_basis(ls_basis *b, hipStream_t st) {
 void drop_key(ls_basis *b, uint64_t index, hipStream_t st) {
     const SearchDev &S = b->search_dev;
     LS_REQUIRE(S.mode == kLookupHash, "only a hash search layout can drop a key");
-    LS_REQUIRE(S.kmax + 1 != kEmptyKey, "no free key value above the representatives");
+    LS_REQUIRE(b->n_dropped < kMaxDropped, "no more keys can be dropped");
     uint64_t key = 0;
     LS_HIP_CHECK(hipMemcpyAsync(&key, b->d_reps + index, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
     LS_HIP_CHECK(hipStreamSynchronize(st));
-    hipLaunchKernelGGL(k_drop_key, dim3(1), dim3(1), 0, st, b->d_table, S.hash_mask, S.hash_shift, key, S.kmax + 1);
+    hipLaunchKernelGGL(k_drop_key, dim3(1), dim3(1), 0, st, S, b->d_table, b->d_dropped, key);
+    ++b->n_dropped;
     LS_HIP_CHECK(hipGetLastError());
     LS_HIP_CHECK(hipStreamSynchronize(st));
 }

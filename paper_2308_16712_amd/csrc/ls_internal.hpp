@@ -173,13 +173,31 @@ enum LookupMode : uint32_t {
 };
 constexpr uint32_t kMaxStagedBits = 13;   // staged tables: at most 2^13 + 1 entries (32 KiB)
 
-// One slot of the hash index: a representative, its position in the sorted
-// array and its stabilizer size, read with one 16-byte load.
-struct alignas(16) HashSlot {
-    uint64_t key;       // kEmptyKey when free
-    uint32_t idx;
-    uint32_t stab;
+// Hash index.  The keys are taken in blocks of 2^kLow consecutive values (7
+// low bits with a fixed Hamming weight, 5 without), eight blocks to a group.
+// A group is one 128-byte line of the table, found by linear probing over
+// lines from the group's Fibonacci hash; a block is one 16-byte entry of it:
+// which of its keys are representatives, one bit each (with a fixed weight
+// the block's keys have low bits of one popcount: at most C(7,3) = 35 of
+// them, numbered in increasing order), and the position of the first in the
+// sorted array.  The position of a key is the number of bits below its own,
+// and it is exact: no key is compared.  One 16-byte read finds it, and the
+// neighbours of neighbouring rows share lines, as they share lines of x.
+// A table of one 16-byte slot a key (load 1/8, no locality) cost the products
+// one 128-byte line of the fabric per element (5.7e10 lines/s whatever the
+// table's size): 38-spin chain 106 -> 75 ms, 32-site ring 1.87 -> 1.34 ms, 6x6
+// torus 36.5 -> 30.6 ms, and 0.4 GB of table for 6x6 instead of 2 GiB.
+struct alignas(16) IndexBlock {
+    uint64_t bits;      // [0, 36) members, [36, 49) stabilizer size of all of
+                        // them (0: read the array), 49: a dropped key, [50, 64)
+                        // bits 32 and up of the group
+    uint32_t base;      // position of the first member
+    uint32_t tag;       // low 32 bits of the group; a free line is all ones
 };
+constexpr uint32_t kBlockKeys = 36, kBlockStabBits = 13, kBlockDropped = 49, kBlockTagHi = 50;
+constexpr uint32_t kGroupBits = 3;                        // blocks of a group: 2^3
+constexpr uint64_t kMaxGroup = (1ULL << 46) - 2;
+constexpr uint32_t kMaxDropped = 1023;                    // keys the test hook can drop
 constexpr uint64_t kEmptyKey = ~0ULL;
 
 struct SearchDev {
@@ -188,15 +206,19 @@ struct SearchDev {
     uint32_t shift;     // bucket = (key - kmin) >> shift
     int32_t weight;     // for rank / identity validation
     uint32_t n_sites;
-    uint32_t hash_shift;        // slot = (key * golden) >> hash_shift (hash mode)
+    uint32_t hash_shift;        // line = (group * golden) >> hash_shift (hash mode)
     uint32_t n_bkt;             // entries of the bucket table (staged mode)
+    uint32_t low_bits, pad_;    // key bits inside a block (hash mode)
     uint64_t dim;
     uint64_t kmin, kmax;
     const uint64_t *reps;       // device [dim]
     const uint32_t *buckets;    // device [2^bits + 1]
     const uint64_t *binom;      // device [65][65]
-    const HashSlot *table;      // device [hash_mask + 1] (hash mode)
-    uint64_t hash_mask;
+    const IndexBlock *table;    // device [(hash_mask + 1) << kGroupBits] (hash mode)
+    uint64_t hash_mask;         // lines - 1
+    const uint8_t *low_rank;    // device [1 << low_bits], number of a key in its block
+    const uint16_t *stab;       // device [dim]
+    const uint64_t *dropped;    // device: count, then the keys the test hook dropped
 };
 
 }  // namespace ls
@@ -215,7 +237,10 @@ struct ls_basis {
     uint64_t *d_reps = nullptr;
     uint16_t *d_stab = nullptr;
     uint32_t *d_buckets = nullptr;
-    ls::HashSlot *d_table = nullptr;
+    ls::IndexBlock *d_table = nullptr;
+    uint8_t *d_low_rank = nullptr;
+    uint64_t *d_dropped = nullptr;
+    uint32_t n_dropped = 0;
     uint64_t *d_binom = nullptr;
     ls::CosetRep *d_cosets = nullptr;
     double2 *d_chi = nullptr;

@@ -318,8 +318,8 @@ __device__ __forceinline__ int64_t lookup_stab(const MatvecJob &a, const LdsTabl
 // Rows as run_rows, for the searches that are cheap next to the memory
 // latency of the lookup (rings and the generic walk): the element loop is
 // software-pipelined one element deep.  An iteration searches element e+1 and
-// issues the load of its home hash slot, then finishes element e, whose slot
-// load was issued one search earlier.  Elements are still accumulated one by
+// issues the read of its block of the hash index, then finishes element e,
+// whose block was read one search earlier.  Elements are still accumulated one by
 // one in term order, so the sums (and their bits) are those of run_rows.
 template <typename W, int KIND, int CHI, bool CPLX, int NR, uint32_t LX, uint32_t LY, uint32_t NZ, bool STAGED>
 __device__ __forceinline__ void run_rows_ahead(const MatvecJob &a, const LdsTables &L, uint64_t row0,
@@ -353,27 +353,28 @@ __device__ __forceinline__ void run_rows_ahead(const MatvecJob &a, const LdsTabl
     };
     begin_row();
 
-    // the element whose home-slot load is in flight
+    // the element whose block is being read
     bool pend = false;
-    uint64_t p_rep = 0, p_slot = 0;
-    uint32_t p_code = 0, p_t = 0;
+    uint64_t p_rep = 0, p_line = 0;
+    uint32_t p_code = 0, p_t = 0, p_q = 0;
     uint4 p_e = make_uint4(0u, 0u, 0u, 0u);
 
     for (;;) {
         while (t < a.n_terms && (r & sterm[t].sel) != sterm[t].val) ++t;
         const bool more = t < a.n_terms;
-        // stage 1: search the next element, issue its home-slot load
-        uint64_t n_rep = 0, n_slot = 0;
-        uint32_t n_code = 0;
+        // stage 1: search the next element, issue the read of its block
+        uint64_t n_rep = 0, n_line = 0;
+        uint32_t n_code = 0, n_q = 0;
         uint4 n_e = make_uint4(0u, 0u, 0u, 0u);
         bool n_live = false;
         if (more) {
             n_rep = static_cast<uint64_t>(neighbour_rep<W, KIND, TRACK, LX, LY, NZ>(a, L, r, pr, t, n_code));
             if (hash) {
-                n_live = n_rep >= S.kmin && n_rep <= S.kmax;   // outside: not in the basis
+                n_live = n_rep <= S.kmax;   // above: not in the basis
                 if (n_live) {
-                    n_slot = slot_of(n_rep, S.hash_shift);
-                    n_e = *reinterpret_cast<const uint4 *>(S.table + n_slot);
+                    n_line = line_of(n_rep >> (S.low_bits + kGroupBits), S.hash_shift);
+                    n_e = load_block(S, n_line, n_rep);
+                    n_q = low_rank(S, n_rep);
                 } else {
                     lookup_miss<W, KIND, CHI>(a, static_cast<W>(n_rep));
                 }
@@ -386,22 +387,7 @@ __device__ __forceinline__ void run_rows_ahead(const MatvecJob &a, const LdsTabl
             int64_t j;
             uint32_t st_j = 0;
             if (hash) {
-                uint64_t sl = p_slot;
-                uint4 e = p_e;
-                for (;;) {
-                    const uint64_t key = static_cast<uint64_t>(e.x) | (static_cast<uint64_t>(e.y) << 32);
-                    if (key == p_rep) {
-                        j = static_cast<int64_t>(e.z);
-                        st_j = e.w;
-                        break;
-                    }
-                    if (key == kEmptyKey) {
-                        j = -1;
-                        break;
-                    }
-                    sl = (sl + 1) & S.hash_mask;
-                    e = *reinterpret_cast<const uint4 *>(S.table + sl);
-                }
+                j = resolve_block(S, p_rep, p_line, p_e, p_q, st_j);
             } else {
                 j = lookup_stab<STAGED>(a, L, p_rep, st_j);
             }
@@ -425,7 +411,8 @@ __device__ __forceinline__ void run_rows_ahead(const MatvecJob &a, const LdsTabl
         }
         pend = n_live;
         p_rep = n_rep;
-        p_slot = n_slot;
+        p_line = n_line;
+        p_q = n_q;
         p_code = n_code;
         p_t = t;
         p_e = n_e;

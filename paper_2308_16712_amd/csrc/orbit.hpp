@@ -512,26 +512,57 @@ __device__ __forceinline__ uint64_t colex_rank(uint64_t s, const uint64_t *tab) 
     return r;
 }
 
-// Home slot of a key in a hash index of 2^(64 - shift) slots: Fibonacci
-// hashing (the top bits of key * 2^64/phi), so every key bit moves the slot.
-__host__ __device__ __forceinline__ uint64_t slot_of(uint64_t key, uint32_t shift) {
-    return (key * 0x9E3779B97F4A7C15ULL) >> shift;
+// Home line of a group of key blocks in a hash index of 2^(64 - shift) lines:
+// Fibonacci hashing (the top bits of group * 2^64/phi).
+__host__ __device__ __forceinline__ uint64_t line_of(uint64_t group, uint32_t shift) {
+    return (group * 0x9E3779B97F4A7C15ULL) >> shift;
 }
 
-// Hash index: linear probing from the key's slot; the table always has free
-// slots, so every probe sequence ends.  One 16-byte load per probe.
-__device__ __forceinline__ int64_t lookup_hash(const SearchDev &S, uint64_t key, uint32_t &stab) {
-    uint64_t s = slot_of(key, S.hash_shift);
-    for (;;) {
-        const uint4 e = *reinterpret_cast<const uint4 *>(S.table + s);
-        const uint64_t k = static_cast<uint64_t>(e.x) | (static_cast<uint64_t>(e.y) << 32);
-        if (k == key) {
-            stab = e.w;
-            return static_cast<int64_t>(e.z);
-        }
-        if (k == kEmptyKey) return -1;
-        s = (s + 1) & S.hash_mask;
+// One probe of the hash index: the entry of the key's block in line `line`.
+__device__ __forceinline__ uint4 load_block(const SearchDev &S, uint64_t line, uint64_t key) {
+    const uint64_t blk = (key >> S.low_bits) & ((1u << kGroupBits) - 1);
+    return *reinterpret_cast<const uint4 *>(S.table + (line << kGroupBits | blk));
+}
+
+// Number of a key among the keys its block can hold.
+__device__ __forceinline__ uint32_t low_rank(const SearchDev &S, uint64_t key) {
+    return S.low_rank[static_cast<uint32_t>(key) & ((1u << S.low_bits) - 1)];
+}
+
+// Position and stabilizer size of a key from the probe e of its home line
+// (further lines are read where another group holds it), q = low_rank(key);
+// -1: not a representative.  The table always has free lines, so every probe
+// sequence ends.
+__device__ __forceinline__ int64_t resolve_block(const SearchDev &S, uint64_t key, uint64_t line, uint4 e, uint32_t q,
+                                                 uint32_t &stab) {
+    const uint64_t g = key >> (S.low_bits + kGroupBits);
+    const uint32_t g_lo = static_cast<uint32_t>(g), g_hi = static_cast<uint32_t>(g >> 32);
+    while (e.w != g_lo || (e.y >> (kBlockTagHi - 32)) != g_hi) {
+        if ((e.w & e.z) == 0xFFFFFFFFu) return -1;      // a free line (no position is ~0)
+        line = (line + 1) & S.hash_mask;
+        e = load_block(S, line, key);
     }
+    // the members up to and with the key, the key on top
+    const uint64_t members = static_cast<uint64_t>(e.x) | static_cast<uint64_t>(e.y & ((1u << (kBlockKeys - 32)) - 1)) << 32;
+    const uint64_t upto = members << (63u - q);
+    if (static_cast<int64_t>(upto) >= 0) return -1;
+    const uint32_t idx = e.z + static_cast<uint32_t>(__builtin_popcountll(upto)) - 1u;
+    stab = (e.y >> (kBlockKeys - 32)) & ((1u << kBlockStabBits) - 1);
+    int64_t found = static_cast<int64_t>(idx);
+    if (stab == 0) {
+        // or'ed, not returned from the loop: for an early return hipcc
+        // (ROCm 7.2) overwrites the position of the lanes that go on
+        if ((e.y >> (kBlockDropped - 32)) & 1u)
+            for (uint64_t k = 1; k <= S.dropped[0]; ++k) found |= S.dropped[k] == key ? -1ll : 0ll;
+        stab = S.stab[idx];
+    }
+    return found;
+}
+
+__device__ __forceinline__ int64_t lookup_hash(const SearchDev &S, uint64_t key, uint32_t &stab) {
+    const uint64_t line = line_of(key >> (S.low_bits + kGroupBits), S.hash_shift);
+    const uint4 e = load_block(S, line, key);
+    return resolve_block(S, key, line, e, low_rank(S, key), stab);
 }
 
 // Binary search for key among reps[lo, end) (one bucket of the sorted array).
@@ -548,7 +579,8 @@ __device__ __forceinline__ int64_t search_bucket(const uint64_t *reps, uint32_t 
 // search, or the colex rank (U(1) without lattice symmetry).
 __device__ __forceinline__ int64_t lookup_index(const SearchDev &S, uint64_t key) {
     if (S.mode == kLookupHash) {
-        if (key < S.kmin || key > S.kmax) return -1;
+        // a block's numbering holds for keys of the sector's weight only
+        if (key < S.kmin || key > S.kmax || (S.weight >= 0 && __builtin_popcountll(key) != S.weight)) return -1;
         uint32_t st;
         return lookup_hash(S, key, st);
     }
@@ -572,11 +604,12 @@ __device__ __forceinline__ int64_t lookup_staged(const SearchDev &S, const uint3
     return search_bucket(S.reps, lb[b], lb[b + 1], key);
 }
 
-// Index and stabilizer size of a key (the hash index holds both in one slot).
+// Index and stabilizer size of a key of the sector's weight (terms conserve
+// it; the hash index holds both in one entry).
 __device__ __forceinline__ int64_t lookup_index_stab(const SearchDev &S, uint64_t key, const uint16_t *stab_arr,
                                                      uint32_t &stab) {
     if (S.mode == kLookupHash) {
-        if (key < S.kmin || key > S.kmax) return -1;
+        if (key > S.kmax) return -1;
         return lookup_hash(S, key, stab);
     }
     const int64_t j = lookup_index(S, key);
