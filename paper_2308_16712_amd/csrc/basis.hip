@@ -485,12 +485,37 @@ void fill_plan_dev(const GroupPlan &gp, PlanDev &pd) {
     pd.n_elements = gp.n_elements;
     pd.full = gp.full;
     pd.col0 = gp.col0;
-    pd.pair_lut = nullptr;
+    pd.pair_lut = pd.pair_arg = pd.op_code = nullptr;
+    pd.bases = nullptr;
+    pd.n_base = static_cast<uint32_t>(gp.base_coset.size());
+    pd.op_flips = gp.op_flips;
     pd.skip = nullptr;
     for (int a = 0; a < 8; ++a) pd.col_ge[a] = gp.col_ge[a];
     pd.n_stab_cls = 0;
     pd.stab_cls = nullptr;
     pd.stab_ratio = nullptr;
+}
+
+// Tables of the torus search, in one block: base images, pair table, argument
+// table, codes of the operations.
+std::vector<unsigned char> torus_tables(const GroupPlan &gp) {
+    std::vector<unsigned char> t;
+    auto add = [&](const void *p, size_t bytes) {
+        const unsigned char *c = static_cast<const unsigned char *>(p);
+        t.insert(t.end(), c, c + bytes);
+    };
+    for (uint32_t p : gp.base_coset) add(&gp.cosets[p], sizeof(CosetRep));
+    add(gp.pair_lut.data(), gp.pair_lut.size() * sizeof(uint32_t));
+    add(gp.pair_arg.data(), gp.pair_arg.size() * sizeof(uint32_t));
+    add(gp.op_code.data(), gp.op_code.size() * sizeof(uint32_t));
+    return t;
+}
+
+void set_torus_tables(const GroupPlan &gp, const unsigned char *d, PlanDev &pd) {
+    pd.bases = reinterpret_cast<const CosetRep *>(d);
+    pd.pair_lut = reinterpret_cast<const uint32_t *>(d + gp.base_coset.size() * sizeof(CosetRep));
+    pd.pair_arg = pd.pair_lut + gp.pair_lut.size();
+    pd.op_code = pd.pair_arg + gp.pair_arg.size();
 }
 
 // Stabilizer-ratio table of a group: the class of every divisor of |G|
@@ -540,10 +565,11 @@ void upload_plan(ls_basis *b, hipStream_t st) {
     pd.chi_one = b->d_chi_one;
     pd.skip = b->d_skip;
     if (gp.torus) {
-        b->d_pair_lut = dev_alloc_n<uint32_t>(gp.pair_lut.size(), st);
-        LS_HIP_CHECK(hipMemcpyAsync(b->d_pair_lut, gp.pair_lut.data(), gp.pair_lut.size() * sizeof(uint32_t),
-                                    hipMemcpyHostToDevice, st));
-        pd.pair_lut = b->d_pair_lut;
+        const std::vector<unsigned char> t = torus_tables(gp);
+        b->d_torus = dev_alloc_n<unsigned char>(t.size(), st);
+        LS_HIP_CHECK(hipMemcpyAsync(b->d_torus, t.data(), t.size(), hipMemcpyHostToDevice, st));
+        LS_HIP_CHECK(hipStreamSynchronize(st));
+        set_torus_tables(gp, b->d_torus, pd);
     }
     uint32_t n_cls = 0;
     const std::vector<unsigned char> stab = stab_table(gp.n_elements, n_cls);
@@ -642,7 +668,9 @@ uint64_t count_members(ls_basis *b, uint64_t begin, uint64_t end, hipStream_t st
 constexpr size_t kCountScratchBytes = 256 * 1024;
 // the skip table of the walk lies after them: at most 4096 images of 64 bits
 constexpr size_t kSkipBytes = 4096 * 64;
-static __device__ __align__(256) unsigned char scratch[kCountScratchBytes + kSkipBytes];
+// and the torus tables: at most 8 base images, twice 4^6 entries, 32 codes
+constexpr size_t kTorusBytes = 8 * sizeof(CosetRep) + 2 * 4096 * sizeof(uint32_t) + 32 * sizeof(uint32_t);
+static __device__ __align__(256) unsigned char scratch[kCountScratchBytes + kSkipBytes + kTorusBytes];
 
 namespace {
 
@@ -702,8 +730,11 @@ uint64_t count_members_noalloc(const GroupPlan &gp, int32_t weight, uint64_t beg
     pd.chi_one = reinterpret_cast<const uint32_t *>(base + o_one);
     pd.skip = base + kCountScratchBytes;
     if (gp.torus) {
-        put(o_lut, gp.pair_lut.data(), gp.pair_lut.size() * sizeof(uint32_t));
-        pd.pair_lut = reinterpret_cast<const uint32_t *>(base + o_lut);
+        const std::vector<unsigned char> t = torus_tables(gp);
+        unsigned char *at = base + kCountScratchBytes + kSkipBytes;
+        put(kCountScratchBytes + kSkipBytes, t.data(), t.size());
+        LS_HIP_CHECK(hipStreamSynchronize(st));
+        set_torus_tables(gp, at, pd);
     }
     unsigned long long *acc = reinterpret_cast<unsigned long long *>(base);
     const uint64_t *binom = reinterpret_cast<const uint64_t *>(base + o_binom);

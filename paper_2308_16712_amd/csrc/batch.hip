@@ -56,8 +56,8 @@ __global__ void __launch_bounds__(batch_block(KIND, CPLX))
         const uint32_t jid = __builtin_amdgcn_readfirstlane(T.job);
         const MatvecJob &a = jobs[jid];
         if (jid != cur) {
-            L = lds_tables<KIND, LX, BLOCK, false>(a, smem);
-            stage_tables<KIND, LX, BLOCK, false>(a, L);
+            L = lds_tables<KIND, LX, BLOCK, false, false>(a, smem);
+            stage_tables<KIND, LX, BLOCK, false, false>(a, L);
             __syncthreads();
             cur = jid;
         }
@@ -469,7 +469,7 @@ static void batch_prepare(ls_batch *B, hipStream_t st) {
     for (uint32_t i = 0; i < n; ++i) {
         const ls_operator *op = B->ops[i];
         const int kind = variant_of(op).kind;
-        const size_t own = lds_bytes(kind, op->n_diag + op->n_off, op->n_off, op->basis->plan.lx) +
+        const size_t own = lds_bytes(kind, op->n_diag + op->n_off, op->n_off, static_cast<uint32_t>(op->basis->plan.base_coset.size())) +
                            (kind == kOrbitTorus ? kPairTableBytes : 0);
         const size_t fr = own + 16 <= kMaxLds ? kMaxLds - own - 16 : 0;
         auto it = lds_free.find(op->basis);
@@ -506,7 +506,7 @@ static void batch_prepare(ls_batch *B, hipStream_t st) {
             g->item_col.push_back({i, col});
             const double nterm = static_cast<double>(op->n_off) + 1.0;
             g->cost.push_back(static_cast<double>(op->basis->dim) * nterm * op->basis->plan.n_elements);
-            size_t lds = lds_bytes(v.kind, op->n_diag + op->n_off, op->n_off, op->basis->plan.lx);
+            size_t lds = lds_bytes(v.kind, op->n_diag + op->n_off, op->n_off, static_cast<uint32_t>(op->basis->plan.base_coset.size()));
             if (j.search.mode == kLookupStaged) lds += static_cast<size_t>(j.search.n_bkt) * sizeof(uint32_t);
             g->lds = std::max(g->lds, lds);
             col += static_cast<uint32_t>(nr);
@@ -673,7 +673,7 @@ void fused_matvec(FusedState *f, uint32_t n, const ls_operator *const *ops, cons
         }
         g->jobs.push_back(job_of(op, xs[i], ys[i], 1, 0));
         g->cost.push_back(static_cast<double>(op->basis->dim) * (op->n_off + 1.0) * op->basis->plan.n_elements);
-        g->lds = std::max(g->lds, lds_bytes(v.kind, op->n_diag + op->n_off, op->n_off, op->basis->plan.lx));
+        g->lds = std::max(g->lds, lds_bytes(v.kind, op->n_diag + op->n_off, op->n_off, static_cast<uint32_t>(op->basis->plan.base_coset.size())));
     }
     f->host_tiles.resize(f->groups.size());
     for (size_t gi = 0; gi < f->groups.size(); ++gi) {

@@ -227,14 +227,12 @@ __device__ __forceinline__ void walk_ring(const PlanDev &P, W s, const CandRange
 }
 
 // Tori with a pair table (lx <= 6, ly >= 2): the top two rows of the smallest
-// image are the smallest pair of rows over every coset, y-shift, flip and
-// x-shift, and the table gives the best x-shift of a pair.  An iteration
-// takes one coset of the lane's candidate: ly table reads decide all its
-// images (a smaller pair rejects, with the m of the two rows it is made of;
-// the largest m of the coset's smaller pairs is taken), and only the images
-// that equal s in the top two rows are compared in full, at every x-shift
-// that may reach them.  About 300 instructions a coset for a member of a 6x6
-// sector, against 72 image steps of 25.
+// image are the smallest pair of rows over every base image, y-shift, flip
+// and row operation, and the pair table gives the smallest value of a pair.
+// An iteration takes one base image of the lane's candidate: ly table reads
+// decide all its images (a smaller pair rejects, with the m of the two rows
+// it is made of; the largest m of the base's smaller pairs is taken), and only
+// the images that equal s in the top two rows are formed and compared.
 template <typename W, typename Hit>
 __device__ __forceinline__ void walk_torus(const PlanDev &P, W s, const CandRange<W> &R, Hit &&hit) {
     const W full = static_cast<W>(P.full);
@@ -243,45 +241,65 @@ __device__ __forceinline__ void walk_torus(const PlanDev &P, W s, const CandRang
     const uint32_t low = n - 2 * L;                    // bits below the top two rows
     uint32_t p = 0, stab = 0;
     for (;;) {
-        const W u = p == 0 ? s : apply_coset<W>(P.cosets[p], s, P);
+        const W u = p == 0 ? s : apply_coset<W>(P.bases[p], s, P);
         const uint32_t own = static_cast<uint32_t>(s >> low);
+        const uint32_t coset = P.op_code[p * 4] & 0xFFu;
         uint32_t m = 0;
         bool out = false;
-        uint64_t ties = 0;                             // bit b * nz + f
+        uint64_t tie = 0, tief = 0;                    // y-shifts: plain, flipped
         W v = u;
         for (uint32_t b = 0; b < ly; ++b) {
             const uint32_t e = P.pair_lut[static_cast<uint32_t>(v >> low)];
-            const uint32_t k0 = (e >> 4) & 0xFFFu, k1 = nz == 2 ? e >> 20 : ~0u;
+            const uint32_t k0 = e & 0xFFFFu, k1 = nz == 2 ? e >> 16 : ~0u;
             if (min(k0, k1) < own) {
                 out = true;
-                m = max(m, static_cast<uint32_t>(P.skip[(p * nt + L * b) * n + low]));
+                m = max(m, static_cast<uint32_t>(P.skip[(coset * nt + L * b) * n + low]));
             }
-            ties |= (k0 == own ? 1ull : 0ull) << (b * nz);
-            ties |= (k1 == own ? 2ull : 0ull) << (b * nz);
+            tie |= (k0 == own ? 1ull : 0ull) << b;
+            tief |= (k1 == own ? 1ull : 0ull) << b;
             v = yrot<W>(v, P);
         }
-        if (!out) {
-            while (ties) {
-                const uint32_t t = static_cast<uint32_t>(__builtin_ctzll(ties));
-                ties &= ties - 1;
-                const uint32_t b = nz == 2 ? t >> 1 : t, f = nz == 2 ? t & 1u : 0u;
-                W c = u;
-                if (b) c = ((c << (L * b)) | (c >> (n - L * b))) & full;
-                if (f) c ^= full;
-                for (uint32_t a = 0; a < L; ++a) {
-                    const uint32_t img = p * nt + a + L * b;
-                    if (c < s) {
-                        out = true;
-                        m = max(m, static_cast<uint32_t>(P.skip[img * n + top_bit<W>(static_cast<W>(c ^ s))]));
-                    } else if (c == s) {
-                        ++stab;
-                        if (!chi_is_one(P, img * nz + f)) out = true;
-                    }
-                    if (a + 1 < L) c = xrot<W>(c, P);
+        if (out) tie = tief = 0;
+        while (tie | tief) {
+            const uint32_t f = tie ? 0u : 1u;
+            uint64_t &set = tie ? tie : tief;
+            const uint32_t b = static_cast<uint32_t>(__builtin_ctzll(set));
+            set &= set - 1;
+            W c = u;
+            if (b) c = ((c << (L * b)) | (c >> (n - L * b))) & full;
+            if (f) c ^= full;
+            uint32_t am = P.pair_arg[static_cast<uint32_t>(c >> low)];
+            W cr = 0;                                  // the rows' bits reversed
+            for (uint32_t x = 0; x < L; ++x) cr |= ((c >> x) & static_cast<W>(P.col0)) << (L - 1 - x);
+            while (am) {
+                const uint32_t j = static_cast<uint32_t>(__builtin_ctz(am));
+                am &= am - 1;
+                const uint32_t o = j >> 3, a = j & 7u;
+                W z = (o == 1 || o == 2) ? cr : c;
+                if (o >= 2) {
+                    // reversed, and the pair (now at the bottom) rotated to the top
+                    z = bit_reverse<W>(z, n);
+                    if (ly > 2) z = ((z << low) | (z >> (n - low))) & full;
+                }
+                if ((P.op_flips >> o) & 1u) z ^= full;
+                const W ma = static_cast<W>(P.col_ge[a]);
+                z = ((z << a) & ma) | ((z >> (L - a)) & ~ma & full);
+                if (z > s) continue;
+                const uint32_t oc = P.op_code[p * 4 + o];
+                uint32_t x = ((oc >> 8) & 0xFFu) + a, y = ((oc >> 16) & 0xFFu) + (o >= 2 ? 2 * ly - 2 - b : b);
+                if (x >= L) x -= L;
+                while (y >= ly) y -= ly;
+                const uint32_t img = (oc & 0xFFu) * nt + x + L * y;
+                if (z < s) {
+                    out = true;
+                    m = max(m, static_cast<uint32_t>(P.skip[img * n + top_bit<W>(static_cast<W>(z ^ s))]));
+                } else {
+                    ++stab;
+                    if (!chi_is_one(P, img * nz + (f ^ (oc >> 24)))) out = true;
                 }
             }
         }
-        if (out || ++p >= P.n_cosets) {
+        if (out || ++p >= P.n_base) {
             if (!out) hit(s, stab);
             if (!R.skip(s, m)) break;
             p = stab = 0;

@@ -321,28 +321,82 @@ GroupPlan compile_group(const ls_sector_desc &d) {
     }
     P.chi_mode = trivial ? kChiTrivial : (real ? kChiReal : kChiComplex);
 
-    // Pruning table for tori: the top two rows of an image decide the order
-    // unless they tie, and for each pair of rows the x-rotation that makes
-    // the pair smallest is fixed by the pair alone.
+    // Tables of the torus search: the row operations present, the base
+    // images that the other cosets are row operations of, and for each pair
+    // of rows the smallest value over operations and x-shifts.
     if (P.lx >= 2 && P.lx <= 6 && P.ly >= 2 && P.cosets.size() <= 8 && P.cosets.size() * P.ly * nz <= 128) {
-        P.torus = true;
         const uint32_t L = P.lx, rm = (1u << L) - 1u;
-        auto rot = [&](uint32_t v, uint32_t a) { return a == 0 ? v : (((v << a) | (v >> (L - a))) & rm); };
-        const uint32_t nq = 1u << (2 * L);
-        std::vector<uint32_t> single(nq);
-        for (uint32_t q = 0; q < nq; ++q) {
-            const uint32_t top = q >> L, second = q & rm;
-            uint32_t best = ~0u, arg = 0, ties = 0;
-            for (uint32_t a = 0; a < L; ++a) {
-                const uint32_t v = (rot(top, a) << L) | rot(second, a);
-                if (v < best) { best = v; arg = a; ties = 1; }
-                else if (v == best) ++ties;
+        std::vector<uint32_t> code_of(ng);
+        for (uint32_t c = 0; c < ng; ++c) code_of[P.code_to_index[c]] = c;
+        // code of row operation m (its flip g) after the element e; -1: not in the group
+        auto op_after = [&](uint32_t m, uint8_t g, int e) -> int {
+            const uint16_t *pe = d.perm + static_cast<size_t>(e) * n;
+            std::vector<uint16_t> c(n);
+            for (uint32_t i = 0; i < n; ++i) {
+                const uint32_t x = pe[i] % L, y = pe[i] / L;
+                c[i] = static_cast<uint16_t>(((m & 1) ? L - 1 - x : x) + L * ((m & 2) ? P.ly - 1 - y : y));
             }
-            single[q] = (best << 4) | ((ties > 1 ? 1u : 0u) << 3) | arg;
+            const int h = find_elem(c, static_cast<uint8_t>(g ^ d.flip[e]));
+            return h < 0 ? -1 : static_cast<int>(code_of[h]);
+        };
+        const uint32_t per_coset = nt * nz;
+        uint32_t ops[4] = {}, n_ops = 0;
+        std::vector<char> seen(P.cosets.size(), 0);
+        for (uint32_t m = 0; m < 4; ++m)
+            for (uint8_t g = 0; g < 2; ++g) {
+                const int c = op_after(m, g, it_id->second);
+                if (c < 0 || seen[c / per_coset]) continue;   // absent, or a translation of another
+                seen[c / per_coset] = 1;
+                ops[n_ops++] = m;
+                if (g) P.op_flips |= 1u << m;
+            }
+        std::vector<char> taken(P.cosets.size(), 0);
+        bool split = true;
+        for (uint32_t p = 0; p < P.cosets.size(); ++p) {
+            if (taken[p]) continue;
+            P.base_coset.push_back(p);
+            P.op_code.resize(P.base_coset.size() * 4, 0);
+            for (uint32_t k = 0; k < n_ops; ++k) {
+                const int c = op_after(ops[k], (P.op_flips >> ops[k]) & 1u, reps[p]);
+                if (c < 0 || taken[c / per_coset]) {
+                    split = false;
+                    break;
+                }
+                taken[c / per_coset] = 1;
+                const uint32_t t = (static_cast<uint32_t>(c) / nz) % nt, f = static_cast<uint32_t>(c) % nz;
+                P.op_code[(P.base_coset.size() - 1) * 4 + ops[k]] =
+                    static_cast<uint32_t>(c) / per_coset | (t % L) << 8 | (t / L) << 16 | f << 24;
+            }
         }
-        // each entry also carries the entry of the spin-flipped pair
+        if (!split) throw Error{LS_EINTERNAL, "row operations do not split the cosets"};
+        P.torus = P.base_coset.size() * P.ly <= 64;   // a bit for every base image and y-shift
+        auto rot = [&](uint32_t v, uint32_t a) { return a == 0 ? v : (((v << a) | (v >> (L - a))) & rm); };
+        auto rev = [&](uint32_t v) {
+            uint32_t r = 0;
+            for (uint32_t x = 0; x < L; ++x) r |= ((v >> x) & 1u) << (L - 1 - x);
+            return r;
+        };
+        const uint32_t nq = 1u << (2 * L);
+        std::vector<uint32_t> key(nq);
+        P.pair_arg.assign(nq, 0);
+        for (uint32_t q = 0; q < nq; ++q) {
+            uint32_t best = ~0u;
+            for (uint32_t k = 0; k < n_ops; ++k) {
+                const uint32_t m = ops[k], w = ((P.op_flips >> m) & 1u) ? q ^ (nq - 1) : q;
+                uint32_t top = w >> L, second = w & rm;
+                if (m & 1) { top = rev(top); second = rev(second); }
+                if (m & 2) std::swap(top, second);
+                for (uint32_t a = 0; a < L; ++a) {
+                    const uint32_t v = (rot(top, a) << L) | rot(second, a);
+                    if (v < best) { best = v; P.pair_arg[q] = 0; }
+                    if (v == best) P.pair_arg[q] |= 1u << (m * 8 + a);
+                }
+            }
+            key[q] = best;
+        }
+        // each entry also carries the key of the spin-flipped pair
         P.pair_lut.resize(nq);
-        for (uint32_t q = 0; q < nq; ++q) P.pair_lut[q] = single[q] | (single[q ^ (nq - 1)] << 16);
+        for (uint32_t q = 0; q < nq; ++q) P.pair_lut[q] = key[q] | (key[q ^ (nq - 1)] << 16);
         for (uint32_t a = 0; a < L; ++a) {
             const uint64_t rowpat = static_cast<uint64_t>(rm & ~((1u << a) - 1u));
             uint64_t m = 0;

@@ -96,7 +96,7 @@ struct CosetRep {
 
 enum ChiMode : int { kChiTrivial = 0, kChiReal = 1, kChiComplex = 2 };
 
-constexpr uint32_t kTorusCosetSlots = 8;   // coset representatives kept per lane
+constexpr uint32_t kTorusCosetSlots = 8;   // base images kept per lane, at most
 
 struct GroupPlan {
     uint32_t n_sites = 0;
@@ -114,12 +114,21 @@ struct GroupPlan {
     // Enumeration: for image p * |T| + t and bit d, the lowest of d and the
     // positions the image moves to bit d or above, [n_elements / |Z|][N].
     std::vector<uint8_t> skip;
-    // Pruned torus search (lx <= 6, ly >= 2): for every pair of rows
-    // q = (top << lx | second) the smallest x-rotation of the pair, as
-    // entry = key << 4 | ambiguous << 3 | argmin_a, stored as
-    // entry(q) | entry(q with all bits flipped) << 16.
+    // Pruned torus search (lx <= 6, ly >= 2).  The row operations among the
+    // cosets (m = 0 identity, 1 x -> lx-1-x, 2 y -> ly-1-y, 3 both; row_ops)
+    // act on a pair of neighbouring rows as on the whole word, so one table
+    // read covers them all: for every pair q = (top << lx | second) the
+    // smallest value the top two rows take over row operations and x-shifts
+    // (key), as key(q) | key(q with all bits flipped) << 16; pair_arg has bit
+    // m * 8 + a for every operation m and x-shift a that give the key.
+    // The other cosets are row operations after one of the base cosets.
     bool torus = false;
-    std::vector<uint32_t> pair_lut;
+    std::vector<uint32_t> pair_lut, pair_arg;
+    uint32_t op_flips = 0;          // row operations that come with a spin flip
+    std::vector<uint32_t> base_coset;   // base images: indices into cosets
+    // code of operation m after base image i, [base * 4 + m]:
+    // coset | x-shift << 8 | y-shift << 16 | flip << 24
+    std::vector<uint32_t> op_code;
     uint64_t col_ge[8] = {};        // bits with x >= a in every row
 };
 
@@ -142,7 +151,11 @@ struct PlanDev {
     const CosetRep *cosets;     // device
     const double2 *chi;         // device, by code
     const uint32_t *chi_one;    // device bitset, by code
-    const uint32_t *pair_lut;   // device, torus pruning table (or null)
+    const uint32_t *pair_lut;   // device, torus search tables (or null)
+    const uint32_t *pair_arg;
+    const uint32_t *op_code;
+    const CosetRep *bases;      // device [n_base]
+    uint32_t n_base, op_flips;
     const uint8_t *skip;        // device, by image and bit (enumeration only; else null)
     uint64_t col_ge[8];
     // Stabilizer-ratio table (0 classes = none): stab_cls[s] is the class of
@@ -245,7 +258,7 @@ struct ls_basis {
     ls::CosetRep *d_cosets = nullptr;
     double2 *d_chi = nullptr;
     uint32_t *d_chi_one = nullptr;
-    uint32_t *d_pair_lut = nullptr;
+    unsigned char *d_torus = nullptr;  // torus search tables
     uint8_t *d_skip = nullptr;
     void *d_stab_tab = nullptr;
     ls::PlanDev plan_dev{};
@@ -264,8 +277,8 @@ struct ls_operator {
     uint32_t n_diag = 0, n_off = 0;
     ls_term_dev *d_terms = nullptr;     // diagonal terms first, then off-diagonal
     std::vector<ls_term_dev> host_terms;
-    // torus search: the permutation part of every coset representative
-    // applied to every off-diagonal flip mask, [n_off][kTorusCosetSlots]
+    // torus search: the permutation part of every base image applied to every
+    // off-diagonal flip mask, [n_base][n_off]
     std::vector<uint64_t> host_cflip;
     uint64_t *d_cflip = nullptr;
     // error flag: a product met a neighbour whose in-sector representative

@@ -20,7 +20,7 @@ namespace {
 // registers (with non-trivial characters the stabilizer walk of a lookup
 // miss is compiled into the element loop) and keep the launch bound.
 constexpr int waves_per_simd(int kind, int chi, bool cplx, int nr, uint32_t lx) {
-    return ((kind == kOrbitTorus && !cplx && chi == kChiTrivial && nr == 1 && lx != 0) ||
+    return ((kind == kOrbitTorus && !cplx && nr == 1 && lx != 0) ||
             (kind == kOrbitRing64 && chi == kChiTrivial && nr <= 2))
                ? 8
                : 1;
@@ -62,8 +62,8 @@ constexpr int kGroupBlock = 256;
 template <typename W, int KIND, int CHI, bool CPLX, uint32_t LX, uint32_t LY, uint32_t NZ>
 __global__ void __launch_bounds__(kGroupBlock) k_matvec_group(MatvecJob a, uint64_t n_groups) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const LdsTables L = lds_tables<KIND, LX, kGroupBlock>(a, smem);
-    stage_tables<KIND, LX, kGroupBlock>(a, L);
+    const LdsTables L = lds_tables<KIND, LX, kGroupBlock, uses_ratio_table(KIND, false), false>(a, smem);
+    stage_tables<KIND, LX, kGroupBlock, uses_ratio_table(KIND, false), false>(a, L);
     __syncthreads();
     const uint64_t group = (static_cast<uint64_t>(blockIdx.x) * kGroupBlock + threadIdx.x) / kGroupLanes;
     run_rows_group<W, KIND, CHI, CPLX, LX, LY, NZ>(a, L, group, n_groups);
@@ -117,7 +117,7 @@ struct SingleLaunch {
         lanes = (lanes + wg_rows - 1) / wg_rows * wg_rows;
         const dim3 grid(static_cast<uint32_t>(lanes / wg_rows));
         const uint32_t rows_per_wg = static_cast<uint32_t>(wg_rows);
-        const size_t lds = lds_bytes(KIND, job.n_terms, job.n_terms - job.n_diag, job.plan.lx);
+        const size_t lds = lds_bytes(KIND, job.n_terms, job.n_terms - job.n_diag, job.plan.n_base);
         // a single column of a sector with fewer rows than the GPU has lanes:
         // several lanes per row (run_rows_group), so that each lane's chain
         // of searches and lookups is short.  The ring searches are cheap next
@@ -236,7 +236,8 @@ Variant variant_of(const ls_operator *op) {
     v.cplx = op->is_complex;
     v.chi = op->is_complex ? kChiComplex : gp.chi_mode;
     const bool torus = gp.torus && op->d_cflip != nullptr &&
-                       lds_bytes(kOrbitTorus, op->n_diag + op->n_off, op->n_off, gp.lx) + kPairTableBytes <= kMaxLds;
+                       lds_bytes(kOrbitTorus, op->n_diag + op->n_off, op->n_off,
+                                 static_cast<uint32_t>(gp.base_coset.size())) + kTorusTableBytes <= kMaxLds;
     if (!v.word64 && gp.ly == 1 && gp.lx == gp.n_sites) {
         v.kind = kOrbitRing32;
     } else if (v.word64 && gp.ly == 1 && gp.lx == gp.n_sites && gp.n_sites < 64) {
@@ -245,8 +246,8 @@ Variant variant_of(const ls_operator *op) {
         v.kind = kOrbitTorus;
         const uint32_t nz = gp.pair_flip ? 2 : 1;
         // compile-time shapes: square tori with the full point group (eight
-        // coset representatives) and spin inversion
-        if (gp.cosets.size() == kTorusCosetSlots && nz == 2 &&
+        // cosets from two base images) and spin inversion
+        if (gp.cosets.size() == 8 && gp.base_coset.size() == 2 && gp.op_flips == 0 && nz == 2 &&
             ((gp.lx == 6 && gp.ly == 6) || (gp.lx == 4 && gp.ly == 4))) {
             v.lx = gp.lx;
             v.ly = gp.ly;

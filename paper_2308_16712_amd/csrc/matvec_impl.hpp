@@ -26,9 +26,9 @@
 // per-row differences in the number of acting terms average out.  The term
 // table is staged in LDS once per workgroup (per item in a batch).
 //
-// Tori (pruned search): permutations act linearly on bits, so for a coset
-// representative p, p(r ^ f) = p(r) ^ pi_p(f).  A lane computes p(r) once per
-// row and each neighbour's images with one XOR per coset, reading pi_p(f)
+// Tori (pruned search): permutations act linearly on bits, so for a base
+// image p, p(r ^ f) = p(r) ^ pi_p(f).  A lane computes p(r) once per row and
+// each neighbour's images with one XOR per base image, reading pi_p(f)
 // from a per-operator table staged in LDS.  Workgroups of 1024 threads share
 // the LDS tables among 16 wavefronts.
 //
@@ -50,7 +50,7 @@ struct MatvecJob {
     SearchDev search;
     const uint16_t *stab;
     const ls_term_dev *terms;
-    const uint64_t *cflip;  // [n_off][kTorusCosetSlots] (torus search only)
+    const uint64_t *cflip;  // [n_base][n_off] (torus search only)
     uint32_t n_diag, n_terms;
     uint64_t dim;
     uint32_t ld;           // row stride of x and y in elements
@@ -124,15 +124,18 @@ __host__ __device__ constexpr size_t align16(size_t v) { return (v + 15) & ~size
 constexpr uint32_t kPairTableEntries = 1u << 12;   // 4^lx for lx <= 6
 
 // Dynamic LDS bytes of a launch (a staged bucket table goes after them).
-__host__ __device__ inline size_t lds_bytes(int kind, uint32_t n_terms, uint32_t n_off, uint32_t lx) {
-    (void)lx;
+__host__ __device__ inline size_t lds_bytes(int kind, uint32_t n_terms, uint32_t n_off, uint32_t n_base) {
     size_t b = align16((n_terms > 0 ? n_terms : 1) * sizeof(ls_term_dev));
-    if (kind == kOrbitTorus) b += 64 + static_cast<size_t>(n_off) * kTorusCosetSlots * sizeof(uint64_t);
+    if (kind == kOrbitTorus) b += 64 + static_cast<size_t>(n_off) * n_base * sizeof(uint64_t);
     return b;
 }
 
-// Static LDS of the torus kernels.
+// Static LDS of the torus kernels: the pair table, and in the single launches
+// over 1024-thread workgroups the argument table as well (ARG).  The others
+// read that one from memory, once or twice an element: small workgroups would
+// hold fewer waves for it, and a batch needs the room for staged buckets.
 constexpr size_t kPairTableBytes = kPairTableEntries * sizeof(uint32_t);
+constexpr size_t kTorusTableBytes = 2 * kPairTableBytes;
 
 // Kernels that read the element normalisation from the stabilizer-ratio
 // table (5.6 KB of static LDS): the single launches of the ring and generic
@@ -146,14 +149,15 @@ constexpr bool uses_ratio_table(int kind, bool batched) { return kind != kOrbitT
 struct LdsTables {
     ls_term_dev *terms;
     uint32_t *lut;
+    const uint32_t *arg;
     uint64_t *col;
-    uint64_t *cflip;   // [slot][n_off]
+    uint64_t *cflip;   // [base][n_off]
     uint32_t *bkt;     // staged bucket table (kLookupStaged)
     uint8_t *scls;     // class of every stabilizer size
     double *sratio;    // sqrt(d_b / d_a) by classes
 };
 
-template <int KIND, uint32_t LX, int BLOCK, bool TAB = uses_ratio_table(KIND, false)>
+template <int KIND, uint32_t LX, int BLOCK, bool TAB = uses_ratio_table(KIND, false), bool ARG = true>
 __device__ __forceinline__ LdsTables lds_tables(const MatvecJob &a, unsigned char *smem) {
     LdsTables L;
     if constexpr (TAB) {
@@ -168,33 +172,40 @@ __device__ __forceinline__ LdsTables lds_tables(const MatvecJob &a, unsigned cha
     if constexpr (KIND == kOrbitTorus) {
         __shared__ uint32_t pair_table[kPairTableEntries];
         L.lut = pair_table;
+        if constexpr (ARG) {
+            __shared__ uint32_t pair_arg[kPairTableEntries];
+            L.arg = pair_arg;
+        } else {
+            L.arg = a.plan.pair_arg;
+        }
         L.col = reinterpret_cast<uint64_t *>(smem);
         L.cflip = L.col + 8;
         L.terms = reinterpret_cast<ls_term_dev *>(
-            smem + 64 + static_cast<size_t>(a.n_terms - a.n_diag) * kTorusCosetSlots * sizeof(uint64_t));
+            smem + 64 + static_cast<size_t>(a.n_terms - a.n_diag) * a.plan.n_base * sizeof(uint64_t));
     } else {
         L.lut = nullptr;
+        L.arg = nullptr;
         L.col = nullptr;
         L.cflip = nullptr;
         L.terms = reinterpret_cast<ls_term_dev *>(smem);
     }
-    L.bkt = reinterpret_cast<uint32_t *>(smem + lds_bytes(KIND, a.n_terms, a.n_terms - a.n_diag, LX));
+    L.bkt = reinterpret_cast<uint32_t *>(smem + lds_bytes(KIND, a.n_terms, a.n_terms - a.n_diag, a.plan.n_base));
     return L;
 }
 
 // All threads of the workgroup stage the job's tables; caller syncs.
-template <int KIND, uint32_t LX, int BLOCK, bool TAB = uses_ratio_table(KIND, false)>
+template <int KIND, uint32_t LX, int BLOCK, bool TAB = uses_ratio_table(KIND, false), bool ARG = true>
 __device__ __forceinline__ void stage_tables(const MatvecJob &a, const LdsTables &L) {
     for (uint32_t t = threadIdx.x; t < a.n_terms; t += BLOCK) L.terms[t] = a.terms[t];
     if constexpr (KIND == kOrbitTorus) {
         const uint32_t n_off = a.n_terms - a.n_diag;
         const uint32_t lut_n = 1u << (2 * (LX ? LX : a.plan.lx));
-        for (uint32_t q = threadIdx.x; q < lut_n; q += BLOCK) L.lut[q] = a.plan.pair_lut[q];
-        if (threadIdx.x < 8) L.col[threadIdx.x] = a.plan.col_ge[threadIdx.x];
-        for (uint32_t q = threadIdx.x; q < n_off * kTorusCosetSlots; q += BLOCK) {
-            const uint32_t k = q / kTorusCosetSlots, p = q % kTorusCosetSlots;
-            L.cflip[p * n_off + k] = a.cflip[q];   // transposed: lanes spread over banks
+        for (uint32_t q = threadIdx.x; q < lut_n; q += BLOCK) {
+            L.lut[q] = a.plan.pair_lut[q];
+            if constexpr (ARG) const_cast<uint32_t *>(L.arg)[q] = a.plan.pair_arg[q];
         }
+        if (threadIdx.x < 8) L.col[threadIdx.x] = a.plan.col_ge[threadIdx.x];
+        for (uint32_t q = threadIdx.x; q < n_off * a.plan.n_base; q += BLOCK) L.cflip[q] = a.cflip[q];
     }
     if (a.search.mode == kLookupStaged)
         for (uint32_t q = threadIdx.x; q < a.search.n_bkt; q += BLOCK) L.bkt[q] = a.search.buckets[q];
@@ -257,12 +268,13 @@ __device__ __forceinline__ void diag_sum(const ls_term_dev *sterm, uint32_t n_di
     }
 }
 
-// Torus search: p(r) for every coset representative p of the row.
-template <typename W>
+// Torus search: p(r) for every base image p of the row.
+template <typename W, uint32_t LX>
 __device__ __forceinline__ void row_images(const PlanDev &P, uint64_t r, W *pr) {
+    pr[0] = static_cast<W>(r);
 #pragma unroll
-    for (uint32_t p = 0; p < kTorusCosetSlots; ++p)
-        if (p < P.n_cosets) pr[p] = apply_coset<W>(P.cosets[p], static_cast<W>(r), P);
+    for (uint32_t p = 1; p < (LX ? 2u : kTorusCosetSlots); ++p)
+        if (LX || p < P.n_base) pr[p] = apply_coset<W>(P.bases[p], static_cast<W>(r), P);
 }
 
 // Orbit minimum of the neighbour r ^ flip_t of off-diagonal term t, and the
@@ -273,7 +285,11 @@ __device__ __forceinline__ W neighbour_rep(const MatvecJob &a, const LdsTables &
     if constexpr (KIND == kOrbitTorus) {
         const uint32_t n_off = a.n_terms - a.n_diag;
         const uint32_t ko = t - a.n_diag;
-        return torus_orbit_min<W, TRACK, LX, LY, NZ>(a.plan, pr, L.cflip + ko, n_off, L.lut, L.col, code);
+        OrbitInfo info;
+        const W rep =
+            torus_orbit_min<W, TRACK, false, LX, LY, NZ>(a.plan, pr, L.cflip + ko, n_off, L.lut, L.arg, L.col, info);
+        code = info.code;
+        return rep;
     } else {
         (void)pr;
         return orbit_min<W, KIND, TRACK>(a.plan, static_cast<W>(r ^ L.terms[t].flip), code);
@@ -458,7 +474,7 @@ __device__ __forceinline__ void run_rows(const MatvecJob &a, const LdsTables &L,
         diag_sum<CPLX>(sterm, a.n_diag, r, dre, dim_);
 #pragma unroll
         for (int q = 0; q < NR; ++q) acc[q] = diag_times<CPLX>(dre, dim_, x[row * a.ld + a.col + q]);
-        if constexpr (KIND == kOrbitTorus) row_images<W>(a.plan, r, pr);
+        if constexpr (KIND == kOrbitTorus) row_images<W, LX>(a.plan, r, pr);
         t = a.n_diag;
     };
     begin_row();
@@ -534,7 +550,7 @@ __device__ __forceinline__ void run_rows_group(const MatvecJob &a, const LdsTabl
             double dre, dim_;
             diag_sum<CPLX>(sterm, a.n_diag, r, dre, dim_);
             acc = diag_times<CPLX>(dre, dim_, x[row * a.ld + a.col]);
-            if constexpr (KIND == kOrbitTorus) row_images<W>(a.plan, r, pr);
+            if constexpr (KIND == kOrbitTorus) row_images<W, LX>(a.plan, r, pr);
         }
         uint32_t t = a.n_diag;   // scan position
         uint32_t seen = 0;       // acting terms passed
@@ -624,7 +640,7 @@ __device__ __forceinline__ void push_rows(const MatvecJob &a, const LdsTables &L
             }
         }
         W pr[kTorusCosetSlots] = {};
-        if constexpr (KIND == kOrbitTorus) row_images<W>(a.plan, r, pr);
+        if constexpr (KIND == kOrbitTorus) row_images<W, LX>(a.plan, r, pr);
         for (uint32_t t = a.n_diag; t < a.n_terms; ++t) {
             const ls_term_dev &Tm = L.terms[t];
             if ((r & Tm.sel) != Tm.val) continue;

@@ -8,6 +8,8 @@
 // The representative is the minimum image (the orbit minimum).
 #pragma once
 
+#include <type_traits>
+
 #include "ls_internal.hpp"
 
 namespace ls {
@@ -16,7 +18,7 @@ namespace ls {
 enum OrbitKind : int {
     kOrbitGeneric = 0,   // runtime lx, ly (ring, torus, or no translations)
     kOrbitRing32 = 1,    // N <= 32 ring: all rotations from one funnel shift each
-    kOrbitTorus = 2,     // lx <= 6, ly >= 2 torus: pruned by the pair table
+    kOrbitTorus = 2,     // lx <= 6, ly >= 2 torus: pruned by the pair table (torus_orbit_min)
     kOrbitRing64 = 3,    // 32 < N < 64 ring: rotations pruned by the longest zero run
 };
 
@@ -281,217 +283,194 @@ __device__ __forceinline__ W orbit_min(const PlanDev &P, W s, uint32_t &code) {
     return best;
 }
 
-// Pruned orbit minimum on an lx-by-ly torus (lx <= 6, ly >= 2).
-//
-// The images p(s) = p(r) ^ pi_p(f) of the coset representatives are formed
-// from the row's images p(r) (pr[]) and the flip images pi_p(f) (cf[p * cstride]).
-// Pass 1a walks every coset p and y-shift b: the top two rows of
-// tau_{0,b}(p(s)) index the pair table, whose entry holds, for the pair and
-// for its spin-flipped partner, the smallest value the two rows take over
-// all x-shifts (the key) and the x-shift reaching it.  The minimum image has
-// the smallest key, so pass 1b marks the (p, b, f) that reach the smallest
-// key in a 128-bit mask, and pass 2 evaluates only those candidates in full
-// at the x-shift the table names (at every x-shift when several shifts tie
-// on the two rows).  LX, LY, NZ are the layout and |Z| when known at compile
-// time (0: read from the plan).
-//   lut   packed pair table in LDS: entry(q) | entry(q ^ all-ones) << 16,
-//         entry = key << 4 | ambiguous << 3 | argmin_a;
-//   lcol  col_ge masks in LDS.
-constexpr uint32_t kTorusMaxCosets = kTorusCosetSlots;
-
-template <typename W, bool TRACK, uint32_t LX, uint32_t LY, uint32_t NZ>
-__device__ __forceinline__ W torus_orbit_min(const PlanDev &P, const W *pr, const uint64_t *cf, uint32_t cstride,
-                                             const uint32_t *lut, const uint64_t *lcol, uint32_t &code) {
-    const uint32_t L = LX ? LX : P.lx, Ly = LY ? LY : P.ly;
-    const uint32_t nz = NZ ? NZ : (P.pair_flip ? 2u : 1u);
-    const uint32_t rm = (1u << L) - 1u, m2 = (1u << (2 * L)) - 1u;
-    // the compile-time shapes are built for the full point group only
-    const uint32_t ncos = LX ? kTorusMaxCosets : P.n_cosets;
-    const W full = static_cast<W>(P.full);
-    // bits [sh, sh + 32) of u shifted up by 2: an index times 4 is the byte
-    // offset of its 4-byte entry
-    auto x4 = [&](W u, uint32_t sh) -> uint32_t {
+// Byte offset of the 4-byte table entry of the top two rows of tau_{0,b}(u),
+// rows ly-1-b and ly-2-b (mod ly) of an L-wide word.
+template <typename W>
+__device__ __forceinline__ uint32_t pair_offset(W u, uint32_t b, uint32_t L, uint32_t ly) {
+    // bits [sh, sh + 32) of u shifted up by 2
+    auto x4 = [&](uint32_t sh) -> uint32_t {
         return sh >= 2 ? static_cast<uint32_t>(u >> (sh - 2)) : static_cast<uint32_t>(u) << (2 - sh);
     };
-    // byte offset of the entry of the top two rows of tau_{0,b}(u): rows
-    // ly-1-b and ly-2-b (mod ly)
-    auto pair_of = [&](W u, uint32_t b) -> uint32_t {
-        const uint32_t ty = Ly - 1 - b;
-        if (ty >= 1) return x4(u, L * (ty - 1)) & (m2 << 2);
-        return ((static_cast<uint32_t>(u) & rm) << (L + 2)) | (x4(u, L * (Ly - 1)) & (rm << 2));
-    };
-    auto entry = [&](uint32_t off) -> uint32_t {
-        return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const unsigned char *>(lut) + off);
-    };
-    // image p(s) = p(r) ^ pi_p(f) of coset p: fixed p (unrolled loops), or a
-    // p that differs between lanes
-#define LS_IMG(p) (pr[p] ^ static_cast<W>(cf[(p) * cstride]))
+    const uint32_t rm = (1u << L) - 1u, m2 = (1u << (2 * L)) - 1u, ty = ly - 1 - b;
+    if (ty >= 1) return x4(L * (ty - 1)) & (m2 << 2);
+    return ((static_cast<uint32_t>(u) & rm) << (L + 2)) | (x4(L * (ly - 1)) & (rm << 2));
+}
+
+// What the torus search found: the smallest image, with TRACK the code of an
+// element reaching it, with COUNT how many images equal it (the stabilizer
+// size of the orbit's states) and whether two elements that reach it have
+// characters that differ (the projector annihilates the orbit).
+struct OrbitInfo {
+    uint32_t code = 0, count = 0;
+    bool mixed = false;
+};
+
+// Pruned orbit minimum on an lx-by-ly torus (lx <= 6, ly >= 2).
+//
+// The group is row operations (x-shifts, the reversal of the rows' bits, the
+// reversal of the rows' order) after y-shifts of a few base images (the
+// identity; on square tori a transposition as well).  The base images of a
+// neighbour are p(r) ^ pi_p(f), from the row's images p(r) (pr[]) and the flip
+// images pi_p(f) (cf[p * cstride]).  Pass 1 reads the pair table for every
+// base image p and y-shift b: the entry of two neighbouring rows holds, for
+// the pair and for its spin-flipped partner, the smallest value they take as
+// top rows over all row operations (the key).  The minimum image has the
+// smallest key, so only the (p, b, f) that reach it are looked at further:
+// 1.09 of 24 on average in a 6x6 sector, at most 2.3 over a wavefront.  Their
+// table `arg` names the operations and x-shifts that reach the key (1.5 images
+// in all), and only the rows below the top two are formed and compared, 24
+// bits for 6x6.  With a table of x-shifts only the 6x6 search made 48 reads,
+// one per coset and y-shift, against 12: the 6x6 product took 30.6 ms, now
+// 25.7 (69% of the cycles issue a VALU instruction; 168 GB of L2 misses at 6.5
+// TB/s).
+// LX, LY, NZ are the layout and |Z| when known at compile time (0: read from
+// the plan); the compile-time shapes have two base images and no operation
+// that comes with a flip of its own.
+//   lut   pair table in LDS: key(q) | key(q ^ all-ones) << 16;
+//   arg   bit m * 8 + a for every operation m and x-shift a reaching key(q);
+//   lcol  col_ge masks.
+constexpr uint32_t kTorusMaxBases = kTorusCosetSlots;
+
+template <typename W, bool TRACK, bool COUNT, uint32_t LX, uint32_t LY, uint32_t NZ>
+__device__ __forceinline__ W torus_orbit_min(const PlanDev &P, const W *pr, const uint64_t *cf, uint32_t cstride,
+                                             const uint32_t *lut, const uint32_t *arg, const uint64_t *lcol,
+                                             OrbitInfo &info) {
+    // the rows below the top two, in 32 bits where they fit
+    constexpr bool SMALL = sizeof(W) == 4 || (LX != 0 && LX * (LY - 2) < 32);
+    using T = typename std::conditional<SMALL, uint32_t, uint64_t>::type;
+    const uint32_t L = LX ? LX : P.lx, Ly = LY ? LY : P.ly;
+    const uint32_t nz = NZ ? NZ : (P.pair_flip ? 2u : 1u);
+    const uint32_t nb = LX ? 2u : P.n_base;
+    const uint32_t n = LX ? LX * LY : P.n_sites, tb = L * (Ly - 2);
+    const W full = static_cast<W>(P.full);
+    const T tmask = static_cast<T>((static_cast<uint64_t>(1) << tb) - 1);
+    const T col0 = static_cast<T>(P.col0) & tmask;
     using u16x2 = unsigned short __attribute__((ext_vector_type(2)));
-    W rmin = static_cast<W>(~static_cast<W>(0));
-    uint32_t arg = 0;
-    // pass 1a: the smallest entry of every coset (both flip entries of a
-    // table word folded with one packed minimum), then the smallest key
-    uint32_t cmin[kTorusMaxCosets];
-    uint32_t ball = 0xFFFFu;
-    uint64_t cf_next = cf[0];
+    auto entry = [&](W u, uint32_t b) -> uint32_t {
+        return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const unsigned char *>(lut) +
+                                                   pair_offset<W>(u, b, L, Ly));
+    };
+    T tail = static_cast<T>(~static_cast<T>(0));
+    uint32_t won = 0;    // base << 16 | y-shift << 8 | flip << 7 | operation << 3 | x-shift
+    auto code_of = [&](uint32_t w) -> uint32_t {
+        const uint32_t i = w >> 16, b = (w >> 8) & 0xFFu, f = (w >> 7) & 1u, m = (w >> 3) & 3u, a = w & 7u;
+        const uint32_t c = P.op_code[i * 4 + m];
+        uint32_t x = ((c >> 8) & 0xFFu) + a, y = ((c >> 16) & 0xFFu) + (m >= 2 ? 2 * Ly - 2 - b : b);
+        if (x >= L) x -= L;
+        while (y >= Ly) y -= Ly;
+        return ((c & 0xFFu) * P.n_trans + x + L * y) * nz + (f ^ (c >> 24));
+    };
+    // the images of base image u, y-shift b and flip f that reach the key
+    auto visit = [&](W u, uint32_t i, uint32_t b, uint32_t f) {
+        W v = u;
+        if (LX || b) v = ((v << (L * b)) | (v >> (n - L * b))) & full;
+        if (f) v ^= full;
+        uint32_t am = arg[static_cast<uint32_t>(v >> tb)];
+        const T t = static_cast<T>(v) & tmask;
+        T tr = 0;        // the rows' bits reversed
 #pragma unroll
-    for (uint32_t p = 0; p < kTorusMaxCosets; ++p) {
-        cmin[p] = 0xFFFFu;
-        if (p >= ncos) continue;
-        u16x2 m = {0xFFFFu, 0xFFFFu};
-        if constexpr (LY != 0) {
-            // the next coset's flip image and all of this coset's table
-            // reads in flight before the first minimum
-            const W u = pr[p] ^ static_cast<W>(cf_next);
-            if (p + 1 < kTorusMaxCosets) cf_next = cf[(p + 1) * cstride];
-            uint32_t e[LY];
-#pragma unroll
-            for (uint32_t b = 0; b < LY; ++b) e[b] = entry(pair_of(u, b));
-#pragma unroll
-            for (uint32_t b = 0; b < LY; ++b) m = __builtin_elementwise_min(m, __builtin_bit_cast(u16x2, e[b]));
-        } else {
-            for (uint32_t b1 = 0; b1 < Ly; ++b1)
-                m = __builtin_elementwise_min(m, __builtin_bit_cast(u16x2, entry(pair_of(LS_IMG(p), uni(b1)))));
+        for (uint32_t x = 0; x < 6; ++x)
+            if (x < L) tr |= ((t >> x) & col0) << (L - 1 - x);
+        while (am) {
+            const uint32_t j = static_cast<uint32_t>(__builtin_ctz(am));
+            am &= am - 1;
+            const uint32_t m = j >> 3, a = j & 7u;
+            // operation 3 reverses all bits, 2 is 3 after 1
+            T z = (m == 1 || m == 2) ? tr : t;
+            if (m >= 2) {
+                if constexpr (SMALL) z = tb ? __builtin_bitreverse32(z) >> ((32 - tb) & 31) : 0;
+                else z = tb ? __builtin_bitreverse64(z) >> ((64 - tb) & 63) : 0;
+            }
+            if (LX == 0 && ((P.op_flips >> m) & 1u)) z ^= tmask;
+            const T ma = static_cast<T>(lcol[a]);
+            z = ((z << a) & ma & tmask) | ((z >> (L - a)) & ~ma);
+            const uint32_t w = i << 16 | b << 8 | f << 7 | j;
+            if constexpr (COUNT) {
+                if (z == tail && info.count) {
+                    ++info.count;
+                    const double2 c0 = P.chi[code_of(won)], c1 = P.chi[code_of(w)];
+                    info.mixed = info.mixed || fabs(c0.x - c1.x) + fabs(c0.y - c1.y) > 1e-6;
+                }
+            }
+            if (z < tail || (COUNT && info.count == 0)) {
+                tail = z;
+                if constexpr (TRACK) won = w;
+                if constexpr (COUNT) {
+                    info.count = 1;
+                    info.mixed = false;
+                }
+            }
         }
-        cmin[p] = nz == 2 ? min(static_cast<uint32_t>(m.x), static_cast<uint32_t>(m.y))
-                          : static_cast<uint32_t>(m.x);
-        ball = min(ball, cmin[p]);
-    }
-    const uint32_t best = ball >> 4;
-    // the cosets that reach the smallest key
-    uint32_t cm = 0;
+    };
+    uint32_t best;
+    if constexpr (LX != 0) {
+        W u[2];
+        uint32_t e[2 * LY];
 #pragma unroll
-    for (uint32_t p = 0; p < kTorusMaxCosets; ++p) cm |= ((cmin[p] >> 4) == best ? 1u : 0u) << p;
-    if constexpr (!TRACK) {
-        // one mask bit per (coset, y-shift), and only the cosets that reach
-        // the smallest key are scanned twice; the kernels that also track g*
-        // do not have the registers for it and keep one bit per (coset,
-        // y-shift, flip)
-        // pass 1b and 2: in those cosets only (a loop per lane), the y-shifts
-        // that reach it with either entry (the key fields of both entries are
-        // compared at once against the pattern), and a full evaluation of the
-        // images they give, with the coset image already at hand
-        const uint32_t pat = (best << 4) | (best << 20);
-        const uint32_t keys = nz == 2 ? 0xFFF0FFF0u : 0x0000FFF0u;
-        while (cm) {
-            const uint32_t p = static_cast<uint32_t>(__builtin_ctz(cm));
-            cm &= cm - 1;
-            W u = pr[0];
+        for (uint32_t i = 0; i < 2; ++i) {
+            u[i] = pr[i] ^ static_cast<W>(cf[i * cstride]);
 #pragma unroll
-            for (uint32_t q = 1; q < kTorusMaxCosets; ++q) u = (q < ncos && p == q) ? pr[q] : u;
-            u ^= static_cast<W>(cf[p * cstride]);
-            uint64_t mb = 0;
-            if constexpr (LY != 0) {
-                uint32_t e[LY];
+            for (uint32_t b = 0; b < LY; ++b) e[i * LY + b] = entry(u[i], b);
+        }
+        u16x2 mn = __builtin_bit_cast(u16x2, e[0]);
 #pragma unroll
-                for (uint32_t b = 0; b < LY; ++b) e[b] = entry(pair_of(u, b));
+        for (uint32_t k = 1; k < 2 * LY; ++k) mn = __builtin_elementwise_min(mn, __builtin_bit_cast(u16x2, e[k]));
+        best = NZ == 2 ? min(static_cast<uint32_t>(mn.x), static_cast<uint32_t>(mn.y)) : static_cast<uint32_t>(mn.x);
+        // bit k: entry k misses the key, bit 16 + k: its flipped partner does
+        const uint32_t pat = best << 16 | best;
+        const u16x2 one = {1, 1};
+        uint32_t miss = 0;
 #pragma unroll
-                for (uint32_t b = 0; b < LY; ++b) {
-                    const uint32_t d = (e[b] ^ pat) & keys;
-                    mb |= ((d & 0xFFFFu) == 0 || (nz == 2 && (d >> 16) == 0)) ? (1ull << b) : 0ull;
-                }
-            } else {
-                for (uint32_t b1 = 0; b1 < Ly; ++b1) {
-                    const uint32_t b = uni(b1);
-                    const uint32_t d = (entry(pair_of(u, b)) ^ pat) & keys;
-                    mb |= ((d & 0xFFFFu) == 0 || (nz == 2 && (d >> 16) == 0)) ? (1ull << b) : 0ull;
-                }
-            }
-            while (mb) {
-                const uint32_t b = static_cast<uint32_t>(__builtin_ctzll(mb));
-                mb &= mb - 1;
-                W v0 = u;
-                if (b) v0 = ((v0 << (L * b)) | (v0 >> (P.n_sites - L * b))) & full;
-                // low entry: v0's top two rows; high entry: those of v0 ^ full
-                const uint32_t e2 = entry(x4(v0, L * (Ly - 2)) & (m2 << 2));
-#pragma unroll
-                for (uint32_t f = 0; f < 2; ++f) {
-                    if (f >= nz) break;
-                    const uint32_t e = f ? (e2 >> 16) : (e2 & 0xFFFFu);
-                    if ((e >> 4) != best) continue;
-                    W v = f ? static_cast<W>(v0 ^ full) : v0;
-                    const uint32_t base = (p * P.n_trans + L * b) * nz + f;
-                    if (e & 8u) {
-                        for (uint32_t a = 0; a < L; ++a) {
-                            if (v < rmin) { rmin = v; arg = base + a * nz; }
-                            if (a + 1 < L) v = xrot<W>(v, P);
-                        }
-                    } else {
-                        const uint32_t a = e & 7u;
-                        W c = v;
-                        if (a) {
-                            const W ma = static_cast<W>(lcol[a]);
-                            c = ((v << a) & ma) | ((v >> (L - a)) & ~ma & full);
-                        }
-                        if (c < rmin) { rmin = c; arg = base + a * nz; }
-                    }
-                }
-            }
+        for (uint32_t k = 0; k < 2 * LY; ++k)
+            miss |= __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, e[k] ^ pat), one))
+                    << k;
+        constexpr uint32_t all = (1u << (2 * LY)) - 1u;
+        uint32_t hits = ~miss & (NZ == 2 ? all << 16 | all : all);
+        while (hits) {
+            const uint32_t k = static_cast<uint32_t>(__builtin_ctz(hits));
+            hits &= hits - 1;
+            const uint32_t f = k >> 4, p = k & 15u, i = p >= LY ? 1u : 0u;
+            visit(i ? u[1] : u[0], i, p - (i ? LY : 0u), f);
         }
     } else {
-        // pass 1b: in those cosets only, which (p, b, f) reach it
-        // (bit (p*ly + b)*nz + f)
-        uint64_t M0 = 0, M1 = 0;
-        while (cm) {
-            const uint32_t p = static_cast<uint32_t>(__builtin_ctz(cm));
-            cm &= cm - 1;
+        u16x2 mn = {0xFFFFu, 0xFFFFu};
+#pragma unroll
+        for (uint32_t i = 0; i < kTorusMaxBases; ++i) {
+            if (i >= nb) continue;
+            const W u = pr[i] ^ static_cast<W>(cf[i * cstride]);
+            for (uint32_t b = 0; b < Ly; ++b)
+                mn = __builtin_elementwise_min(mn, __builtin_bit_cast(u16x2, entry(u, uni(b))));
+        }
+        best = nz == 2 ? min(static_cast<uint32_t>(mn.x), static_cast<uint32_t>(mn.y)) : static_cast<uint32_t>(mn.x);
+        uint64_t hp = 0, hf = 0;     // bit i * Ly + b: plain, flipped
+#pragma unroll
+        for (uint32_t i = 0; i < kTorusMaxBases; ++i) {
+            if (i >= nb) continue;
+            const W u = pr[i] ^ static_cast<W>(cf[i * cstride]);
+            for (uint32_t b = 0; b < Ly; ++b) {
+                const uint32_t e = entry(u, uni(b));
+                hp |= ((e & 0xFFFFu) == best ? 1ull : 0ull) << (i * Ly + b);
+                hf |= (nz == 2 && (e >> 16) == best ? 1ull : 0ull) << (i * Ly + b);
+            }
+        }
+        while (hp | hf) {
+            const uint32_t f = hp ? 0u : 1u;
+            uint64_t &h = hp ? hp : hf;
+            const uint32_t k = static_cast<uint32_t>(__builtin_ctzll(h));
+            h &= h - 1;
+            uint32_t i = 0, b = k;
+            while (b >= Ly) {
+                b -= Ly;
+                ++i;
+            }
             W u = pr[0];
 #pragma unroll
-            for (uint32_t q = 1; q < kTorusMaxCosets; ++q) u = (q < ncos && p == q) ? pr[q] : u;
-            u ^= static_cast<W>(cf[p * cstride]);
-#pragma unroll
-            for (uint32_t b0 = 0; b0 < (LY ? LY : 1u); ++b0) {
-                for (uint32_t b1 = 0; b1 < (LY ? 1u : Ly); ++b1) {
-                    const uint32_t b = LY ? b0 : uni(b1);
-                    const uint32_t e = entry(pair_of(u, b));
-                    const uint32_t idx = (p * Ly + b) * nz;
-                    const uint64_t hit = (((e >> 4) & 0xFFFu) == best ? 1ull : 0ull) |
-                                         ((nz == 2 && (e >> 20) == best) ? 2ull : 0ull);
-                    if (idx < 63) M0 |= hit << idx;
-                    else if (idx == 63) { M0 |= hit << 63; M1 |= hit >> 1; }
-                    else M1 |= hit << (idx - 64);
-                }
-            }
-        }
-        while (M0 | M1) {
-            uint32_t idx;
-            if (M0) {
-                idx = static_cast<uint32_t>(__builtin_ctzll(M0));
-                M0 &= M0 - 1;
-            } else {
-                idx = 64u + static_cast<uint32_t>(__builtin_ctzll(M1));
-                M1 &= M1 - 1;
-            }
-            const uint32_t f = idx % nz, pb = idx / nz;
-            const uint32_t b = pb % Ly, p = pb / Ly;
-            W v = pr[0];
-#pragma unroll
-            for (uint32_t q = 1; q < kTorusMaxCosets; ++q) v = (q < ncos && p == q) ? pr[q] : v;
-            v ^= static_cast<W>(cf[p * cstride]);
-            if (b) v = ((v << (L * b)) | (v >> (P.n_sites - L * b))) & full;
-            if (f) v ^= full;
-            const uint32_t e = entry(x4(v, L * (Ly - 2)) & (m2 << 2)) & 0xFFFFu;
-            const uint32_t base = (p * P.n_trans + L * b) * nz + f;
-            if (e & 8u) {
-                for (uint32_t a = 0; a < L; ++a) {
-                    if (v < rmin) { rmin = v; arg = base + a * nz; }
-                    if (a + 1 < L) v = xrot<W>(v, P);
-                }
-            } else {
-                const uint32_t a = e & 7u;
-                W c = v;
-                if (a) {
-                    const W ma = static_cast<W>(lcol[a]);
-                    c = ((v << a) & ma) | ((v >> (L - a)) & ~ma & full);
-                }
-                if (c < rmin) { rmin = c; arg = base + a * nz; }
-            }
+            for (uint32_t q = 1; q < kTorusMaxBases; ++q) u = (q < nb && i == q) ? pr[q] : u;
+            visit(u ^ static_cast<W>(cf[i * cstride]), i, b, f);
         }
     }
-    if constexpr (TRACK) code = arg;
-    else code = 0;
-    return rmin;
-#undef LS_IMG
+    if constexpr (TRACK) info.code = code_of(won);
+    return static_cast<W>(static_cast<W>(best) << tb) | static_cast<W>(tail);
 }
 
 // Binomial coefficient table [65][65] in device memory.

@@ -109,7 +109,7 @@ __global__ void __launch_bounds__(block_of(KIND)) k_store(StoreArgs s) {
     if constexpr (CPLX) static_cast<double2 *>(s.diag)[row] = make_double2(dre, dim_);
     else static_cast<double *>(s.diag)[row] = dre;
     W pr[kTorusCosetSlots] = {};
-    if constexpr (KIND == kOrbitTorus) row_images<W>(a.plan, r, pr);
+    if constexpr (KIND == kOrbitTorus) row_images<W, LX>(a.plan, r, pr);
     const uint64_t base = s.off[row / kSlice] + (row & (kSlice - 1));
     uint32_t k = 0;
     for (uint32_t t = a.n_diag; t < a.n_terms; ++t) {
@@ -146,7 +146,7 @@ struct StoreLaunch {
         } else {
             constexpr int BLOCK = block_of(KIND);
             const MatvecJob &j = args.job;
-            const size_t lds = lds_bytes(KIND, j.n_terms, j.n_terms - j.n_diag, j.plan.lx);
+            const size_t lds = lds_bytes(KIND, j.n_terms, j.n_terms - j.n_diag, j.plan.n_base);
             const uint64_t blocks = (j.dim + BLOCK - 1) / BLOCK;
             hipLaunchKernelGGL((k_store<W, KIND, CHI, CPLX, LX, LY, NZ>), dim3(static_cast<uint32_t>(blocks)),
                                dim3(BLOCK), lds, st, args);

@@ -1,0 +1,43 @@
+"""The torus search (merged pair table) against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import configs, lattice, rng, terms
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import paper_2308_16712_amd as ls  # noqa: E402
+
+
+@pytest.mark.parametrize("lx,ly,w,kx,point,inv", [
+    (2, 3, 3, 0, "full", 1), (2, 16, 4, 1, "none", 0), (3, 2, 3, 0, "full", 1), (3, 6, 9, 0, "full", 1),
+    (4, 4, 8, 0, "c2v", 1), (4, 4, 7, 2, "none", 0), (4, 5, 10, 0, "full", -1), (5, 5, 12, 0, "full", 0),
+    (5, 5, 5, 2, "none", 0), (6, 4, 12, 0, "full", 1), (6, 6, 4, 0, "full", 0), (6, 6, 4, 0, "c2v", 0),
+    (6, 10, 3, 0, "full", 0), (6, 10, 3, 1, "none", 0)])
+def test_torus_search_shapes(lx, ly, w, kx, point, inv):
+    """The torus search over shapes, point groups and momenta against the
+    oracle: products of two columns and one, generated and stored, at the
+    shapes where a table or a row operation degenerates (two rows, two
+    columns, rows that do not fit 32 bits below the top two)."""
+    g = lattice.torus_group(lx, ly, kx, 0, point, None, inv)
+    sec = configs.sector_from_arrays(f"torus{lx}x{ly}_w{w}_{point}_k{kx}_{inv}", lx * ly, w, g.perm, g.flip, g.chi,
+                                     terms.heisenberg_terms(lattice.torus_bonds(lx, ly, 1.0, 0.35)))
+    print(f"[gpu] {sec.name}", flush=True)
+    P = oracle.Problem(sec)
+    reps, stab = oracle.enumerate_basis(P)
+    b = ls.ls_basis_build(sec)
+    assert np.array_equal(b.copy()[0].cpu().numpy().view(np.uint64), reps)
+    op = ls.ls_operator_create(b, sec.terms)
+    x = rng.vector(5, len(reps), 2, complex_=op.is_complex)
+    y = op.matvec(torch.from_numpy(x).cuda())
+    y1 = op.matvec(torch.from_numpy(np.ascontiguousarray(x[:, 0])).cuda())
+    assert torch.equal(y[:, 0], y1)
+    ref_y = oracle.matvec(P, reps, stab, np.ascontiguousarray(x[:, 0]))
+    # every element is off by a few roundings of its value, a row sums under 200 of them
+    assert np.abs(y1.cpu().numpy() - ref_y).max() <= 1e-13 * max(1.0, np.abs(ref_y).max())
+    st = ls.ls_operator_create(b, sec.terms)
+    ls.ls_operator_store(st)
+    assert torch.equal(st.matvec(torch.from_numpy(x).cuda()), y)
+    op.check()
