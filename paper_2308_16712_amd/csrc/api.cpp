@@ -125,6 +125,7 @@ void free_operator(ls_operator *op) {
     op->used.drain();
     ls::dev_free(op->d_terms);
     ls::dev_free(op->d_cflip);
+    ls::dev_free(op->d_steps);
     ls::dev_free(op->d_err);
     ls::dev_free(op->d_st_off);
     ls::dev_free(op->d_st_width);
@@ -281,6 +282,11 @@ ls_status ls_operator_create(const ls_basis *b, uint32_t n_terms, const ls_term 
         if (!op->host_cflip.empty()) {
             op->d_cflip = ls::dev_alloc_n<uint64_t>(op->host_cflip.size(), st0);
             LS_HIP_CHECK(hipMemcpyAsync(op->d_cflip, op->host_cflip.data(), op->host_cflip.size() * sizeof(uint64_t),
+                                        hipMemcpyHostToDevice, st0));
+        }
+        if (!op->host_steps.empty()) {
+            op->d_steps = ls::dev_alloc_n<ls_step_dev>(op->host_steps.size(), st0);
+            LS_HIP_CHECK(hipMemcpyAsync(op->d_steps, op->host_steps.data(), op->host_steps.size() * sizeof(ls_step_dev),
                                         hipMemcpyHostToDevice, st0));
         }
         op->d_err = ls::dev_alloc_n<uint32_t>(1, st0);

@@ -57,7 +57,7 @@ __global__ void __launch_bounds__(batch_block(KIND, CPLX))
         const MatvecJob &a = jobs[jid];
         if (jid != cur) {
             L = lds_tables<KIND, LX, BLOCK, false, false>(a, smem);
-            stage_tables<KIND, LX, BLOCK, false, false>(a, L);
+            stage_tables<KIND, LX, BLOCK, false, false>(a, L, KIND != kOrbitTorus || a.steps == nullptr);
             __syncthreads();
             cur = jid;
         }

@@ -270,6 +270,16 @@ struct ls_term_dev {
     uint64_t sel, val, flip, sign;
 };
 
+// One step of a row's element loop: the off-diagonal term `term` (counted
+// from the first off-diagonal one), or two of them in a row that move the same
+// spins with the same coefficient (the two directions of an exchange, of
+// which a state has at most one): acts where state & sel is val or val2.
+struct ls_step_dev {
+    double re, im;          // as the terms'
+    uint64_t sel, val, val2, flip, sign;
+    uint32_t term, pad_;
+};
+
 struct ls_operator {
     const ls_basis *basis = nullptr;
     mutable ls::StreamSet used;        // streams of the calls that ran its products
@@ -277,6 +287,8 @@ struct ls_operator {
     uint32_t n_diag = 0, n_off = 0;
     ls_term_dev *d_terms = nullptr;     // diagonal terms first, then off-diagonal
     std::vector<ls_term_dev> host_terms;
+    std::vector<ls_step_dev> host_steps;
+    ls_step_dev *d_steps = nullptr;     // null: the rows walk their own lists
     // torus search: the permutation part of every base image applied to every
     // off-diagonal flip mask, [n_base][n_off]
     std::vector<uint64_t> host_cflip;

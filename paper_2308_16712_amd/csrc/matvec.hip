@@ -49,7 +49,7 @@ k_matvec(MatvecJob a, uint64_t n_lanes, uint32_t rows_per_lane, uint32_t rows_pe
     constexpr int BLOCK = block_of(KIND);
     extern __shared__ __align__(16) unsigned char smem[];
     const LdsTables L = lds_tables<KIND, LX, BLOCK>(a, smem);
-    stage_tables<KIND, LX, BLOCK>(a, L);
+    stage_tables<KIND, LX, BLOCK>(a, L, KIND != kOrbitTorus || a.steps == nullptr);
     __syncthreads();
     if (threadIdx.x >= rows_per_wg) return;
     const uint64_t lane = static_cast<uint64_t>(xcd_chunk(blockIdx.x, gridDim.x)) * rows_per_wg + threadIdx.x;
@@ -218,6 +218,8 @@ MatvecJob job_of(const ls_operator *op, const void *x, void *y, uint32_t ld, uin
     a.stab = b->d_stab;
     a.terms = op->d_terms;
     a.cflip = op->d_cflip;
+    a.steps = op->d_steps;
+    a.n_steps = static_cast<uint32_t>(op->host_steps.size());
     a.n_diag = op->n_diag;
     a.n_terms = op->n_diag + op->n_off;
     a.dim = b->dim;

@@ -51,6 +51,8 @@ struct MatvecJob {
     const uint16_t *stab;
     const ls_term_dev *terms;
     const uint64_t *cflip;  // [n_base][n_off] (torus search only)
+    const ls_step_dev *steps;   // null: rows walk their own lists of terms
+    uint32_t n_steps, pad_;
     uint32_t n_diag, n_terms;
     uint64_t dim;
     uint32_t ld;           // row stride of x and y in elements
@@ -86,17 +88,18 @@ __device__ __forceinline__ typename Val<CPLX>::T diag_times(double dre, double d
 }
 
 // Element value conj(c_t) (-1)^popcount(r & sign_t) chi(g*) sqrt(stab_j / stab_i)
-// (the term table already holds conj(c_t)); fs = sqrt(stab_j / stab_i).
+// of a term with coefficient re + i im (the term table already holds
+// conj(c_t)); fs = sqrt(stab_j / stab_i).
 template <int CHI, bool CPLX>
-__device__ __forceinline__ typename Val<CPLX>::T element_value(const ls_term_dev &Tm, uint64_t r, double fs,
-                                                               const PlanDev &P, uint32_t code) {
-    const double f = sign_of(r & Tm.sign) * fs;
+__device__ __forceinline__ typename Val<CPLX>::T element_value(double re, double im, uint64_t sign, uint64_t r,
+                                                               double fs, const PlanDev &P, uint32_t code) {
+    const double f = sign_of(r & sign) * fs;
     if constexpr (!CPLX) {
-        double coef = f * Tm.re;
+        double coef = f * re;
         if constexpr (CHI == kChiReal) coef *= P.chi[code].x;
         return coef;
     } else {
-        double cre = f * Tm.re, cim = f * Tm.im;
+        double cre = f * re, cim = f * im;
         if constexpr (CHI != kChiTrivial) {
             const double2 c = P.chi[code];
             const double tre = cre * c.x - cim * c.y;
@@ -105,6 +108,11 @@ __device__ __forceinline__ typename Val<CPLX>::T element_value(const ls_term_dev
         }
         return make_double2(cre, cim);
     }
+}
+template <int CHI, bool CPLX>
+__device__ __forceinline__ typename Val<CPLX>::T element_value(const ls_term_dev &Tm, uint64_t r, double fs,
+                                                               const PlanDev &P, uint32_t code) {
+    return element_value<CHI, CPLX>(Tm.re, Tm.im, Tm.sign, r, fs, P, code);
 }
 
 // acc += value * x_j
@@ -193,10 +201,13 @@ __device__ __forceinline__ LdsTables lds_tables(const MatvecJob &a, unsigned cha
     return L;
 }
 
-// All threads of the workgroup stage the job's tables; caller syncs.
+// All threads of the workgroup stage the job's tables (without `lists`, not
+// the terms and their flip images: run_rows_steps reads them as scalars);
+// caller syncs.
 template <int KIND, uint32_t LX, int BLOCK, bool TAB = uses_ratio_table(KIND, false), bool ARG = true>
-__device__ __forceinline__ void stage_tables(const MatvecJob &a, const LdsTables &L) {
-    for (uint32_t t = threadIdx.x; t < a.n_terms; t += BLOCK) L.terms[t] = a.terms[t];
+__device__ __forceinline__ void stage_tables(const MatvecJob &a, const LdsTables &L, bool lists = true) {
+    if (lists)
+        for (uint32_t t = threadIdx.x; t < a.n_terms; t += BLOCK) L.terms[t] = a.terms[t];
     if constexpr (KIND == kOrbitTorus) {
         const uint32_t n_off = a.n_terms - a.n_diag;
         const uint32_t lut_n = 1u << (2 * (LX ? LX : a.plan.lx));
@@ -205,7 +216,8 @@ __device__ __forceinline__ void stage_tables(const MatvecJob &a, const LdsTables
             if constexpr (ARG) const_cast<uint32_t *>(L.arg)[q] = a.plan.pair_arg[q];
         }
         if (threadIdx.x < 8) L.col[threadIdx.x] = a.plan.col_ge[threadIdx.x];
-        for (uint32_t q = threadIdx.x; q < n_off * a.plan.n_base; q += BLOCK) L.cflip[q] = a.cflip[q];
+        if (lists)
+            for (uint32_t q = threadIdx.x; q < n_off * a.plan.n_base; q += BLOCK) L.cflip[q] = a.cflip[q];
     }
     if (a.search.mode == kLookupStaged)
         for (uint32_t q = threadIdx.x; q < a.search.n_bkt; q += BLOCK) L.bkt[q] = a.search.buckets[q];
@@ -254,17 +266,15 @@ __device__ __forceinline__ double stab_factor(const PlanDev &P, const LdsTables 
 }
 
 // Sum of the diagonal terms acting on r: dre + i dim_.
-template <bool CPLX>
-__device__ __forceinline__ void diag_sum(const ls_term_dev *sterm, uint32_t n_diag, uint64_t r, double &dre,
-                                         double &dim_) {
+template <bool CPLX, typename Terms>
+__device__ __forceinline__ void diag_sum(Terms terms, uint32_t n_diag, uint64_t r, double &dre, double &dim_) {
     dre = 0.0;
     dim_ = 0.0;
     for (uint32_t q = 0; q < n_diag; ++q) {
-        const ls_term_dev &D = sterm[q];
-        if ((r & D.sel) != D.val) continue;
-        const double sg = sign_of(r & D.sign);
-        dre += sg * D.re;
-        if constexpr (CPLX) dim_ += sg * D.im;
+        if ((r & terms[q].sel) != terms[q].val) continue;
+        const double sg = sign_of(r & terms[q].sign);
+        dre += sg * terms[q].re;
+        if constexpr (CPLX) dim_ += sg * terms[q].im;
     }
 }
 
@@ -436,6 +446,61 @@ __device__ __forceinline__ void run_rows_ahead(const MatvecJob &a, const LdsTabl
     }
 }
 
+// Rows row, row + step, ... (count of them, below dim) of one job on a torus
+// whose operator has steps: the lanes of a wavefront take the steps together,
+// each lane those that act on its row.  Neighbouring lanes hold neighbouring
+// rows, which agree in their high bits: a step up there acts on all of them or
+// on none, their neighbours stay neighbours, and the blocks of the hash index
+// and the entries of x that they read share lines.  Lanes that walk lists of
+// their own are at different terms after a few elements: 6x6 product 25.7 ms
+// and 168 GB of L2 misses, against 20.6 ms and 123 GB.  The steps and the
+// diagonal terms are scalar loads, and no lane scans for its next term.  A
+// row's elements are summed one by one in term order in every form, so the
+// bits are the same.  Rings keep the lists: their searches saturate the VALU,
+// and idle lanes cost more than the lines (38-spin chain 75 ms, 81 in steps).
+template <typename W, int KIND, int CHI, bool CPLX, int NR, uint32_t LX, uint32_t LY, uint32_t NZ, bool STAGED>
+__device__ __forceinline__ void run_rows_steps(const MatvecJob &a, const LdsTables &L, uint64_t row, uint64_t step,
+                                               uint32_t count) {
+    constexpr bool TAB = uses_ratio_table(KIND, STAGED);
+    using T = typename Val<CPLX>::T;
+    const T *x = static_cast<const T *>(a.x);
+    T *y = static_cast<T *>(a.y);
+    const ConstPtr<ls_step_dev> steps = as_const(a.steps);
+    const ConstPtr<uint64_t> cflip = as_const(a.cflip);
+    for (uint32_t k = 0; k < count && row < a.dim; ++k, row += step) {
+        const uint64_t r = a.search.reps[row];
+        const RowStab<TAB> rs = row_stab<TAB>(a.plan, L, a.stab[row]);
+        T acc[NR];
+        {
+            double dre, dim_;
+            diag_sum<CPLX>(as_const(a.terms), a.n_diag, r, dre, dim_);
+#pragma unroll
+            for (int q = 0; q < NR; ++q) acc[q] = diag_times<CPLX>(dre, dim_, x[row * a.ld + a.col + q]);
+        }
+        W pr[kTorusCosetSlots] = {};
+        row_images<W, LX>(a.plan, r, pr);
+        for (uint32_t s = 0; s < a.n_steps; ++s) {
+            const uint64_t m = r & steps[s].sel;
+            if (m != steps[s].val && m != steps[s].val2) continue;
+            OrbitInfo info;
+            const W rep = torus_orbit_min<W, CHI != kChiTrivial, false, LX, LY, NZ>(
+                a.plan, pr, cflip + steps[s].term, a.n_terms - a.n_diag, L.lut, L.arg, L.col, info);
+            uint32_t st_j = 0;
+            const int64_t j = lookup_stab<STAGED>(a, L, static_cast<uint64_t>(rep), st_j);
+            if (j < 0) {
+                lookup_miss<W, KIND, CHI>(a, rep);
+                continue;
+            }
+            const T c = element_value<CHI, CPLX>(steps[s].re, steps[s].im, steps[s].sign, r,
+                                                 stab_factor(a.plan, L, rs, st_j), a.plan, info.code);
+#pragma unroll
+            for (int q = 0; q < NR; ++q) accumulate(acc[q], c, x[j * a.ld + a.col + q]);
+        }
+#pragma unroll
+        for (int q = 0; q < NR; ++q) y[row * a.ld + a.col + q] = acc[q];
+    }
+}
+
 // Rows row0, row0 + step, ... (count of them, below dim) of one job.
 // STAGED: the batched launch, whose job's search layout may be a bucket table
 // staged in LDS; the other launches never meet one.
@@ -443,6 +508,12 @@ template <typename W, int KIND, int CHI, bool CPLX, int NR, uint32_t LX, uint32_
           bool STAGED = false>
 __device__ __forceinline__ void run_rows(const MatvecJob &a, const LdsTables &L, uint64_t row0, uint64_t step,
                                          uint32_t count) {
+    if constexpr (KIND == kOrbitTorus) {
+        if (a.steps) {
+            run_rows_steps<W, KIND, CHI, CPLX, NR, LX, LY, NZ, STAGED>(a, L, row0, step, count);
+            return;
+        }
+    }
     // the pipelined loop pays off where up to four columns leave registers
     // for the element in flight (64 ring sectors x 4 columns: 271 -> 259 ms
     // as separate products, 267 -> 261 ms batched); wider products keep the

@@ -14,6 +14,15 @@
 
 namespace ls {
 
+// Memory that no kernel writes while it is read this way: at an index that is
+// the same in all lanes, the reads are scalar loads.
+template <typename T>
+using ConstPtr = const __attribute__((address_space(4))) T *;
+template <typename T>
+__device__ __forceinline__ ConstPtr<T> as_const(const T *p) {
+    return (ConstPtr<T>)p;
+}
+
 // Structure kinds the kernels are specialised for.
 enum OrbitKind : int {
     kOrbitGeneric = 0,   // runtime lx, ly (ring, torus, or no translations)
@@ -331,8 +340,8 @@ struct OrbitInfo {
 //   lcol  col_ge masks.
 constexpr uint32_t kTorusMaxBases = kTorusCosetSlots;
 
-template <typename W, bool TRACK, bool COUNT, uint32_t LX, uint32_t LY, uint32_t NZ>
-__device__ __forceinline__ W torus_orbit_min(const PlanDev &P, const W *pr, const uint64_t *cf, uint32_t cstride,
+template <typename W, bool TRACK, bool COUNT, uint32_t LX, uint32_t LY, uint32_t NZ, typename FlipPtr>
+__device__ __forceinline__ W torus_orbit_min(const PlanDev &P, const W *pr, FlipPtr cf, uint32_t cstride,
                                              const uint32_t *lut, const uint32_t *arg, const uint64_t *lcol,
                                              OrbitInfo &info) {
     // the rows below the top two, in 32 bits where they fit

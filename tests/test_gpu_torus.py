@@ -41,3 +41,42 @@ def test_torus_search_shapes(lx, ly, w, kx, point, inv):
     ls.ls_operator_store(st)
     assert torch.equal(st.matvec(torch.from_numpy(x).cuda()), y)
     op.check()
+
+
+@pytest.mark.parametrize("extra", ["pairs", "single", "ising", "split"])
+@pytest.mark.parametrize("lx,ly,w,inv", [(4, 4, 8, 1), (5, 6, 4, 0), (6, 6, 5, 0)])
+def test_steps_and_lists_agree(lx, ly, w, inv, extra):
+    """Large enough or not, in steps or in lists: operators whose terms form
+    steps (exchanges, both directions in a row), whose directions are apart
+    (lists), with diagonal terms only, and with unequal coefficients in the
+    two directions (no pair), against the oracle and the stored form."""
+    g = lattice.torus_group(lx, ly, 0, 0, "full", None, inv)
+    t = terms.heisenberg_terms(lattice.torus_bonds(lx, ly, 1.0, 0.35))
+    diag, off = t[t["flip"] == 0], t[t["flip"] != 0]
+    if extra == "single":     # one direction of all bonds, then the other
+        t = np.concatenate([diag, off[0::2], off[1::2]])
+    elif extra == "ising":
+        t = diag
+    elif extra == "split":    # every direction twice, as halves: equal coefficients on one state
+        half = off.copy()
+        half["re"] /= 2
+        t = np.concatenate([diag, np.repeat(half, 2)])
+    sec = configs.sector_from_arrays(f"steps{lx}x{ly}", lx * ly, w, g.perm, g.flip, g.chi, t)
+    print(f"[gpu] {sec.name} {extra}", flush=True)
+    P = oracle.Problem(sec)
+    reps, stab = oracle.enumerate_basis(P)
+    b = ls.ls_basis_build(sec)
+    op, st = ls.ls_operator_create(b, t), ls.ls_operator_create(b, t)
+    ls.ls_operator_store(st)
+    for cols in (1, 2, 5):
+        x = torch.from_numpy(np.ascontiguousarray(rng.vector(6, len(reps), cols).reshape(len(reps), cols))).cuda()
+        y = op.matvec(x)
+        assert torch.equal(y, st.matvec(x))
+        B = ls.Batch([op], [cols])
+        yb = torch.empty_like(x)
+        B.matvec([x], [yb])
+        assert torch.equal(yb, y)
+        want = oracle.matvec(P, reps, stab, np.ascontiguousarray(x[:, 0].cpu().numpy()))
+        # a few roundings an element, under 300 elements a row
+        assert np.abs(y[:, 0].cpu().numpy() - want).max() <= 1e-13 * max(1.0, np.abs(want).max())
+    op.check()
