@@ -214,11 +214,141 @@ __device__ __forceinline__ uint64_t ring64_mirror(uint64_t starts, uint32_t L, u
     return rotr_n(r, L - 1, n, full);
 }
 
+// What a search found beside the smallest image: with TRACK the code of an
+// element reaching it, with COUNT how many images equal it (the stabilizer
+// size of the orbit's states) and whether two elements that reach it have
+// characters that differ (the projector annihilates the orbit).
+struct OrbitInfo {
+    uint32_t code = 0, count = 0;
+    bool mixed = false;
+};
+
+// Notes the image v of the element with code `code` (given as a function): the
+// smallest so far, and with COUNT how many are equal to it, the smallest of
+// their codes, and whether their characters differ.
+template <bool TRACK, bool COUNT, typename W, typename Code>
+__device__ __forceinline__ void fold_image(const PlanDev &P, W v, Code &&code, W &best, OrbitInfo &info) {
+    if constexpr (COUNT) {
+        if (v == best && info.count) {
+            const uint32_t c = code();
+            const double2 c0 = P.chi[info.code], c1 = P.chi[c];
+            ++info.count;
+            info.mixed = info.mixed || fabs(c0.x - c1.x) + fabs(c0.y - c1.y) > 1e-6;
+            info.code = min(info.code, c);
+        }
+    }
+    if (v < best || (COUNT && info.count == 0)) {
+        best = v;
+        if constexpr (TRACK) info.code = code();
+        if constexpr (COUNT) {
+            info.count = 1;
+            info.mixed = false;
+        }
+    }
+}
+
+// Folds the rotations of the ring word w (n <= 32, or 32 < n < 64 in 64 bits)
+// that can be the orbit's smallest into `best`; with `mirror` also those of
+// the reversed word, with spin inversion also of the flipped ones.  The
+// smallest image has the longest zero run on top.  With spin inversion the
+// runs of equal spins are the zero runs of the boundaries w ^ (w >> 1), so
+// one search finds the zero and the one runs.  The word is doubled (as far as
+// 64 bits go), so windows that wrap are plain shifts: doubled windows of 2, 4
+// and 8, then binary lifting of the length.  For a run starting at bit i, the
+// rotation y of the (flipped) word that brings it to the bottom gives both
+// images: y >> length has the run on top, and so has y reversed.  Code of
+// rotating left by k: code0 + k * |Z| + flip, mirrored mcode0 + i * |Z| + flip.
+// false: a run longer than the doubled word shows, or a constant word (the
+// caller compares every rotation).  About 45 instructions and 15 to 25 a run,
+// where 32 sites took 4 for each of 128 images (32-site ring product 1.34 ms)
+// and more sites 118 for each of the zero and the one runs (38-spin chain
+// 75 ms, VALU busy all the time).
+template <typename W, bool TRACK, bool COUNT>
+__device__ __forceinline__ bool ring_fold(const PlanDev &P, W w, bool mirror, uint32_t code0, uint32_t mcode0, W &best,
+                                          OrbitInfo &info) {
+    constexpr bool SMALL = sizeof(W) == 4;
+    const uint32_t n = P.n_sites, pf = P.pair_flip ? 1u : 0u, nz = 1u + pf;
+    const W full = static_cast<W>(P.full);
+    const uint32_t seen = (SMALL ? 2 * n : 64u) - pf;      // bits of z that tell
+    const uint64_t ext = static_cast<uint64_t>(w) | static_cast<uint64_t>(w) << (SMALL ? n : n & 63u);
+    const uint64_t z = ~(pf ? ext ^ (ext >> 1) : ext) & (~0ull >> (64 - seen));
+    const uint64_t z2 = z & (z >> 1), z4 = z2 & (z2 >> 2), z8 = z4 & (z4 >> 4);
+    uint64_t cur = z;
+    uint32_t len = 1;
+    auto lift = [&](uint64_t zl, uint32_t l) {
+        const uint64_t t = cur & (zl >> len);
+        if (t != 0) {
+            cur = t;
+            len += l;
+        }
+    };
+    lift(z8, 8);
+    lift(z4, 4);
+    lift(z2, 2);
+    lift(z, 1);
+    if (z == 0) {                                          // no two equal neighbours
+        cur = P.full;
+        len = 0;
+    } else if (len == 16) {
+        while (len < n && (cur & (z >> len)) != 0) {
+            cur &= z >> len;
+            ++len;
+        }
+    }
+    if (len + n > seen || w == 0 || w == full) return false;
+    const uint32_t run = len + pf;
+    W starts = static_cast<W>(cur) & full;
+    while (starts) {
+        const uint32_t i = SMALL ? static_cast<uint32_t>(__builtin_ctz(static_cast<uint32_t>(starts)))
+                                 : static_cast<uint32_t>(__builtin_ctzll(static_cast<uint64_t>(starts)));
+        starts &= starts - 1;
+        const uint32_t f = pf ? static_cast<uint32_t>(w >> i) & 1u : 0u;
+        W y;
+        if constexpr (SMALL) {
+            y = static_cast<W>((f ? ~ext : ext) >> i) & full;
+        } else {
+            const W wf = f ? w ^ full : w;
+            y = ((wf >> i) | (wf << (n - i))) & full;
+        }
+        fold_image<TRACK, COUNT>(P, static_cast<W>(y >> run), [&] {
+            const uint32_t k = 2 * n - i - run;
+            return code0 + (k >= n ? k - n : k) * nz + f;
+        }, best, info);
+        if (mirror) {
+            fold_image<TRACK, COUNT>(P, bit_reverse<W>(y, n), [&] { return mcode0 + i * nz + f; }, best, info);
+        }
+    }
+    return true;
+}
+
+// The orbit minimum of a ring word by ring_fold over the cosets (the plain
+// reversal folded into the identity's); false as in ring_fold.
+template <typename W, bool TRACK, bool COUNT>
+__device__ __forceinline__ bool ring_orbit_min(const PlanDev &P, W s, W &best, OrbitInfo &info) {
+    const uint32_t nz = P.pair_flip ? 2u : 1u, per = P.n_sites * nz;
+    if (P.n_cosets == 2 && P.cosets[1].kind == kCosetReverse && P.cosets[1].flip == 0)
+        return ring_fold<W, TRACK, COUNT>(P, s, true, 0, per, best, info);
+    for (uint32_t p0 = 0; p0 < P.n_cosets; ++p0) {
+        const uint32_t p = uni(p0);
+        const W u = p == 0 ? s : apply_coset<W>(P.cosets[p], s, P);
+        if (!ring_fold<W, TRACK, COUNT>(P, u, false, p * per, 0, best, info)) return false;
+    }
+    return true;
+}
+
 // Orbit minimum; with TRACK also the code of the first element reaching it.
 template <typename W, int KIND, bool TRACK>
 __device__ __forceinline__ W orbit_min(const PlanDev &P, W s, uint32_t &code) {
     W best = s;
     uint32_t arg = 0;
+    if constexpr (KIND == kOrbitRing32 || KIND == kOrbitRing64) {
+        OrbitInfo info;
+        W least = static_cast<W>(~static_cast<W>(0));
+        if (ring_orbit_min<W, TRACK, false>(P, s, least, info)) {
+            code = info.code;
+            return least;
+        }
+    }
     if constexpr (KIND == kOrbitRing64) {
         const uint64_t full = P.full;
         const uint32_t n = P.n_sites;
@@ -304,15 +434,6 @@ __device__ __forceinline__ uint32_t pair_offset(W u, uint32_t b, uint32_t L, uin
     if (ty >= 1) return x4(L * (ty - 1)) & (m2 << 2);
     return ((static_cast<uint32_t>(u) & rm) << (L + 2)) | (x4(L * (ly - 1)) & (rm << 2));
 }
-
-// What the torus search found: the smallest image, with TRACK the code of an
-// element reaching it, with COUNT how many images equal it (the stabilizer
-// size of the orbit's states) and whether two elements that reach it have
-// characters that differ (the projector annihilates the orbit).
-struct OrbitInfo {
-    uint32_t code = 0, count = 0;
-    bool mixed = false;
-};
 
 // Pruned orbit minimum on an lx-by-ly torus (lx <= 6, ly >= 2).
 //
