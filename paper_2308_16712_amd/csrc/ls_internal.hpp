@@ -132,6 +132,12 @@ struct GroupPlan {
     uint64_t col_ge[8] = {};        // bits with x >= a in every row
 };
 
+// Square tori with the full point group (eight cosets from two base images)
+// and spin inversion: the shapes with a compile-time torus search.
+inline bool square_torus(const GroupPlan &p) {
+    return p.torus && p.lx == p.ly && p.cosets.size() == 8 && p.base_coset.size() == 2 && p.op_flips == 0 && p.pair_flip;
+}
+
 // Validates the descriptor and compiles the plan.  Throws Error.
 GroupPlan compile_group(const ls_sector_desc &d);
 

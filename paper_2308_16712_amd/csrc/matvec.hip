@@ -246,14 +246,10 @@ Variant variant_of(const ls_operator *op) {
         v.kind = kOrbitRing64;
     } else if (torus) {
         v.kind = kOrbitTorus;
-        const uint32_t nz = gp.pair_flip ? 2 : 1;
-        // compile-time shapes: square tori with the full point group (eight
-        // cosets from two base images) and spin inversion
-        if (gp.cosets.size() == 8 && gp.base_coset.size() == 2 && gp.op_flips == 0 && nz == 2 &&
-            ((gp.lx == 6 && gp.ly == 6) || (gp.lx == 4 && gp.ly == 4))) {
+        if (square_torus(gp) && (gp.lx == 6 || gp.lx == 4)) {
             v.lx = gp.lx;
             v.ly = gp.ly;
-            v.nz = nz;
+            v.nz = 2;
         }
     } else {
         v.kind = kOrbitGeneric;

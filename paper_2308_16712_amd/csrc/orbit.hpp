@@ -516,19 +516,10 @@ __device__ __forceinline__ W torus_orbit_min(const PlanDev &P, const W *pr, Flip
             z = ((z << a) & ma & tmask) | ((z >> (L - a)) & ~ma);
             const uint32_t w = i << 16 | b << 8 | f << 7 | j;
             if constexpr (COUNT) {
-                if (z == tail && info.count) {
-                    ++info.count;
-                    const double2 c0 = P.chi[code_of(won)], c1 = P.chi[code_of(w)];
-                    info.mixed = info.mixed || fabs(c0.x - c1.x) + fabs(c0.y - c1.y) > 1e-6;
-                }
-            }
-            if (z < tail || (COUNT && info.count == 0)) {
+                fold_image<true, true>(P, z, [&] { return code_of(w); }, tail, info);
+            } else if (z < tail) {
                 tail = z;
                 if constexpr (TRACK) won = w;
-                if constexpr (COUNT) {
-                    info.count = 1;
-                    info.mixed = false;
-                }
             }
         }
     };
@@ -599,7 +590,7 @@ __device__ __forceinline__ W torus_orbit_min(const PlanDev &P, const W *pr, Flip
             visit(u ^ static_cast<W>(cf[i * cstride]), i, b, f);
         }
     }
-    if constexpr (TRACK) info.code = code_of(won);
+    if constexpr (TRACK && !COUNT) info.code = code_of(won);
     return static_cast<W>(static_cast<W>(best) << tb) | static_cast<W>(tail);
 }
 

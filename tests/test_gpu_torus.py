@@ -11,6 +11,27 @@ pytestmark = pytest.mark.gpu
 import paper_2308_16712_amd as ls  # noqa: E402
 
 
+def _check_states(sec, b):
+    """state_info of members, random words of the weight and of others, and
+    words with bits past the sites, against the oracle."""
+    P = oracle.Problem(sec)
+    reps, _ = oracle.enumerate_basis(P)
+    n = sec.n_sites
+    words = rng.counter_u64(4, np.arange(3000, dtype=np.uint64)) & np.uint64((1 << n) - 1)
+    pick = rng.counter_u64(5, np.arange(3000, dtype=np.uint64)) % np.uint64(len(reps))
+    k = (rng.counter_u64(6, np.arange(3000, dtype=np.uint64)) % np.uint64(n)).astype(np.uint64)
+    full = np.uint64((1 << n) - 1)
+    turned = ((reps[pick] << k) | (reps[pick] >> (np.uint64(n) - k))) & full
+    states = np.concatenate([reps[:2000], turned, words, np.array([0, full, 1], np.uint64)]).astype(np.uint64)
+    got = [t.cpu().numpy() for t in b.state_info(torch.from_numpy(states.view(np.int64)).cuda())]
+    want = oracle.state_info(P, states)
+    assert np.array_equal(got[0].view(np.uint64), want[0])
+    w = want[1]
+    w = np.stack([w.real, w.imag], axis=1) if np.iscomplexobj(w) else w.reshape(len(states), 2)
+    assert np.abs(got[1] - w).max() <= 1e-9          # characters are given to 1e-9
+    assert np.abs(got[2] - want[2]).max() <= 1e-15   # one division and one root
+
+
 @pytest.mark.parametrize("lx,ly,w,kx,point,inv", [
     (2, 3, 3, 0, "full", 1), (2, 16, 4, 1, "none", 0), (3, 2, 3, 0, "full", 1), (3, 6, 9, 0, "full", 1),
     (4, 4, 8, 0, "c2v", 1), (4, 4, 7, 2, "none", 0), (4, 5, 10, 0, "full", -1), (5, 5, 12, 0, "full", 0),
@@ -41,6 +62,7 @@ def test_torus_search_shapes(lx, ly, w, kx, point, inv):
     ls.ls_operator_store(st)
     assert torch.equal(st.matvec(torch.from_numpy(x).cuda()), y)
     op.check()
+    _check_states(sec, b)
 
 
 @pytest.mark.parametrize("extra", ["pairs", "single", "ising", "split"])
