@@ -144,22 +144,69 @@ GroupPlan compile_group(const ls_sector_desc &d) {
         LS_REQUIRE(std::fabs(d.chi[2 * g] - 1.0) < 1e-9 && std::fabs(d.chi[2 * g + 1]) < 1e-9,
                    "the identity must have character 1");
     }
-    // closure and homomorphism: chi(g h) = chi(g) chi(h)
+    // closure and homomorphism: chi(g h) = chi(g) chi(h) for all pairs.  The
+    // product of a pair is found through generators: right multiplication by
+    // a generator takes |G| compositions and lookups, a product by h = h' s is
+    // the product by h' times s, so only |G| x (generators) permutations are
+    // composed instead of |G|^2 (6x6 torus, 576 elements: 15 ms of a build).
+    // A list that is not closed is composed pair by pair for its error.
     std::vector<uint16_t> comp(n);
-    for (uint32_t g = 0; g < ng; ++g) {
-        const uint16_t *pg = d.perm + static_cast<size_t>(g) * n;
-        for (uint32_t h = 0; h < ng; ++h) {
-            const uint16_t *ph = d.perm + static_cast<size_t>(h) * n;
-            for (uint32_t i = 0; i < n; ++i) comp[i] = pg[ph[i]];
-            auto it = index.find(key_of(comp.data(), n, d.flip[g] ^ d.flip[h]));
-            LS_REQUIRE(it != index.end(), "the elements are not closed under composition");
-            const int gh = it->second;
-            const double are = d.chi[2 * g], aim = d.chi[2 * g + 1];
-            const double bre = d.chi[2 * h], bim = d.chi[2 * h + 1];
-            const double pre = are * bre - aim * bim, pim = are * bim + aim * bre;
-            LS_REQUIRE(std::fabs(pre - d.chi[2 * gh]) < 1e-9 && std::fabs(pim - d.chi[2 * gh + 1]) < 1e-9,
-                       "chi is not a one-dimensional representation (chi(gh) != chi(g) chi(h))");
+    auto product = [&](uint32_t g, uint32_t h) -> int {
+        const uint16_t *pg = d.perm + static_cast<size_t>(g) * n, *ph = d.perm + static_cast<size_t>(h) * n;
+        for (uint32_t i = 0; i < n; ++i) comp[i] = pg[ph[i]];
+        auto it = index.find(key_of(comp.data(), n, d.flip[g] ^ d.flip[h]));
+        return it == index.end() ? -1 : it->second;
+    };
+    auto check_pair = [&](uint32_t g, uint32_t h, int gh) {
+        LS_REQUIRE(gh >= 0, "the elements are not closed under composition");
+        const double are = d.chi[2 * g], aim = d.chi[2 * g + 1];
+        const double bre = d.chi[2 * h], bim = d.chi[2 * h + 1];
+        const double pre = are * bre - aim * bim, pim = are * bim + aim * bre;
+        LS_REQUIRE(std::fabs(pre - d.chi[2 * gh]) < 1e-9 && std::fabs(pim - d.chi[2 * gh + 1]) < 1e-9,
+                   "chi is not a one-dimensional representation (chi(gh) != chi(g) chi(h))");
+    };
+    {
+        // right[k][g] = g * generator k; reached: h = from[h] * generator via[h]
+        std::vector<std::vector<int>> right;
+        std::vector<int> from(ng, -1), via(ng, -1), order;
+        std::vector<char> reached(ng, 0);
+        order.push_back(it_id->second);
+        reached[it_id->second] = 1;
+        bool closed = true;
+        for (uint32_t g = 0; g < ng && closed; ++g) {
+            if (reached[g]) continue;
+            std::vector<int> r(ng);
+            for (uint32_t a = 0; a < ng && closed; ++a) {
+                r[a] = product(a, g);
+                closed = r[a] >= 0;
+            }
+            if (!closed) break;
+            right.push_back(std::move(r));
+            // all words in the generators so far
+            for (size_t at = 0; at < order.size(); ++at)
+                for (size_t k = 0; k < right.size(); ++k) {
+                    const int h = right[k][order[at]];
+                    if (!reached[h]) {
+                        reached[h] = 1;
+                        from[h] = order[at];
+                        via[h] = static_cast<int>(k);
+                        order.push_back(h);
+                    }
+                }
         }
+        if (!closed) {
+            for (uint32_t g = 0; g < ng; ++g)
+                for (uint32_t h = 0; h < ng; ++h) check_pair(g, h, product(g, h));
+        }
+        // by[h][g] = g * h along the words (a word's beginning comes first)
+        std::vector<std::vector<int>> by(ng);
+        for (int h : order) {
+            by[h].resize(ng);
+            for (uint32_t g = 0; g < ng; ++g)
+                by[h][g] = from[h] < 0 ? static_cast<int>(g) : right[via[h]][by[from[h]][g]];
+        }
+        for (uint32_t h = 0; h < ng; ++h)
+            for (uint32_t g = 0; g < ng; ++g) check_pair(g, h, by[h][g]);
     }
 
     GroupPlan P;
