@@ -1,5 +1,6 @@
 // The C ABI: argument checks, exception-to-status translation, handles.
 
+#include <algorithm>
 #include <cstring>
 #include <new>
 
@@ -107,6 +108,7 @@ void free_basis(ls_basis *b) {
     ls::dev_free(b->d_reps);
     ls::dev_free(b->d_stab);
     ls::dev_free(b->d_skip);
+    ls::dev_free(b->d_rank);
     ls::dev_free(b->d_low_rank);
     ls::dev_free(b->d_dropped);
     ls::dev_free(b->d_buckets);
@@ -125,7 +127,6 @@ void free_operator(ls_operator *op) {
     op->used.drain();
     ls::dev_free(op->d_terms);
     ls::dev_free(op->d_cflip);
-    ls::dev_free(op->d_steps);
     ls::dev_free(op->d_err);
     ls::dev_free(op->d_st_off);
     ls::dev_free(op->d_st_width);
@@ -275,18 +276,19 @@ ls_status ls_operator_create(const ls_basis *b, uint32_t n_terms, const ls_term 
         // created without a stream: the default stream, waited for here
         hipStream_t st0 = nullptr;
         op->used.add(st0);
-        const size_t bytes = std::max<size_t>(op->host_terms.size(), 1) * sizeof(ls_term_dev);
-        op->d_terms = ls::dev_alloc_n<ls_term_dev>(std::max<size_t>(op->host_terms.size(), 1), st0);
-        if (!op->host_terms.empty())
-            LS_HIP_CHECK(hipMemcpyAsync(op->d_terms, op->host_terms.data(), bytes, hipMemcpyHostToDevice, st0));
+        // terms, then steps, in one block
+        const size_t bytes = op->host_terms.size() * sizeof(ls_term_dev);
+        const size_t step_bytes = op->host_steps.size() * sizeof(ls_step_dev);
+        std::vector<unsigned char> table(bytes + step_bytes);
+        std::copy_n(reinterpret_cast<const unsigned char *>(op->host_terms.data()), bytes, table.data());
+        std::copy_n(reinterpret_cast<const unsigned char *>(op->host_steps.data()), step_bytes, table.data() + bytes);
+        unsigned char *d_table = ls::dev_alloc_n<unsigned char>(std::max<size_t>(table.size(), 1), st0);
+        op->d_terms = reinterpret_cast<ls_term_dev *>(d_table);
+        if (step_bytes) op->d_steps = reinterpret_cast<ls_step_dev *>(d_table + bytes);
+        if (!table.empty()) LS_HIP_CHECK(hipMemcpyAsync(d_table, table.data(), table.size(), hipMemcpyHostToDevice, st0));
         if (!op->host_cflip.empty()) {
             op->d_cflip = ls::dev_alloc_n<uint64_t>(op->host_cflip.size(), st0);
             LS_HIP_CHECK(hipMemcpyAsync(op->d_cflip, op->host_cflip.data(), op->host_cflip.size() * sizeof(uint64_t),
-                                        hipMemcpyHostToDevice, st0));
-        }
-        if (!op->host_steps.empty()) {
-            op->d_steps = ls::dev_alloc_n<ls_step_dev>(op->host_steps.size(), st0);
-            LS_HIP_CHECK(hipMemcpyAsync(op->d_steps, op->host_steps.data(), op->host_steps.size() * sizeof(ls_step_dev),
                                         hipMemcpyHostToDevice, st0));
         }
         op->d_err = ls::dev_alloc_n<uint32_t>(1, st0);

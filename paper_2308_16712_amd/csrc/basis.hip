@@ -220,51 +220,69 @@ __global__ void k_clear_u64(unsigned long long *p) { *p = 0ull; }
 __global__ void __launch_bounds__(kBlock) k_count_groups(const uint64_t *reps, uint64_t d, uint32_t shift,
                                                          unsigned long long *total) {
     __shared__ uint32_t sh[kBlock];
-    const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    const bool head = i < d && (i == 0 || (reps[i] >> shift) != (reps[i - 1] >> shift));
-    const uint32_t c = block_sum(head ? 1u : 0u, sh);
+    uint32_t heads = 0;
+    const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kBlock;
+    for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x; i < d; i += stride)
+        heads += (i == 0 || (reps[i] >> shift) != (reps[i - 1] >> shift)) ? 1u : 0u;
+    const uint32_t c = block_sum(heads, sh);
     if (threadIdx.x == 0 && c != 0) atomicAdd(total, static_cast<unsigned long long>(c));
 }
 
-// Hash index: the first representative of every group claims the first free
-// line of the group's probe sequence with a compare-and-swap (groups are
-// distinct and the table has more lines than groups, so every sequence ends)
-// and fills its eight blocks.
-__global__ void __launch_bounds__(kBlock) k_index_fill(SearchDev S, IndexBlock *table) {
+// Hash index, first pass: the first representative of every group claims the
+// first free line of the group's probe sequence with a compare-and-swap
+// (groups are distinct and the table has more lines than groups, so every
+// sequence ends) and marks its eight blocks as the group's, empty.
+__global__ void __launch_bounds__(kBlock) k_index_claim(SearchDev S, IndexBlock *table) {
     const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
     if (i >= S.dim) return;
     const uint32_t shift = S.low_bits + kGroupBits;
-    uint64_t key = S.reps[i];
-    const uint64_t g = key >> shift;
+    const uint64_t g = S.reps[i] >> shift;
     if (i > 0 && (S.reps[i - 1] >> shift) == g) return;
     const uint32_t tag = static_cast<uint32_t>(g);
     uint64_t line = line_of(g, S.hash_shift);
     for (;;) {
         // tag and position of the line's first block: ~0 while it is free
         unsigned long long *w = reinterpret_cast<unsigned long long *>(&table[line << kGroupBits].base);
-        const unsigned long long mine = static_cast<unsigned long long>(tag) << 32 | static_cast<uint32_t>(i);
+        const unsigned long long mine = static_cast<unsigned long long>(tag) << 32;
         if (atomicCAS(w, ~0ull, mine) == ~0ull) break;
         line = (line + 1) & S.hash_mask;
     }
-    const uint64_t hi = (g >> 32) << kBlockTagHi;
-    uint64_t j = i;
     for (uint32_t b = 0; b < (1u << kGroupBits); ++b) {
-        uint64_t bits = hi, stab = 0;
-        const uint32_t base = static_cast<uint32_t>(j);
-        bool one = true;
-        for (; j < S.dim; ++j) {
-            key = S.reps[j];
-            if ((key >> shift) != g || ((key >> S.low_bits) & ((1u << kGroupBits) - 1)) != b) break;
-            bits |= 1ull << low_rank(S, key);
-            const uint64_t st = S.stab[j];
-            if (stab == 0) stab = st;
-            one = one && st == stab;
-        }
-        if (one) bits |= stab << kBlockKeys;
         IndexBlock &B = table[line << kGroupBits | b];
-        B.bits = bits;
-        B.base = base;
-        B.tag = tag;
+        B.bits = (g >> 32) << kBlockTagHi;
+        if (b) {
+            B.base = 0;
+            B.tag = tag;
+        }
+    }
+}
+
+// Second pass: the first representative of every block fills it.
+__global__ void __launch_bounds__(kBlock) k_index_fill(SearchDev S, IndexBlock *table) {
+    const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    if (i >= S.dim) return;
+    uint64_t key = S.reps[i];
+    const uint64_t blk = key >> S.low_bits, g = blk >> kGroupBits;
+    if (i > 0 && (S.reps[i - 1] >> S.low_bits) == blk) return;
+    uint64_t bits = 0, stab = S.stab[i];
+    bool one = true;
+    for (uint64_t j = i;;) {
+        bits |= 1ull << low_rank(S, key);
+        one = one && S.stab[j] == stab;
+        if (++j >= S.dim) break;
+        key = S.reps[j];
+        if ((key >> S.low_bits) != blk) break;
+    }
+    if (one) bits |= stab << kBlockKeys;
+    uint64_t line = line_of(g, S.hash_shift);
+    for (;;) {
+        IndexBlock &B = table[line << kGroupBits | (blk & ((1u << kGroupBits) - 1))];
+        if (B.tag == static_cast<uint32_t>(g) && (B.bits >> kBlockTagHi) == (g >> 32)) {
+            B.bits |= bits;
+            B.base = static_cast<uint32_t>(i);
+            return;
+        }
+        line = (line + 1) & S.hash_mask;
     }
 }
 
@@ -501,7 +519,8 @@ PlanTables plan_tables() {
     PlanTables t;
     t.binom.assign(65 * 65, 0);
     for (uint32_t i = 0; i <= 64; ++i)
-        for (uint32_t k = 0; k <= i; ++k) t.binom[i * 65 + k] = host_binom(i, k);
+        for (uint32_t k = 0; k <= i; ++k)
+            t.binom[i * 65 + k] = k == 0 || k == i ? 1 : t.binom[(i - 1) * 65 + k - 1] + t.binom[(i - 1) * 65 + k];
     return t;
 }
 
@@ -585,8 +604,11 @@ void upload_plan(ls_basis *b, hipStream_t st) {
     LS_HIP_CHECK(hipMemcpyAsync(b->d_cosets, gp.cosets.data(), ncos * sizeof(CosetRep), hipMemcpyHostToDevice, st));
     b->d_chi = dev_alloc_n<double2>(gp.n_elements, st);
     LS_HIP_CHECK(hipMemcpyAsync(b->d_chi, gp.chi.data(), gp.n_elements * sizeof(double2), hipMemcpyHostToDevice, st));
-    b->d_skip = dev_alloc_n<uint8_t>(gp.skip.size(), st);
-    LS_HIP_CHECK(hipMemcpyAsync(b->d_skip, gp.skip.data(), gp.skip.size(), hipMemcpyHostToDevice, st));
+    // (rings take m from the rotation, one element never rejects)
+    if (gp.n_elements > 1 && walk_kind(gp) != kWalkRing) {
+        b->d_skip = dev_alloc_n<uint8_t>(gp.skip.size(), st);
+        LS_HIP_CHECK(hipMemcpyAsync(b->d_skip, gp.skip.data(), gp.skip.size(), hipMemcpyHostToDevice, st));
+    }
     b->d_chi_one = dev_alloc_n<uint32_t>(gp.chi_one.size(), st);
     LS_HIP_CHECK(hipMemcpyAsync(b->d_chi_one, gp.chi_one.data(), gp.chi_one.size() * sizeof(uint32_t),
                                 hipMemcpyHostToDevice, st));
@@ -792,11 +814,27 @@ void build_basis(ls_basis *b, hipStream_t st) {
     S.weight = b->weight;
     S.dim = b->dim;
     S.reps = b->d_reps;
-    S.binom = b->d_binom;
+    std::vector<uint64_t> rank;   // host table of the rank layout, until the last synchronisation
     if (gp.n_elements == 1 && b->weight < 0) {
         S.mode = kLookupIdentity;
     } else if (gp.n_elements == 1) {
         S.mode = kLookupRank;
+        const uint32_t w = static_cast<uint32_t>(b->weight);
+        const std::vector<uint64_t> pascal = plan_tables().binom;
+        const uint32_t chunks = (n + kRankBits - 1) / kRankBits;
+        rank.assign((static_cast<size_t>(chunks) << kRankBits) * (w + 1), 0);
+        for (uint32_t c = 0; c < chunks; ++c)
+            for (uint32_t v = 0; v < (1u << kRankBits); ++v)
+                for (uint32_t k = 0; k <= w; ++k) {
+                    uint64_t r = 0;
+                    uint32_t set = k;
+                    for (uint32_t i = 0; i < kRankBits; ++i)
+                        if (((v >> i) & 1u) && kRankBits * c + i < n && set < w) r += pascal[(kRankBits * c + i) * 65 + ++set];
+                    rank[((static_cast<size_t>(c) << kRankBits) + v) * (w + 1) + k] = r;
+                }
+        b->d_rank = dev_alloc_n<uint64_t>(rank.size(), st);
+        S.rank = b->d_rank;
+        LS_HIP_CHECK(hipMemcpyAsync(b->d_rank, rank.data(), rank.size() * sizeof(uint64_t), hipMemcpyHostToDevice, st));
     } else {
         uint64_t kmin = 0, kmax = 0;
         if (b->dim > 0) {
@@ -818,8 +856,9 @@ void build_basis(ls_basis *b, hipStream_t st) {
             unsigned long long *d_groups = groups_b.as<unsigned long long>(), groups = 0;
             hipLaunchKernelGGL(k_clear_u64, dim3(1), dim3(1), 0, st, d_groups);
             if (b->dim > 0)
-                hipLaunchKernelGGL(k_count_groups, dim3(grid_for(b->dim)), dim3(kBlock), 0, st, b->d_reps, b->dim,
-                                   shift, d_groups);
+                // (a workgroup a 256 rows: 0.74 ms of atomic adds for 6x6)
+                hipLaunchKernelGGL(k_count_groups, dim3(std::min<uint64_t>(2048, grid_for(b->dim))), dim3(kBlock), 0,
+                                   st, b->d_reps, b->dim, shift, d_groups);
             LS_HIP_CHECK(hipGetLastError());
             LS_HIP_CHECK(hipMemcpyAsync(&groups, d_groups, sizeof(groups), hipMemcpyDeviceToHost, st));
             LS_HIP_CHECK(hipStreamSynchronize(st));
@@ -846,8 +885,10 @@ void build_basis(ls_basis *b, hipStream_t st) {
             S.low_rank = b->d_low_rank;
             S.stab = b->d_stab;
             S.dropped = b->d_dropped;
-            if (b->dim > 0)
+            if (b->dim > 0) {
+                hipLaunchKernelGGL(k_index_claim, dim3(grid_for(b->dim)), dim3(kBlock), 0, st, S, b->d_table);
                 hipLaunchKernelGGL(k_index_fill, dim3(grid_for(b->dim)), dim3(kBlock), 0, st, S, b->d_table);
+            }
             LS_HIP_CHECK(hipGetLastError());
             LS_HIP_CHECK(hipStreamSynchronize(st));
             return;

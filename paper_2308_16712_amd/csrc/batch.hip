@@ -37,7 +37,7 @@ struct Tile {
 // around the tile loop, so it runs in 512-thread workgroups.
 constexpr int batch_block(int kind, bool cplx) { return (kind == kOrbitTorus && cplx) ? 512 : block_of(kind); }
 
-template <typename W, int KIND, int CHI, bool CPLX, int NR, uint32_t LX, uint32_t LY, uint32_t NZ>
+template <typename W, int KIND, int CHI, bool CPLX, int NR, uint32_t LX, uint32_t LY, uint32_t NZ, bool TOGETHER>
 __global__ void __launch_bounds__(batch_block(KIND, CPLX))
     k_matvec_batch(const MatvecJob *jobs, const Tile *tiles, uint32_t n_tiles, uint32_t *counter, uint32_t rpl,
                    uint32_t tile_rows) {
@@ -57,14 +57,14 @@ __global__ void __launch_bounds__(batch_block(KIND, CPLX))
         const MatvecJob &a = jobs[jid];
         if (jid != cur) {
             L = lds_tables<KIND, LX, BLOCK, false, false>(a, smem);
-            stage_tables<KIND, LX, BLOCK, false, false>(a, L, KIND != kOrbitTorus || a.steps == nullptr);
+            stage_tables<KIND, LX, BLOCK, false, false>(a, L, !TOGETHER);
             __syncthreads();
             cur = jid;
         }
         // a tile is rows row0 + t + k * tile_rows (t < tile_rows, k < rpl);
         // tile_rows < BLOCK spreads small jobs over more workgroups
         if (threadIdx.x < tile_rows)
-            run_rows<W, KIND, CHI, CPLX, NR, LX, LY, NZ, true>(a, L, T.row0 + threadIdx.x, tile_rows, rpl);
+            run_rows<W, KIND, CHI, CPLX, NR, LX, LY, NZ, true, TOGETHER>(a, L, T.row0 + threadIdx.x, tile_rows, rpl);
     }
 }
 
@@ -154,9 +154,17 @@ struct BatchLaunch {
         } else {
             constexpr int BLOCK = batch_block(KIND, CPLX);
             hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, st, g->d_counter);
-            hipLaunchKernelGGL((k_matvec_batch<W, KIND, CHI, CPLX, NR, LX, LY, NZ>), dim3(g->grid), dim3(BLOCK),
-                               g->lds, st, g->d_jobs, g->d_tiles, g->n_tiles, g->d_counter, g->rpl,
-                               g->tile_rows ? g->tile_rows : static_cast<uint32_t>(BLOCK));
+            const uint32_t rows = g->tile_rows ? g->tile_rows : static_cast<uint32_t>(BLOCK);
+            if constexpr (KIND == kOrbitTorus) {
+                if (g->v.together) {
+                    hipLaunchKernelGGL((k_matvec_batch<W, KIND, CHI, CPLX, NR, LX, LY, NZ, true>), dim3(g->grid),
+                                       dim3(BLOCK), g->lds, st, g->d_jobs, g->d_tiles, g->n_tiles, g->d_counter, g->rpl,
+                                       rows);
+                    return;
+                }
+            }
+            hipLaunchKernelGGL((k_matvec_batch<W, KIND, CHI, CPLX, NR, LX, LY, NZ, false>), dim3(g->grid), dim3(BLOCK),
+                               g->lds, st, g->d_jobs, g->d_tiles, g->n_tiles, g->d_counter, g->rpl, rows);
         }
     }
 };

@@ -190,6 +190,7 @@ enum LookupMode : uint32_t {
     kLookupHash = 3,
     kLookupStaged = 4
 };
+constexpr uint32_t kRankBits = 5;         // bits of a chunk of the colex rank table
 constexpr uint32_t kMaxStagedBits = 13;   // staged tables: at most 2^13 + 1 entries (32 KiB)
 
 // Hash index.  The keys are taken in blocks of 2^kLow consecutive values (7
@@ -232,7 +233,7 @@ struct SearchDev {
     uint64_t kmin, kmax;
     const uint64_t *reps;       // device [dim]
     const uint32_t *buckets;    // device [2^bits + 1]
-    const uint64_t *binom;      // device [65][65]
+    const uint64_t *rank;       // device, colex rank by chunks (rank mode)
     const IndexBlock *table;    // device [(hash_mask + 1) << kGroupBits] (hash mode)
     uint64_t hash_mask;         // lines - 1
     const uint8_t *low_rank;    // device [1 << low_bits], number of a key in its block
@@ -261,6 +262,7 @@ struct ls_basis {
     uint64_t *d_dropped = nullptr;
     uint32_t n_dropped = 0;
     uint64_t *d_binom = nullptr;
+    uint64_t *d_rank = nullptr;
     ls::CosetRep *d_cosets = nullptr;
     double2 *d_chi = nullptr;
     uint32_t *d_chi_one = nullptr;
@@ -294,7 +296,7 @@ struct ls_operator {
     ls_term_dev *d_terms = nullptr;     // diagonal terms first, then off-diagonal
     std::vector<ls_term_dev> host_terms;
     std::vector<ls_step_dev> host_steps;
-    ls_step_dev *d_steps = nullptr;     // null: the rows walk their own lists
+    ls_step_dev *d_steps = nullptr;     // in d_terms' block; null: the rows walk their own lists
     // torus search: the permutation part of every base image applied to every
     // off-diagonal flip mask, [n_base][n_off]
     std::vector<uint64_t> host_cflip;

@@ -43,22 +43,21 @@ __device__ __forceinline__ uint32_t xcd_chunk(uint32_t wg, uint32_t count) {
 // every CU instead of a few full workgroups.  A row's elements are summed by
 // one lane in term order whatever the mapping, so the results do not depend
 // on it.
-template <typename W, int KIND, int CHI, bool CPLX, int NR, uint32_t LX, uint32_t LY, uint32_t NZ>
+template <typename W, int KIND, int CHI, bool CPLX, int NR, uint32_t LX, uint32_t LY, uint32_t NZ, bool TOGETHER>
 __global__ void __launch_bounds__(block_of(KIND)) __attribute__((amdgpu_waves_per_eu(waves_per_simd(KIND, CHI, CPLX, NR, LX))))
 k_matvec(MatvecJob a, uint64_t n_lanes, uint32_t rows_per_lane, uint32_t rows_per_wg) {
     constexpr int BLOCK = block_of(KIND);
     extern __shared__ __align__(16) unsigned char smem[];
     const LdsTables L = lds_tables<KIND, LX, BLOCK>(a, smem);
-    stage_tables<KIND, LX, BLOCK>(a, L, KIND != kOrbitTorus || a.steps == nullptr);
+    stage_tables<KIND, LX, BLOCK>(a, L, !TOGETHER);
     __syncthreads();
     if (threadIdx.x >= rows_per_wg) return;
     const uint64_t lane = static_cast<uint64_t>(xcd_chunk(blockIdx.x, gridDim.x)) * rows_per_wg + threadIdx.x;
-    run_rows<W, KIND, CHI, CPLX, NR, LX, LY, NZ>(a, L, lane, n_lanes, rows_per_lane);
+    run_rows<W, KIND, CHI, CPLX, NR, LX, LY, NZ, false, TOGETHER>(a, L, lane, n_lanes, rows_per_lane);
 }
 
 // Small sectors, single column: kGroupLanes lanes per row (run_rows_group),
-// 256-thread workgroups; the tables are staged per workgroup as in k_matvec.
-constexpr int kGroupBlock = 256;
+// or T with an operator's steps (run_rows_group_steps), one row a group.
 template <typename W, int KIND, int CHI, bool CPLX, uint32_t LX, uint32_t LY, uint32_t NZ>
 __global__ void __launch_bounds__(kGroupBlock) k_matvec_group(MatvecJob a, uint64_t n_groups) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -67,6 +66,17 @@ __global__ void __launch_bounds__(kGroupBlock) k_matvec_group(MatvecJob a, uint6
     __syncthreads();
     const uint64_t group = (static_cast<uint64_t>(blockIdx.x) * kGroupBlock + threadIdx.x) / kGroupLanes;
     run_rows_group<W, KIND, CHI, CPLX, LX, LY, NZ>(a, L, group, n_groups);
+}
+
+template <typename W, int KIND, int CHI, bool CPLX, uint32_t LX, uint32_t LY, uint32_t NZ, uint32_t T>
+__global__ void __launch_bounds__(kGroupBlock) k_matvec_group_steps(MatvecJob a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ __align__(16) typename Val<CPLX>::T sh[2 * kGroupBlock];
+    const LdsTables L = lds_tables<KIND, LX, kGroupBlock, uses_ratio_table(KIND, false), false>(a, smem);
+    stage_tables<KIND, LX, kGroupBlock, uses_ratio_table(KIND, false), false>(a, L, false);
+    __syncthreads();
+    run_rows_group_steps<W, KIND, CHI, CPLX, LX, LY, NZ, T>(
+        a, L, (static_cast<uint64_t>(blockIdx.x) * kGroupBlock + threadIdx.x) / T, sh);
 }
 
 // Push form (comparison variant): same launch shape as k_matvec.
@@ -99,6 +109,7 @@ struct SingleLaunch {
     MatvecJob job;
     hipStream_t st;
     bool push = false;
+    bool together = false;
     template <typename W, int KIND, int CHI, bool CPLX, int NR, uint32_t LX, uint32_t LY, uint32_t NZ>
     void run() {
         constexpr int BLOCK = block_of(KIND);
@@ -125,6 +136,21 @@ struct SingleLaunch {
         // 15,578 rows: 645 -> 200 us; 26-site ring, 101,340 rows: slower).
         if constexpr (NR == 1) {
             if (!push && job.ld == 1 && job.dim < group_rows_below(KIND)) {
+                if (job.steps) {
+                    // 32 lanes a row while their waves fit the chip at once
+                    constexpr uint64_t kWaves = kCUs * 4 * 8;
+                    const size_t dyn = KIND == kOrbitTorus ? 64 : 0;
+                    const uint64_t per16 = kGroupBlock / 16, per32 = kGroupBlock / 32;
+                    if (job.n_steps > 16 && job.dim * 32 <= kWaves * 64)
+                        hipLaunchKernelGGL((k_matvec_group_steps<W, KIND, CHI, CPLX, LX, LY, NZ, 32>),
+                                           dim3(static_cast<uint32_t>((job.dim + per32 - 1) / per32)),
+                                           dim3(kGroupBlock), dyn, st, job);
+                    else
+                        hipLaunchKernelGGL((k_matvec_group_steps<W, KIND, CHI, CPLX, LX, LY, NZ, 16>),
+                                           dim3(static_cast<uint32_t>((job.dim + per16 - 1) / per16)),
+                                           dim3(kGroupBlock), dyn, st, job);
+                    return;
+                }
                 const uint64_t groups_per_wg = kGroupBlock / kGroupLanes;
                 const uint64_t wgs = (job.dim + groups_per_wg - 1) / groups_per_wg;
                 hipLaunchKernelGGL((k_matvec_group<W, KIND, CHI, CPLX, LX, LY, NZ>),
@@ -140,9 +166,17 @@ struct SingleLaunch {
                                    job, lanes, rpl, rows_per_wg);
             else
                 throw Error{LS_EINTERNAL, "push products run one column per launch"};
-        } else
-            hipLaunchKernelGGL((k_matvec<W, KIND, CHI, CPLX, NR, LX, LY, NZ>), grid, dim3(BLOCK), lds, st, job, lanes,
-                               rpl, rows_per_wg);
+            return;
+        }
+        if constexpr (KIND == kOrbitTorus) {
+            if (together) {
+                hipLaunchKernelGGL((k_matvec<W, KIND, CHI, CPLX, NR, LX, LY, NZ, true>), grid, dim3(BLOCK), lds, st, job,
+                                   lanes, rpl, rows_per_wg);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_matvec<W, KIND, CHI, CPLX, NR, LX, LY, NZ, false>), grid, dim3(BLOCK), lds, st, job, lanes,
+                           rpl, rows_per_wg);
     }
 };
 
@@ -246,6 +280,7 @@ Variant variant_of(const ls_operator *op) {
         v.kind = kOrbitRing64;
     } else if (torus) {
         v.kind = kOrbitTorus;
+        v.together = op->d_steps != nullptr;
         if (square_torus(gp) && (gp.lx == 6 || gp.lx == 4)) {
             v.lx = gp.lx;
             v.ly = gp.ly;
@@ -269,7 +304,7 @@ void launch_matvec(const ls_operator *op, uint32_t nrhs, const void *x, void *y,
     uint32_t col = 0;
     while (col < nrhs) {
         const int nr = nr_chunk(nrhs - col);
-        SingleLaunch L{job_of(op, x, y, nrhs, col), st};
+        SingleLaunch L{job_of(op, x, y, nrhs, col), st, false, v.together};
         dispatch(v, nr, L);
         LS_HIP_CHECK(hipGetLastError());
         col += static_cast<uint32_t>(nr);

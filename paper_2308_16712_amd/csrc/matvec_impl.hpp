@@ -254,11 +254,16 @@ __device__ __forceinline__ RowStab<TAB> row_stab(const PlanDev &P, const LdsTabl
 
 // sqrt(stab_j / stab_i), correctly rounded: read from the ratio table when
 // the kernel and the group have one, else divided and rooted (the same bits).
-template <bool TAB>
+template <int KIND, bool TAB>
 __device__ __forceinline__ double stab_factor(const PlanDev &P, const LdsTables &L, const RowStab<TAB> &R,
                                               uint32_t st_j) {
     if constexpr (!TAB) {
-        return __dsqrt_rn(__ddiv_rn(static_cast<double>(st_j), R.st));
+        // most elements join orbits of one size: a wavefront that has no other
+        // skips the division and the root (6x6 product 20.65 -> 19.95 ms; the
+        // batched rings lose 2% with the branch)
+        const double sj = static_cast<double>(st_j);
+        if (KIND == kOrbitTorus && sj == R.st) return 1.0;
+        return __dsqrt_rn(__ddiv_rn(sj, R.st));
     } else {
         if (P.n_stab_cls) return L.sratio[R.base + L.scls[st_j]];
         return __dsqrt_rn(__ddiv_rn(static_cast<double>(st_j), static_cast<double>(R.st)));
@@ -418,7 +423,7 @@ __device__ __forceinline__ void run_rows_ahead(const MatvecJob &a, const LdsTabl
                 j = lookup_stab<STAGED>(a, L, p_rep, st_j);
             }
             if (j >= 0) {
-                const T c = element_value<CHI, CPLX>(sterm[p_t], r, stab_factor(a.plan, L, rs, st_j), a.plan, p_code);
+                const T c = element_value<CHI, CPLX>(sterm[p_t], r, stab_factor<KIND>(a.plan, L, rs, st_j), a.plan, p_code);
 #pragma unroll
                 for (int q = 0; q < NR; ++q) accumulate(acc[q], c, x[j * a.ld + a.col + q]);
             } else {
@@ -492,7 +497,7 @@ __device__ __forceinline__ void run_rows_steps(const MatvecJob &a, const LdsTabl
                 continue;
             }
             const T c = element_value<CHI, CPLX>(steps[s].re, steps[s].im, steps[s].sign, r,
-                                                 stab_factor(a.plan, L, rs, st_j), a.plan, info.code);
+                                                 stab_factor<KIND>(a.plan, L, rs, st_j), a.plan, info.code);
 #pragma unroll
             for (int q = 0; q < NR; ++q) accumulate(acc[q], c, x[j * a.ld + a.col + q]);
         }
@@ -503,16 +508,16 @@ __device__ __forceinline__ void run_rows_steps(const MatvecJob &a, const LdsTabl
 
 // Rows row0, row0 + step, ... (count of them, below dim) of one job.
 // STAGED: the batched launch, whose job's search layout may be a bucket table
-// staged in LDS; the other launches never meet one.
+// staged in LDS; the other launches never meet one.  TOGETHER: run_rows_steps
+// (a kernel of its own: with both loops in one, the runtime torus shapes run
+// out of scalar registers).
 template <typename W, int KIND, int CHI, bool CPLX, int NR, uint32_t LX, uint32_t LY, uint32_t NZ,
-          bool STAGED = false>
+          bool STAGED = false, bool TOGETHER = false>
 __device__ __forceinline__ void run_rows(const MatvecJob &a, const LdsTables &L, uint64_t row0, uint64_t step,
                                          uint32_t count) {
-    if constexpr (KIND == kOrbitTorus) {
-        if (a.steps) {
-            run_rows_steps<W, KIND, CHI, CPLX, NR, LX, LY, NZ, STAGED>(a, L, row0, step, count);
-            return;
-        }
+    if constexpr (TOGETHER) {
+        run_rows_steps<W, KIND, CHI, CPLX, NR, LX, LY, NZ, STAGED>(a, L, row0, step, count);
+        return;
     }
     // the pipelined loop pays off where up to four columns leave registers
     // for the element in flight (64 ring sectors x 4 columns: 271 -> 259 ms
@@ -571,14 +576,15 @@ __device__ __forceinline__ void run_rows(const MatvecJob &a, const LdsTables &L,
             lookup_miss<W, KIND, CHI>(a, rep);
             continue;
         }
-        const T c = element_value<CHI, CPLX>(Tm, r, stab_factor(a.plan, L, rs, st_j), a.plan, code);
+        const T c = element_value<CHI, CPLX>(Tm, r, stab_factor<KIND>(a.plan, L, rs, st_j), a.plan, code);
 #pragma unroll
         for (int q = 0; q < NR; ++q) accumulate(acc[q], c, x[j * a.ld + a.col + q]);
     }
 }
 
-// Lanes per row of the row-group form.
+// Lanes per row of the row-group form, and its workgroups.
 constexpr int kGroupLanes = 16;
+constexpr int kGroupBlock = 256;
 
 // One value from lane `src` of the wavefront (all lanes must be active).
 __device__ __forceinline__ double lane_value(double v, int src) { return __shfl(v, src, 64); }
@@ -648,7 +654,7 @@ __device__ __forceinline__ void run_rows_group(const MatvecJob &a, const LdsTabl
                 uint32_t st_j = 0;
                 const int64_t j = lookup_index_stab(a.search, static_cast<uint64_t>(rep), a.stab, st_j);
                 if (j >= 0) {
-                    c = element_value<CHI, CPLX>(sterm[t], r, stab_factor(a.plan, L, rs, st_j), a.plan, code);
+                    c = element_value<CHI, CPLX>(sterm[t], r, stab_factor<KIND>(a.plan, L, rs, st_j), a.plan, code);
                     xv = x[static_cast<uint64_t>(j) * a.ld + a.col];
                     present = true;
                 } else {
@@ -669,6 +675,87 @@ __device__ __forceinline__ void run_rows_group(const MatvecJob &a, const LdsTabl
         }
         if (live && q == 0) y[row * a.ld + a.col] = acc;
     }
+}
+
+// The row-group form for operators with steps: lane q of a group of T takes
+// the steps q, q + T, ..., of which a row acts on about half, without looking
+// for its terms; a state acts on a step once at most, so step order is term
+// order.  After a round the elements of all groups lie in LDS, and the first
+// lane of every group adds its row's in step order (a step that gives none
+// adds 0 * 0).  Bound by latency: one row's chain of reads.  16-site ring
+// without symmetry 25.7 -> 15.1 us, 4x6 torus 199 -> 89 us, 16-site symmetric
+// ring 34 -> 18 us against the lists (every lane looking through all terms for
+// its own, the sum by 16 lane exchanges).  sh: [256] values, then [256]
+// entries of x.
+template <typename W, int KIND, int CHI, bool CPLX, uint32_t LX, uint32_t LY, uint32_t NZ, uint32_t T>
+__device__ __forceinline__ void run_rows_group_steps(const MatvecJob &a, const LdsTables &L, uint64_t row,
+                                                     typename Val<CPLX>::T *sh) {
+    constexpr bool TRACK = CHI != kChiTrivial;
+    using V = typename Val<CPLX>::T;
+    const V *x = static_cast<const V *>(a.x);
+    V *y = static_cast<V *>(a.y);
+    const uint32_t q = threadIdx.x % T;
+    const bool live = row < a.dim;
+    const uint64_t r = live ? a.search.reps[row] : 0;
+    const auto rs = row_stab<uses_ratio_table(KIND, false)>(a.plan, L, live ? a.stab[row] : 1u);
+    V acc{};
+    if (live && q == 0) acc = x[row * a.ld + a.col];
+    W pr[kTorusCosetSlots] = {};
+    if constexpr (KIND == kOrbitTorus) row_images<W, LX>(a.plan, r, pr);
+    V *cs = sh, *xs = sh + kGroupBlock;
+    for (uint32_t s0 = 0; s0 < a.n_steps; s0 += T) {
+        const uint32_t s = s0 + q;
+        V c{}, xv{};
+        if (live && s < a.n_steps) {
+            const ls_step_dev &S = a.steps[s];
+            const uint64_t m = r & S.sel;
+            if (m == S.val || m == S.val2) {
+                uint32_t code = 0;
+                W rep;
+                if constexpr (KIND == kOrbitTorus) {
+                    OrbitInfo info;
+                    rep = torus_orbit_min<W, TRACK, false, LX, LY, NZ>(a.plan, pr, a.cflip + S.term,
+                                                                       a.n_terms - a.n_diag, L.lut, L.arg, L.col, info);
+                    code = info.code;
+                } else {
+                    rep = orbit_min<W, KIND, TRACK>(a.plan, static_cast<W>(r ^ S.flip), code);
+                }
+                uint32_t st_j = 0;
+                const int64_t j = lookup_index_stab(a.search, static_cast<uint64_t>(rep), a.stab, st_j);
+                if (j >= 0) {
+                    c = element_value<CHI, CPLX>(S.re, S.im, S.sign, r, stab_factor<KIND>(a.plan, L, rs, st_j), a.plan,
+                                                 code);
+                    xv = x[static_cast<uint64_t>(j) * a.ld + a.col];
+                } else {
+                    lookup_miss<W, KIND, CHI>(a, rep);
+                }
+            }
+        }
+        cs[threadIdx.x] = c;
+        xs[threadIdx.x] = xv;
+        if (s0 == 0) {
+            // the diagonal, while the first round's reads are on their way
+            double dre, dim_;
+            diag_sum<CPLX>(as_const(a.terms), a.n_diag, r, dre, dim_);
+            acc = diag_times<CPLX>(dre, dim_, acc);
+        }
+        // a group's lanes are of one wavefront: its LDS writes are done in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (q == 0) {
+            const uint32_t most = min(T, a.n_steps - s0);
+#pragma unroll 4
+            for (uint32_t k = 0; k < most; ++k) accumulate(acc, cs[threadIdx.x + k], xs[threadIdx.x + k]);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (a.n_steps == 0) {
+        double dre, dim_;
+        diag_sum<CPLX>(as_const(a.terms), a.n_diag, r, dre, dim_);
+        acc = diag_times<CPLX>(dre, dim_, acc);
+    }
+    if (live && q == 0) y[row * a.ld + a.col] = acc;
 }
 
 // y_j += conj(v) x_i with device-scope atomic adds (push form)
@@ -723,7 +810,7 @@ __device__ __forceinline__ void push_rows(const MatvecJob &a, const LdsTables &L
                 lookup_miss<W, KIND, CHI>(a, rep);
                 continue;
             }
-            const T v = element_value<CHI, CPLX>(Tm, r, stab_factor(a.plan, L, rs, st_j), a.plan, code);
+            const T v = element_value<CHI, CPLX>(Tm, r, stab_factor<KIND>(a.plan, L, rs, st_j), a.plan, code);
 #pragma unroll
             for (int q = 0; q < NR; ++q) scatter_add(&y[static_cast<uint64_t>(j) * a.ld + a.col + q], v, xi[q]);
         }
@@ -737,9 +824,10 @@ struct Variant {
     uint32_t lx, ly, nz;   // compile-time torus shape (0 = runtime)
     int chi;         // ChiMode used by the kernel
     bool cplx;
+    bool together;   // torus: rows of a wavefront take the steps together
     bool operator==(const Variant &o) const {
         return word64 == o.word64 && kind == o.kind && lx == o.lx && ly == o.ly && nz == o.nz && chi == o.chi &&
-               cplx == o.cplx;
+               cplx == o.cplx && together == o.together;
     }
 };
 

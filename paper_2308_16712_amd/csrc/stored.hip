@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(block_of(KIND)) k_store(StoreArgs s) {
             continue;
         }
         s.cols[slot] = static_cast<uint32_t>(j);
-        const T v = element_value<CHI, CPLX>(Tm, r, stab_factor(a.plan, L, rs, st_j), a.plan, code);
+        const T v = element_value<CHI, CPLX>(Tm, r, stab_factor<KIND>(a.plan, L, rs, st_j), a.plan, code);
         if constexpr (CPLX) {
             static_cast<T *>(s.vals)[slot] = v;
         } else {

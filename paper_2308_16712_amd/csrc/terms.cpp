@@ -162,11 +162,11 @@ void compile_terms(const ls_basis *b, uint32_t n_terms, const ls_term *terms, ls
     for (const Term &t : ts) op->n_diag += t.flip == 0 ? 1u : 0u;
     op->n_off = static_cast<uint32_t>(ts.size()) - op->n_diag;
 
-    // torus search: steps of the element loop that a wavefront takes together
-    // (run_rows_steps).  On average over states a step of an exchange acts on
-    // half of the rows, a step of a single term on a quarter or less; where
-    // fewer than 0.4 act, more lanes would idle than the shared lines are
-    // worth, and the rows walk their own lists
+    // steps of the element loop, for the forms in which the lanes take them
+    // without looking for the row's terms (run_rows_steps, row groups).  On
+    // average over states a step of an exchange acts on half of the rows, a
+    // step of a single term on a quarter or less; where fewer than 0.4 act,
+    // the idle lanes cost more than the look, and the rows walk their lists
     op->host_steps.clear();
     double acting = 0.0;
     for (uint32_t k = 0; k < op->n_off; ++k) {
@@ -182,7 +182,7 @@ void compile_terms(const ls_basis *b, uint32_t n_terms, const ls_term *terms, ls
         }
         op->host_steps.push_back(ls_step_dev{t.re, t.im, t.sel, t.val, t.val, t.flip, t.sign, k, 0});
     }
-    if (!gp.torus || acting < 0.4 * static_cast<double>(op->host_steps.size())) op->host_steps.clear();
+    if (acting < 0.4 * static_cast<double>(op->host_steps.size())) op->host_steps.clear();
 
     // p(r ^ f) = p(r) ^ pi_p(f) for a base image p = (pi_p, flip): the images
     // of each flip mask let the kernel reuse p(r) for a whole row
