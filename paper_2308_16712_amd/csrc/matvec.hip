@@ -10,15 +10,14 @@ namespace ls {
 
 namespace {
 
-// Waves per SIMD the register allocator must allow.  The real single-RHS
-// torus search with a compile-time shape fits 64 VGPRs without spilling:
-// 8 waves per SIMD, so two 1024-thread workgroups share a CU and twice the
-// waves are in flight to cover the latency of the random gathers (measured
-// 12% faster on the 6x6 product than the compiler's 71-register choice).
-// The 33..63-site ring search with trivial characters (the paper's chains)
-// fits as well for one or two columns.  Other variants would spill at 64
-// registers (with non-trivial characters the stabilizer walk of a lookup
-// miss is compiled into the element loop) and keep the launch bound.
+// Waves per SIMD the register allocator must allow.  The real single-column
+// torus search with a compile-time shape fits 64 VGPRs without spilling: 8
+// waves per SIMD, so two 1024-thread workgroups share a CU and twice the waves
+// are in flight to cover the latency of the gathers.  The 33..63-site ring
+// search with trivial characters (the paper's chains) fits as well for one or
+// two columns.  Other variants would spill at 64 registers (with non-trivial
+// characters the stabilizer walk of a lookup miss is compiled into the element
+// loop) and keep the launch bound.
 constexpr int waves_per_simd(int kind, int chi, bool cplx, int nr, uint32_t lx) {
     return ((kind == kOrbitTorus && !cplx && nr == 1 && lx != 0) ||
             (kind == kOrbitRing64 && chi == kChiTrivial && nr <= 2))

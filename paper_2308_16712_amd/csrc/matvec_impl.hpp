@@ -19,12 +19,13 @@
 // Work layout.  Each off-diagonal term acts on only part of the rows (a
 // Heisenberg exchange term on about a quarter of them), so a loop over the
 // terms that is uniform across a wavefront would run the orbit search for
-// every term with most lanes idle.  Instead every lane walks its own list:
-// one loop iteration = one element (the lane's next acting term of its
-// current row); when a lane's row is exhausted it stores y_i and moves to
-// its next row.  A lane owns several rows strided by a fixed step, so
-// per-row differences in the number of acting terms average out.  The term
-// table is staged in LDS once per workgroup (per item in a batch).
+// every term with most lanes idle.  On rings and in the generic walk every
+// lane walks its own list instead: one loop iteration = one element (the
+// lane's next acting term of its current row); when a lane's row is exhausted
+// it stores y_i and moves to its next row.  On tori the lanes take steps
+// together (run_rows_steps).  A lane owns several rows strided by a fixed
+// step, so per-row differences in the number of acting terms average out.  The
+// lists' term table is staged in LDS once per workgroup (per item in a batch).
 //
 // Tori (pruned search): permutations act linearly on bits, so for a base
 // image p, p(r ^ f) = p(r) ^ pi_p(f).  A lane computes p(r) once per row and

@@ -1,11 +1,12 @@
 // Device helpers: group action, orbit search and stateToIndex.
 //
-// Every lane owns one basis state and walks the whole group in registers:
-// for each coset representative p (identity, full bit reversal or a Benes
-// network of delta swaps), the translated images tau_t(p(s)) are produced
+// Every lane owns one basis state.  The general walk visits the whole group in
+// registers: for each coset representative p (identity, full bit reversal or a
+// Benes network of delta swaps), the translated images tau_t(p(s)) are produced
 // by shifts (x-rotation of every row, rotation of the word by one row), and
-// with spin inversion in the group each image v is paired with v ^ full.
-// The representative is the minimum image (the orbit minimum).
+// with spin inversion in the group each image v is paired with v ^ full.  The
+// representative is the minimum image (the orbit minimum).  Rings and tori find
+// it from a few images (ring_fold, torus_orbit_min).
 #pragma once
 
 #include <type_traits>
