@@ -749,7 +749,10 @@ __device__ __forceinline__ void run_rows_group_steps(const MatvecJob &a, const L
 #pragma unroll 4
             for (uint32_t k = 0; k < most; ++k) accumulate(acc, cs[threadIdx.x + k], xs[threadIdx.x + k]);
         }
+        // the next round's writes stay behind these reads
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
     if (a.n_steps == 0) {
         double dre, dim_;
