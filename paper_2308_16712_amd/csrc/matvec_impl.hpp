@@ -682,8 +682,9 @@ __device__ __forceinline__ void run_rows_group(const MatvecJob &a, const LdsTabl
 // the steps q, q + T, ..., of which a row acts on about half, without looking
 // for its terms; a state acts on a step once at most, so step order is term
 // order.  After a round the elements of all groups lie in LDS, and the first
-// lane of every group adds its row's in step order (a step that gives none
-// adds 0 * 0).  Bound by latency: one row's chain of reads.  16-site ring
+// lane of every group adds its row's in step order.  A step that gives none
+// leaves the sum alone, down to the sign of a zero: real ones add 0 * -0 = -0,
+// complex ones are passed over.  Bound by latency: one row's chain of reads.  16-site ring
 // without symmetry 25.7 -> 15.1 us, 4x6 torus 199 -> 89 us, 16-site symmetric
 // ring 34 -> 18 us against the lists (every lane looking through all terms for
 // its own, the sum by 16 lane exchanges).  sh: [256] values, then [256]
@@ -707,6 +708,8 @@ __device__ __forceinline__ void run_rows_group_steps(const MatvecJob &a, const L
     for (uint32_t s0 = 0; s0 < a.n_steps; s0 += T) {
         const uint32_t s = s0 + q;
         V c{}, xv{};
+        bool have = false;
+        if constexpr (!CPLX) xv = -0.0;
         if (live && s < a.n_steps) {
             const ls_step_dev &S = a.steps[s];
             const uint64_t m = r & S.sel;
@@ -727,6 +730,7 @@ __device__ __forceinline__ void run_rows_group_steps(const MatvecJob &a, const L
                     c = element_value<CHI, CPLX>(S.re, S.im, S.sign, r, stab_factor<KIND>(a.plan, L, rs, st_j), a.plan,
                                                  code);
                     xv = x[static_cast<uint64_t>(j) * a.ld + a.col];
+                    have = true;
                 } else {
                     lookup_miss<W, KIND, CHI>(a, rep);
                 }
@@ -744,11 +748,14 @@ __device__ __forceinline__ void run_rows_group_steps(const MatvecJob &a, const L
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const uint64_t given = __ballot(have) >> (threadIdx.x & 63u);   // of the group from its first lane
         if (q == 0) {
             const uint32_t most = min(T, a.n_steps - s0);
 #pragma unroll 4
-            for (uint32_t k = 0; k < most; ++k) accumulate(acc, cs[threadIdx.x + k], xs[threadIdx.x + k]);
+            for (uint32_t k = 0; k < most; ++k)
+                if (!CPLX || ((given >> k) & 1u)) accumulate(acc, cs[threadIdx.x + k], xs[threadIdx.x + k]);
         }
+        if (s0 + T >= a.n_steps) break;
         // the next round's writes stay behind these reads
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();

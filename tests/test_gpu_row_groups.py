@@ -42,3 +42,29 @@ def test_many_rounds(name, n, w, group, bonds):
     # a few roundings an element, under 200 elements a row
     assert np.abs(want.cpu().numpy() - ref).max() <= 1e-13 * max(1.0, np.abs(ref).max())
     op.check()
+
+
+@pytest.mark.parametrize("name,group,w", [("plain", lambda: lattice.trivial_group(12), 6),
+                                          ("real", lambda: lattice.ring_group(12, 0, 1, 1), 6),
+                                          ("complex", lambda: lattice.ring_group(12, 1, 0, 0), 5),
+                                          ("torus", lambda: lattice.torus_group(3, 4, 0, 0, "full", None, 1), 6)],
+                         ids=lambda v: v if isinstance(v, str) else "")
+def test_signs_of_zero(name, group, w):
+    """A step that does not act on a row leaves its sum alone, also a sum of
+    -0: vectors of zeros and of a few entries, bit for bit."""
+    g = group()
+    bonds = lattice.torus_bonds(3, 4, -1.0) if name == "torus" else lattice.ring_bonds(12, -1.0)
+    sec = configs.sector_from_arrays(name, 12, w, g.perm, g.flip, g.chi, terms.heisenberg_terms(bonds))
+    print(f"[gpu] {name}", flush=True)
+    b = ls.ls_basis_build(sec)
+    op = ls.ls_operator_create(b, sec.terms)
+    dtype = torch.complex128 if op.is_complex else torch.float64
+    negative = 0
+    for few in (0, 3):
+        for zero in (0.0, -0.0):
+            x = torch.full((b.dim, 2), zero, dtype=dtype, device="cuda")
+            x[:few] = 1.0
+            want = op.matvec(x)[:, 0].contiguous().view(torch.int64)
+            assert torch.equal(op.matvec(x[:, 0].contiguous()).view(torch.int64), want)
+            negative += int((want == -2 ** 63).sum())
+    assert negative > 0 or op.is_complex     # (complex sums with an element end at +0)
