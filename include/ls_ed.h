@@ -107,10 +107,12 @@ typedef struct {
  * stabilizer sizes and the search layout used by ls_index_lookup and the
  * products (stateToIndex, Section 5.3): a hash index over blocks of
  * consecutive keys (16 bytes a block: a bit for every key the block can
- * hold, and the position of the first; eight blocks to a 128-byte line,
- * linear probing over lines from the Fibonacci hash of the block group,
- * the top bits of group * 0x9E3779B97F4A7C15; load at most 1/4, in sparse
- * sectors 1/2 or 3/4), or, where it would pass 128 GiB or the environment
+ * hold, and the position of the first; eight blocks to a 128-byte line at
+ * load at most 1/4, or one block a line in sectors with few keys a block;
+ * linear probing over lines from the Fibonacci hash of the line's group of
+ * blocks, the top bits of group * 0x9E3779B97F4A7C15; never more bytes than
+ * 16-byte slots for every key at load 1/8 within 8 GiB, 1/4 within 64 GiB,
+ * 1/2 or 3/4 within 128 GiB), or, where the environment
  * variable LS_ED_SEARCH is "buckets" at build time, a bucket
  * table over the keys' high bits with binary search in reps.  A group of
  * one element needs neither (colex rank, or the state itself).

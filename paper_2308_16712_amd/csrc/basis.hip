@@ -228,28 +228,32 @@ __global__ void __launch_bounds__(kBlock) k_count_groups(const uint64_t *reps, u
     if (threadIdx.x == 0 && c != 0) atomicAdd(total, static_cast<unsigned long long>(c));
 }
 
+// Whether an entry belongs to group g.
+__device__ __forceinline__ bool holds_group(const SearchDev &S, const IndexBlock &B, uint64_t g) {
+    return B.tag == static_cast<uint32_t>(g) && (B.bits >> (S.tag_shift() + 32)) == (g >> 32);
+}
+
 // Hash index, first pass: the first representative of every group claims the
 // first free line of the group's probe sequence with a compare-and-swap
 // (groups are distinct and the table has more lines than groups, so every
-// sequence ends) and marks its eight blocks as the group's, empty.
+// sequence ends) and marks its blocks as the group's, empty.
 __global__ void __launch_bounds__(kBlock) k_index_claim(SearchDev S, IndexBlock *table) {
     const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
     if (i >= S.dim) return;
-    const uint32_t shift = S.low_bits + kGroupBits;
-    const uint64_t g = S.reps[i] >> shift;
-    if (i > 0 && (S.reps[i - 1] >> shift) == g) return;
+    const uint64_t key = S.reps[i], g = group_of(S, key);
+    if (i > 0 && group_of(S, S.reps[i - 1]) == g) return;
     const uint32_t tag = static_cast<uint32_t>(g);
-    uint64_t line = line_of(g, S.hash_shift);
+    uint64_t line = home_line(S, key);
     for (;;) {
         // tag and position of the line's first block: ~0 while it is free
-        unsigned long long *w = reinterpret_cast<unsigned long long *>(&table[line << kGroupBits].base);
+        unsigned long long *w = reinterpret_cast<unsigned long long *>(&table[line << S.group_bits()].base);
         const unsigned long long mine = static_cast<unsigned long long>(tag) << 32;
         if (atomicCAS(w, ~0ull, mine) == ~0ull) break;
         line = (line + 1) & S.hash_mask;
     }
-    for (uint32_t b = 0; b < (1u << kGroupBits); ++b) {
-        IndexBlock &B = table[line << kGroupBits | b];
-        B.bits = (g >> 32) << kBlockTagHi;
+    for (uint32_t b = 0; b < (1u << S.group_bits()); ++b) {
+        IndexBlock &B = table[line << S.group_bits() | b];
+        B.bits = (g >> 32) << (S.tag_shift() + 32);
         if (b) {
             B.base = 0;
             B.tag = tag;
@@ -261,23 +265,22 @@ __global__ void __launch_bounds__(kBlock) k_index_claim(SearchDev S, IndexBlock 
 __global__ void __launch_bounds__(kBlock) k_index_fill(SearchDev S, IndexBlock *table) {
     const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
     if (i >= S.dim) return;
-    uint64_t key = S.reps[i];
-    const uint64_t blk = key >> S.low_bits, g = blk >> kGroupBits;
-    if (i > 0 && (S.reps[i - 1] >> S.low_bits) == blk) return;
-    uint64_t bits = 0, stab = S.stab[i];
+    const uint64_t first = S.reps[i], blk = first >> S.low_bits(), g = group_of(S, first);
+    if (i > 0 && (S.reps[i - 1] >> S.low_bits()) == blk) return;
+    uint64_t key = first, bits = 0, stab = S.stab[i];
     bool one = true;
     for (uint64_t j = i;;) {
         bits |= 1ull << low_rank(S, key);
         one = one && S.stab[j] == stab;
         if (++j >= S.dim) break;
         key = S.reps[j];
-        if ((key >> S.low_bits) != blk) break;
+        if ((key >> S.low_bits()) != blk) break;
     }
-    if (one) bits |= stab << kBlockKeys;
-    uint64_t line = line_of(g, S.hash_shift);
+    if (one) bits |= (stab & S.stab_mask()) << kBlockStab;
+    uint64_t line = home_line(S, first);
     for (;;) {
-        IndexBlock &B = table[line << kGroupBits | (blk & ((1u << kGroupBits) - 1))];
-        if (B.tag == static_cast<uint32_t>(g) && (B.bits >> kBlockTagHi) == (g >> 32)) {
+        IndexBlock &B = table[block_at(S, line, first)];
+        if (holds_group(S, B, g)) {
             B.bits |= bits;
             B.base = static_cast<uint32_t>(i);
             return;
@@ -290,14 +293,12 @@ __global__ void __launch_bounds__(kBlock) k_index_fill(SearchDev S, IndexBlock *
 // makes lookups compare with them.  One thread; the walk is bounded by the
 // table size.
 __global__ void k_drop_key(SearchDev S, IndexBlock *table, uint64_t *dropped, uint64_t key) {
-    const uint64_t g = key >> (S.low_bits + kGroupBits);
-    const uint64_t blk = (key >> S.low_bits) & ((1u << kGroupBits) - 1);
-    uint64_t line = line_of(g, S.hash_shift);
+    uint64_t line = home_line(S, key);
     for (uint64_t n = 0; n <= S.hash_mask; ++n) {
-        IndexBlock &B = table[line << kGroupBits | blk];
-        if (B.tag == static_cast<uint32_t>(g) && (B.bits >> kBlockTagHi) == (g >> 32)) {
+        IndexBlock &B = table[block_at(S, line, key)];
+        if (holds_group(S, B, group_of(S, key))) {
             dropped[++dropped[0]] = key;
-            B.bits &= ~(((1ull << kBlockStabBits) - 1) << kBlockKeys);
+            B.bits &= ~(static_cast<uint64_t>(S.stab_mask()) << kBlockStab);
             B.bits |= 1ull << kBlockDropped;
             return;
         }
@@ -476,33 +477,32 @@ uint64_t host_binom(uint32_t n, uint32_t k) {
 
 }  // namespace
 
-// Lines of the hash index, a power of two: load at most 1/4, or 1/2 or 3/4
-// where that would pass the bytes a table of one 16-byte slot a key takes at
-// load 1/8 within 8 GiB, 1/4 within 64 GiB and 3/4 within 128 GiB (dense
-// sectors hold about 20 keys a line and stay far below; the admission of the
-// serving loop reserves those bytes); 0: over 128 GiB.
-uint64_t index_lines(uint64_t dim, uint64_t groups) {
+// Lines of the hash index, a power of two, and the bits of a block's number
+// in its line, within the bytes of a table of one 16-byte slot a key (load 1/8
+// within 8 GiB, 1/4 within 64 GiB, 1/2 or 3/4 within 128 GiB; the admission of
+// the serving loop reserves them): 128-byte lines at load 1/4 where they fit,
+// which they do in dense sectors with room to spare (about 20 keys a line), else
+// one block a line, as many lines as fit.  0: over 128 GiB.
+uint64_t index_lines(uint64_t dim, uint64_t groups, uint32_t *group_bits) {
     struct Tier {
         uint64_t num, den, limit;   // slots >= dim * num / den while slots * 16 <= limit
     };
     const Tier tiers[] = {{8, 1, 8ULL << 30}, {4, 1, 64ULL << 30}, {2, 1, 128ULL << 30}, {4, 3, 128ULL << 30}};
-    uint64_t room = 128ULL << 30;
+    uint64_t slots = 0;
     for (const Tier &t : tiers) {
         uint64_t cap = 1024;
         while (cap * t.den < t.num * dim) cap <<= 1;
         if (cap * 16 <= t.limit) {
-            room = cap * 16;
+            slots = cap;
             break;
         }
     }
-    constexpr uint64_t line = sizeof(IndexBlock) << kGroupBits;
-    const uint64_t load[3][2] = {{4, 1}, {2, 1}, {4, 3}};
-    for (int k = 0; k < 3; ++k) {
-        uint64_t lines = 8;
-        while (lines * load[k][1] < load[k][0] * groups) lines <<= 1;
-        if (lines * line <= (k < 2 ? room : 128ULL << 30)) return lines;
-    }
-    return 0;
+    uint64_t lines = 8;
+    while (lines < 4 * groups) lines <<= 1;
+    *group_bits = kGroupBits;
+    if (lines << kGroupBits <= slots) return lines;
+    *group_bits = 0;
+    return slots;
 }
 
 namespace {
@@ -848,39 +848,42 @@ void build_basis(ls_basis *b, hipStream_t st) {
         // for, the bucket search.
         const char *env = std::getenv("LS_ED_SEARCH");
         const bool want_buckets = env != nullptr && std::string(env) == "buckets";
-        S.low_bits = b->weight >= 0 ? 7 : 5;
-        const uint32_t shift = S.low_bits + kGroupBits;
+        const uint32_t low_bits = b->weight >= 0 ? 7 : 5;
+        uint32_t group_bits = 0;
         uint64_t lines = 0;
-        if (!want_buckets && kmax != kEmptyKey && (kmax >> shift) <= kMaxGroup) {
+        if (!want_buckets) {
             StreamBuf groups_b(sizeof(uint64_t), st);
             unsigned long long *d_groups = groups_b.as<unsigned long long>(), groups = 0;
             hipLaunchKernelGGL(k_clear_u64, dim3(1), dim3(1), 0, st, d_groups);
             if (b->dim > 0)
                 // (a workgroup a 256 rows: 0.74 ms of atomic adds for 6x6)
                 hipLaunchKernelGGL(k_count_groups, dim3(std::min<uint64_t>(2048, grid_for(b->dim))), dim3(kBlock), 0,
-                                   st, b->d_reps, b->dim, shift, d_groups);
+                                   st, b->d_reps, b->dim, low_bits + kGroupBits, d_groups);
             LS_HIP_CHECK(hipGetLastError());
             LS_HIP_CHECK(hipMemcpyAsync(&groups, d_groups, sizeof(groups), hipMemcpyDeviceToHost, st));
             LS_HIP_CHECK(hipStreamSynchronize(st));
-            lines = index_lines(b->dim, groups);
+            lines = index_lines(b->dim, groups, &group_bits);
         }
         if (lines != 0) {
             S.mode = kLookupHash;
             S.hash_mask = lines - 1;
             S.hash_shift = 64;
             for (uint64_t c = lines; c > 1; c >>= 1) --S.hash_shift;
+            // wide groups leave the entries no room for stabilizer sizes
+            const bool wide = (kmax >> (low_bits + group_bits)) > kMaxGroup;
+            S.index_format = low_bits | group_bits << 8 | ((wide ? kBlockTagWide : kBlockTag) - 32) << 16 | (wide ? 1u << 24 : 0u);
             // a key's number in its block: its low bits, or their rank among
             // those of their popcount
             uint8_t rank[128] = {}, next[8] = {};
-            for (uint32_t v = 0; v < (1u << S.low_bits); ++v)
+            for (uint32_t v = 0; v < (1u << S.low_bits()); ++v)
                 rank[v] = b->weight >= 0 ? next[__builtin_popcount(v)]++ : static_cast<uint8_t>(v);
             b->d_low_rank = dev_alloc_n<uint8_t>(sizeof(rank), st);
             LS_HIP_CHECK(hipMemcpyAsync(b->d_low_rank, rank, sizeof(rank), hipMemcpyHostToDevice, st));
             b->d_dropped = dev_alloc_n<uint64_t>(1 + kMaxDropped, st);
             hipLaunchKernelGGL(k_clear_u64, dim3(1), dim3(1), 0, st,
                                reinterpret_cast<unsigned long long *>(b->d_dropped));
-            b->d_table = dev_alloc_n<IndexBlock>(lines << kGroupBits, st);
-            LS_HIP_CHECK(hipMemsetAsync(b->d_table, 0xFF, (lines << kGroupBits) * sizeof(IndexBlock), st));
+            b->d_table = dev_alloc_n<IndexBlock>(lines << S.group_bits(), st);
+            LS_HIP_CHECK(hipMemsetAsync(b->d_table, 0xFF, (lines << S.group_bits()) * sizeof(IndexBlock), st));
             S.table = b->d_table;
             S.low_rank = b->d_low_rank;
             S.stab = b->d_stab;

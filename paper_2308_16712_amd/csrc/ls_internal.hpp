@@ -193,32 +193,38 @@ enum LookupMode : uint32_t {
 constexpr uint32_t kRankBits = 5;         // bits of a chunk of the colex rank table
 constexpr uint32_t kMaxStagedBits = 13;   // staged tables: at most 2^13 + 1 entries (32 KiB)
 
-// Hash index.  The keys are taken in blocks of 2^kLow consecutive values (7
-// low bits with a fixed Hamming weight, 5 without), eight blocks to a group.
-// A group is one 128-byte line of the table, found by linear probing over
+// Hash index.  The keys are taken in blocks of 2^low_bits consecutive values
+// (7 low bits with a fixed Hamming weight, 5 without), 2^group_bits blocks to
+// a group.  A group is one line of the table, found by linear probing over
 // lines from the group's Fibonacci hash; a block is one 16-byte entry of it:
 // which of its keys are representatives, one bit each (with a fixed weight
 // the block's keys have low bits of one popcount: at most C(7,3) = 35 of
 // them, numbered in increasing order), and the position of the first in the
 // sorted array.  The position of a key is the number of bits below its own,
-// and it is exact: no key is compared.  One 16-byte read finds it, and the
-// neighbours of neighbouring rows share lines, as they share lines of x.
-// A table of one 16-byte slot a key (load 1/8, no locality) cost the products
-// one 128-byte line of the fabric per element (5.7e10 lines/s whatever the
-// table's size): 38-spin chain 106 -> 75 ms, 32-site ring 1.87 -> 1.34 ms, 6x6
-// torus 36.5 -> 30.6 ms, and 0.4 GB of table for 6x6 instead of 2 GiB.
+// and it is exact: no key is compared.  One 16-byte read finds it, and with
+// eight blocks to a 128-byte line the neighbours of neighbouring rows share
+// lines, as they share lines of x.  A table of one 16-byte slot a key (load
+// 1/8, no locality) cost the products one 128-byte line of the fabric per
+// element (5.7e10 lines/s whatever the table's size): 38-spin chain 106 -> 75
+// ms, 32-site ring 1.87 -> 1.34 ms, 6x6 torus 36.5 -> 30.6 ms, and 0.27 GB of
+// table for 6x6 instead of 2 GiB.
+// Sectors with few keys a group (index_layout) take one block a line: their
+// wide lines would be mostly empty, and at the loads that fit, probe
+// sequences get long.
 struct alignas(16) IndexBlock {
-    uint64_t bits;      // [0, 36) members, [36, 49) stabilizer size of all of
-                        // them (0: read the array), 49: a dropped key, [50, 64)
-                        // bits 32 and up of the group
+    uint64_t bits;      // [0, 36) members, 36: a dropped key, [37, 50) stabilizer
+                        // size of all members (0: read the array), [50, 64)
+                        // bits 32 and up of the group; groups of more bits
+                        // (wide) have them in [37, 64)
     uint32_t base;      // position of the first member
     uint32_t tag;       // low 32 bits of the group; a free line is all ones
 };
-constexpr uint32_t kBlockKeys = 36, kBlockStabBits = 13, kBlockDropped = 49, kBlockTagHi = 50;
-constexpr uint32_t kGroupBits = 3;                        // blocks of a group: 2^3
-constexpr uint64_t kMaxGroup = (1ULL << 46) - 2;
+constexpr uint32_t kBlockKeys = 36, kBlockDropped = 36, kBlockStab = 37;
+constexpr uint32_t kBlockTag = 50, kBlockTagWide = 37;
+constexpr uint32_t kBlockStabMask = (1u << (kBlockTag - kBlockStab)) - 1;
+constexpr uint32_t kGroupBits = 3;                        // blocks of a wide line: 2^3
+constexpr uint64_t kMaxGroup = (1ULL << (32 + 64 - kBlockTag)) - 2;   // above: wide
 constexpr uint32_t kMaxDropped = 1023;                    // keys the test hook can drop
-constexpr uint64_t kEmptyKey = ~0ULL;
 
 struct SearchDev {
     uint32_t mode;      // LookupMode
@@ -228,17 +234,26 @@ struct SearchDev {
     uint32_t n_sites;
     uint32_t hash_shift;        // line = (group * golden) >> hash_shift (hash mode)
     uint32_t n_bkt;             // entries of the bucket table (staged mode)
-    uint32_t low_bits, pad_;    // key bits inside a block (hash mode)
+    // hash mode: bits of a key inside its block (bits 0..7), bits of a block's
+    // number in its group (8..15), where an entry's high half has the group's
+    // bits 32 and up (16..23), and whether the entries hold no stabilizer sizes
+    // (24); one word, for the registers
+    uint32_t index_format;
     uint64_t dim;
     uint64_t kmin, kmax;
     const uint64_t *reps;       // device [dim]
     const uint32_t *buckets;    // device [2^bits + 1]
     const uint64_t *rank;       // device, colex rank by chunks (rank mode)
-    const IndexBlock *table;    // device [(hash_mask + 1) << kGroupBits] (hash mode)
+    const IndexBlock *table;    // device [(hash_mask + 1) << group_bits] (hash mode)
     uint64_t hash_mask;         // lines - 1
     const uint8_t *low_rank;    // device [1 << low_bits], number of a key in its block
     const uint16_t *stab;       // device [dim]
     const uint64_t *dropped;    // device: count, then the keys the test hook dropped
+
+    __host__ __device__ uint32_t low_bits() const { return index_format & 0xFFu; }
+    __host__ __device__ uint32_t group_bits() const { return (index_format >> 8) & 0xFFu; }
+    __host__ __device__ uint32_t tag_shift() const { return (index_format >> 16) & 0xFFu; }
+    __host__ __device__ uint32_t stab_mask() const { return (index_format >> 24) ? 0u : kBlockStabMask; }
 };
 
 }  // namespace ls
@@ -321,8 +336,8 @@ namespace ls {
 
 // basis.hip
 void upload_plan(ls_basis *b, hipStream_t stream);
-// Test hook: the representative at `index` is taken out of the hash index
-// (its slot keeps a key no lookup asks for), so lookups of it miss.
+// Test hook: the representative at `index` joins the hash index's list of
+// dropped keys, which lookups of its block compare with, so they miss it.
 void drop_key(ls_basis *b, uint64_t index, hipStream_t stream);
 // C(N, w) with U(1), else 2^N
 uint64_t candidate_count(const ls_basis *b);

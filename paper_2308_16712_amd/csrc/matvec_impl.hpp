@@ -404,7 +404,7 @@ __device__ __forceinline__ void run_rows_ahead(const MatvecJob &a, const LdsTabl
             if (hash) {
                 n_live = n_rep <= S.kmax;   // above: not in the basis
                 if (n_live) {
-                    n_line = line_of(n_rep >> (S.low_bits + kGroupBits), S.hash_shift);
+                    n_line = home_line(S, n_rep);
                     n_e = load_block(S, n_line, n_rep);
                     n_q = low_rank(S, n_rep);
                 } else {

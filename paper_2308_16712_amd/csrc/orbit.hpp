@@ -629,16 +629,26 @@ __device__ __forceinline__ uint64_t colex_rank(uint64_t s, uint32_t n_sites, uin
 __host__ __device__ __forceinline__ uint64_t line_of(uint64_t group, uint32_t shift) {
     return (group * 0x9E3779B97F4A7C15ULL) >> shift;
 }
+__device__ __forceinline__ uint64_t group_of(const SearchDev &S, uint64_t key) {
+    return key >> (S.low_bits() + S.group_bits());
+}
+__device__ __forceinline__ uint64_t home_line(const SearchDev &S, uint64_t key) {
+    return line_of(group_of(S, key), S.hash_shift);
+}
+
+// Number of the key's block among all entries of the table, in line `line`.
+__device__ __forceinline__ uint64_t block_at(const SearchDev &S, uint64_t line, uint64_t key) {
+    return line << S.group_bits() | ((key >> S.low_bits()) & ((1u << S.group_bits()) - 1));
+}
 
 // One probe of the hash index: the entry of the key's block in line `line`.
 __device__ __forceinline__ uint4 load_block(const SearchDev &S, uint64_t line, uint64_t key) {
-    const uint64_t blk = (key >> S.low_bits) & ((1u << kGroupBits) - 1);
-    return *reinterpret_cast<const uint4 *>(S.table + (line << kGroupBits | blk));
+    return *reinterpret_cast<const uint4 *>(S.table + block_at(S, line, key));
 }
 
 // Number of a key among the keys its block can hold.
 __device__ __forceinline__ uint32_t low_rank(const SearchDev &S, uint64_t key) {
-    return S.low_rank[static_cast<uint32_t>(key) & ((1u << S.low_bits) - 1)];
+    return S.low_rank[static_cast<uint32_t>(key) & ((1u << S.low_bits()) - 1)];
 }
 
 // Position and stabilizer size of a key from the probe e of its home line
@@ -647,9 +657,9 @@ __device__ __forceinline__ uint32_t low_rank(const SearchDev &S, uint64_t key) {
 // sequence ends.
 __device__ __forceinline__ int64_t resolve_block(const SearchDev &S, uint64_t key, uint64_t line, uint4 e, uint32_t q,
                                                  uint32_t &stab) {
-    const uint64_t g = key >> (S.low_bits + kGroupBits);
+    const uint64_t g = group_of(S, key);
     const uint32_t g_lo = static_cast<uint32_t>(g), g_hi = static_cast<uint32_t>(g >> 32);
-    while (e.w != g_lo || (e.y >> (kBlockTagHi - 32)) != g_hi) {
+    while (e.w != g_lo || (e.y >> S.tag_shift()) != g_hi) {
         if ((e.w & e.z) == 0xFFFFFFFFu) return -1;      // a free line (no position is ~0)
         line = (line + 1) & S.hash_mask;
         e = load_block(S, line, key);
@@ -659,11 +669,9 @@ __device__ __forceinline__ int64_t resolve_block(const SearchDev &S, uint64_t ke
     const uint64_t upto = members << (63u - q);
     if (static_cast<int64_t>(upto) >= 0) return -1;
     const uint32_t idx = e.z + static_cast<uint32_t>(__builtin_popcountll(upto)) - 1u;
-    stab = (e.y >> (kBlockKeys - 32)) & ((1u << kBlockStabBits) - 1);
+    stab = (e.y >> (kBlockStab - 32)) & S.stab_mask();
     int64_t found = static_cast<int64_t>(idx);
     if (stab == 0) {
-        // or'ed, not returned from the loop: for an early return hipcc
-        // (ROCm 7.2) overwrites the position of the lanes that go on
         if ((e.y >> (kBlockDropped - 32)) & 1u)
             for (uint64_t k = 1; k <= S.dropped[0]; ++k) found |= S.dropped[k] == key ? -1ll : 0ll;
         stab = S.stab[idx];
@@ -672,7 +680,7 @@ __device__ __forceinline__ int64_t resolve_block(const SearchDev &S, uint64_t ke
 }
 
 __device__ __forceinline__ int64_t lookup_hash(const SearchDev &S, uint64_t key, uint32_t &stab) {
-    const uint64_t line = line_of(key >> (S.low_bits + kGroupBits), S.hash_shift);
+    const uint64_t line = home_line(S, key);
     const uint4 e = load_block(S, line, key);
     return resolve_block(S, key, line, e, low_rank(S, key), stab);
 }

@@ -74,9 +74,9 @@ def _search_bytes(dim: int) -> int:
     """Bytes reserved for the search layout of the basis build: one 16-byte
     slot a state, a power of two with load factor at most 1/8 within 8 GiB,
     else 1/4 within 64 GiB, else 1/2 or 3/4 within 128 GiB; above that the
-    bucket table (at most 2^22 + 1 four-byte offsets).  The hash index over
-    blocks of keys takes this room only where few states share a block (the
-    library's index_lines)."""
+    bucket table (at most 2^22 + 1 four-byte offsets).  The library's hash
+    index stays within them (index_lines): far below in dense sectors, close
+    in sectors with few keys a block."""
     for num, den, limit in ((8, 1, 8 << 30), (4, 1, 64 << 30), (2, 1, 128 << 30), (4, 3, 128 << 30)):
         cap = 1024
         while cap * den < num * dim:
@@ -86,16 +86,25 @@ def _search_bytes(dim: int) -> int:
     return ((1 << 22) + 1) * 4
 
 
+def _walk_bytes(cand: int) -> int:
+    """Scratch of the enumeration: a count per lane (128 candidates, fewer in
+    small sectors; rings have up to 512), and a count and an offset per block
+    of 256 lanes."""
+    lanes = -(-cand // min(128, max(4, cand >> 20)))
+    blocks = -(-lanes // 256)
+    return blocks * (256 * 4 + 12)
+
+
 def footprint_bytes(sector, max_iter: int) -> int:
     """Device bytes a request holds while admitted: representatives and
-    stabilizers, search layout, Krylov space, and the build's mark words."""
+    stabilizers, search layout, Krylov space, and the build's scratch."""
     from math import comb
     dim = sector_dimension(sector)
     complex_ = not (np.all(sector.group.chi[:, 1] == 0) and np.all(sector.terms["im"] == 0))
     es = 16 if complex_ else 8
     m = min(max_iter, max(dim, 1))
     cand = comb(sector.n_sites, sector.weight) if sector.weight >= 0 else 2 ** sector.n_sites
-    return dim * 10 + _search_bytes(dim) + (m + 1) * dim * es + 2048 * m * 16 + cand // 8 + (64 << 20)
+    return dim * 10 + _search_bytes(dim) + (m + 1) * dim * es + 2048 * m * 16 + _walk_bytes(cand) + (64 << 20)
 
 
 @dataclass

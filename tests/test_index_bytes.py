@@ -1,0 +1,40 @@
+"""Bytes of the hash index (no device): what the library takes for any number
+of keys and of key groups stays within what a served request is admitted with."""
+import ctypes
+
+import paper_2308_16712_amd as ls
+from paper_2308_16712_amd import serve
+
+
+def _index_lines():
+    """ls::index_lines(dim, groups, &group_bits) of the library."""
+    f = ls.load()._ZN2ls11index_linesEmmPj
+    f.argtypes, f.restype = [ctypes.c_uint64, ctypes.c_uint64, ctypes.POINTER(ctypes.c_uint32)], ctypes.c_uint64
+    return f
+
+
+def test_index_stays_within_the_reserved_bytes():
+    f = _index_lines()
+    bits = ctypes.c_uint32()
+    dims = sorted({d for k in range(33) for d in ((1 << k) - 1, 1 << k, (1 << k) + 1, 3 << k, 5 << k)
+                   if d < 2 ** 32 - 1} | {26517, 932398, 15804956, 63068876, 861725794, 3204236779})
+    for dim in dims:
+        for groups in sorted({0, 1, dim // 20, dim // 8, dim // 3, dim // 2, 3 * dim // 4, dim - 1, dim}):
+            if not 0 <= groups <= dim:
+                continue
+            lines = f(dim, groups, ctypes.byref(bits))
+            assert lines & (lines - 1) == 0
+            assert (lines << bits.value) * 16 <= serve._search_bytes(dim), (dim, groups)
+            # a free line ends every probe sequence: groups (of one block: at most a key each) leave one
+            assert lines > (groups if bits.value else dim), (dim, groups)
+    # dense sectors: wide lines at load 1/4 at most
+    assert f(15804956, 500000, ctypes.byref(bits)) == 1 << 21 and bits.value == 3
+
+
+def test_build_scratch_is_reserved():
+    """A lane takes at least 4 and at most 512 candidates; in large sectors
+    that are not rings 128."""
+    for cand in (1, 1000, 1 << 20, (1 << 27) - 1, 9075135300):
+        lanes = -(-cand // min(128, max(4, cand >> 20)))
+        assert serve._walk_bytes(cand) >= lanes * 4 + -(-lanes // 256) * 12
+    assert serve._walk_bytes(9075135300) < 9075135300 // 24
