@@ -167,7 +167,8 @@ struct PlanDev {
     // Stabilizer-ratio table (0 classes = none): stab_cls[s] is the class of
     // the divisor s of |G|, stab_ratio[a * n_stab_cls + b] the correctly
     // rounded sqrt(d_b / d_a) of classes a and b.
-    uint32_t n_stab_cls, pad_;
+    uint32_t n_stab_cls;
+    uint32_t pad_;
     const uint8_t *stab_cls;    // device [kStabMapBytes]
     const double *stab_ratio;   // device [n_stab_cls][n_stab_cls]
 };
@@ -339,6 +340,9 @@ void upload_plan(ls_basis *b, hipStream_t stream);
 // Test hook: the representative at `index` joins the hash index's list of
 // dropped keys, which lookups of its block compare with, so they miss it.
 void drop_key(ls_basis *b, uint64_t index, hipStream_t stream);
+// Whether a product's words on a ring of 33 to 63 sites have runs that do not
+// show when the word is doubled in 64 bits.
+bool ring_turns(const GroupPlan &gp, int32_t weight);
 // C(N, w) with U(1), else 2^N
 uint64_t candidate_count(const ls_basis *b);
 void build_basis(ls_basis *b, hipStream_t stream);

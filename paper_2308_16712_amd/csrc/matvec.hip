@@ -20,7 +20,7 @@ namespace {
 // loop) and keep the launch bound.
 constexpr int waves_per_simd(int kind, int chi, bool cplx, int nr, uint32_t lx) {
     return ((kind == kOrbitTorus && !cplx && nr == 1 && lx != 0) ||
-            (kind == kOrbitRing64 && chi == kChiTrivial && nr <= 2))
+            ((kind == kOrbitRing64 || kind == kOrbitRing64T) && chi == kChiTrivial && nr <= 2))
                ? 8
                : 1;
 }
@@ -239,7 +239,7 @@ void check_operator(const ls_operator *op, hipStream_t st) {
 
 void search_kind(const ls_operator *op, uint32_t *kind, uint32_t *fixed_shape) {
     const Variant v = variant_of(op);
-    *kind = static_cast<uint32_t>(v.kind);
+    *kind = static_cast<uint32_t>(v.kind == kOrbitRing64T ? kOrbitRing64 : v.kind);
     *fixed_shape = v.lx != 0 ? 1u : 0u;
 }
 
@@ -276,7 +276,7 @@ Variant variant_of(const ls_operator *op) {
     if (!v.word64 && gp.ly == 1 && gp.lx == gp.n_sites) {
         v.kind = kOrbitRing32;
     } else if (v.word64 && gp.ly == 1 && gp.lx == gp.n_sites && gp.n_sites < 64) {
-        v.kind = kOrbitRing64;
+        v.kind = ring_turns(gp, op->basis->weight) ? kOrbitRing64T : kOrbitRing64;
     } else if (torus) {
         v.kind = kOrbitTorus;
         v.together = op->d_steps != nullptr;

@@ -29,7 +29,8 @@ enum OrbitKind : int {
     kOrbitGeneric = 0,   // runtime lx, ly (ring, torus, or no translations)
     kOrbitRing32 = 1,    // N <= 32 ring: all rotations from one funnel shift each
     kOrbitTorus = 2,     // lx <= 6, ly >= 2 torus: pruned by the pair table (torus_orbit_min)
-    kOrbitRing64 = 3,    // 32 < N < 64 ring: rotations pruned by the longest zero run
+    kOrbitRing64 = 3,    // 32 < N < 64 ring whose words' longest runs show in 64 bits when doubled
+    kOrbitRing64T = 4,   // other 32 < N < 64 rings: the words are turned (ring_fold)
 };
 
 // A value that is the same in every active lane, moved to a scalar register.
@@ -135,86 +136,6 @@ __device__ __forceinline__ void for_each_image(const PlanDev &P, W s, F &&f) {
     }
 }
 
-// Rotations of the low n bits of a 64-bit word (0 <= k < n < 64).
-__device__ __forceinline__ uint64_t rotl_n(uint64_t w, uint32_t k, uint32_t n, uint64_t full) {
-    return ((w << k) | (w >> (n - k))) & full;
-}
-__device__ __forceinline__ uint64_t rotr_n(uint64_t w, uint32_t k, uint32_t n, uint64_t full) {
-    return ((w >> k) | (w << (n - k))) & full;
-}
-
-// Longest cyclic run of zeros of the n-bit ring word w (32 < n < 64): its
-// length L and the mask of the bits where such a run starts (runs go upward,
-// wrapping from bit n-1 to bit 0).  Doubling masks R_k (bit i set when zeros
-// occupy i .. i+k-1) and binary lifting of the length.  L = 0 when w has no
-// zero; L = n and start mask 1 when w is zero.
-__device__ __forceinline__ uint64_t ring64_runs(uint64_t w, uint32_t n, uint64_t full, uint32_t &L) {
-    const uint64_t z = ~w & full;
-    if (z == 0) {
-        L = 0;
-        return 0;
-    }
-    if (z == full) {
-        L = n;
-        return 1;
-    }
-    uint64_t R[6];               // runs of 1, 2, 4, 8, 16, 32 zeros (32 < n)
-    R[0] = z;
-#pragma unroll
-    for (uint32_t l = 1; l < 6; ++l) R[l] = R[l - 1] & rotr_n(R[l - 1], 1u << (l - 1), n, full);
-    uint64_t cur = z;
-    uint32_t len = 1;
-#pragma unroll
-    for (int l = 5; l >= 0; --l) {
-        const uint32_t k = 1u << l;
-        if (len + k < n) {
-            const uint64_t c = cur & rotr_n(R[l], len, n, full);
-            if (c) {
-                cur = c;
-                len += k;
-            }
-        }
-    }
-    L = len;
-    return cur;
-}
-
-// The smallest rotation of w puts one of its longest zero runs on top (a
-// smaller word has more leading zeros): compare the rotations that lift each
-// run start in `starts` (runs of length L) to bit n-1, folding into (best,
-// arg).  Rotating left by k is the translation with code code0 + k * nz.
-template <bool TRACK>
-__device__ __forceinline__ void ring64_eval(uint64_t w, uint64_t starts, uint32_t L, uint32_t n, uint64_t full,
-                                            uint32_t code0, uint32_t nz, uint64_t &best, uint32_t &arg) {
-    if (L == 0 || L >= n) {      // all ones / all zeros: every rotation is w
-        if (w < best) {
-            best = w;
-            if constexpr (TRACK) arg = code0;
-        }
-        return;
-    }
-    while (starts) {
-        const uint32_t i = static_cast<uint32_t>(__builtin_ctzll(starts));
-        starts &= starts - 1;
-        uint32_t top = i + L - 1;             // the run's highest bit
-        if (top >= n) top -= n;
-        const uint32_t k = n - 1 - top;       // rotate it to bit n-1
-        const uint64_t v = rotl_n(w, k, n, full);
-        if (v < best) {
-            best = v;
-            if constexpr (TRACK) arg = code0 + k * nz;
-        }
-    }
-}
-
-// Run starts of the reversed word: a run of L zeros starting at i in w
-// starts at n - L - i (mod n) in the bit reversal of w.
-__device__ __forceinline__ uint64_t ring64_mirror(uint64_t starts, uint32_t L, uint32_t n, uint64_t full) {
-    if (L == 0 || L >= n) return starts;
-    const uint64_t r = __builtin_bitreverse64(starts) >> (64u - n);   // i -> n-1-i
-    return rotr_n(r, L - 1, n, full);
-}
-
 // What a search found beside the smallest image: with TRACK the code of an
 // element reaching it, with COUNT how many images equal it (the stabilizer
 // size of the orbit's states) and whether two elements that reach it have
@@ -253,25 +174,35 @@ __device__ __forceinline__ void fold_image(const PlanDev &P, W v, Code &&code, W
 // the reversed word, with spin inversion also of the flipped ones.  The
 // smallest image has the longest zero run on top.  With spin inversion the
 // runs of equal spins are the zero runs of the boundaries w ^ (w >> 1), so
-// one search finds the zero and the one runs.  The word is doubled (as far as
-// 64 bits go), so windows that wrap are plain shifts: doubled windows of 2, 4
-// and 8, then binary lifting of the length.  For a run starting at bit i, the
-// rotation y of the (flipped) word that brings it to the bottom gives both
-// images: y >> length has the run on top, and so has y reversed.  Code of
-// rotating left by k: code0 + k * |Z| + flip, mirrored mcode0 + i * |Z| + flip.
-// false: a run longer than the doubled word shows, or a constant word (the
-// caller compares every rotation).  About 45 instructions and 15 to 25 a run,
-// where 32 sites took 4 for each of 128 images (32-site ring product 1.34 ms)
-// and more sites 118 for each of the zero and the one runs (38-spin chain
-// 75 ms, VALU busy all the time).
-template <typename W, bool TRACK, bool COUNT>
+// one search finds the zero and the one runs: doubled windows, then binary
+// lifting of the length.  For a run starting at bit i, the rotation y of the
+// (flipped) word that brings it to the bottom gives both images: y >> length
+// has the run on top, and so has y reversed.  Code of rotating left by k:
+// code0 + k * |Z| + flip, mirrored mcode0 + i * |Z| + flip.
+// Windows that wrap are plain shifts of the doubled word, which holds them as
+// far as 64 bits go.  Where the sector has longer runs (ring_turns), the word is
+// turned instead so that no run wraps (TURN).
+// About 45 instructions and 15 to 25 a run, where 32 sites took 4 for each of
+// 128 images (32-site ring product 1.34 ms) and more sites 118 for each of the
+// zero and the one runs (38-spin chain 75 ms, VALU busy all the time).
+// Constant words: every rotation is the word (false with COUNT: the caller
+// counts every image).
+template <typename W, bool TRACK, bool COUNT, bool TURN>
 __device__ __forceinline__ bool ring_fold(const PlanDev &P, W w, bool mirror, uint32_t code0, uint32_t mcode0, W &best,
                                           OrbitInfo &info) {
     constexpr bool SMALL = sizeof(W) == 4;
     const uint32_t n = P.n_sites, pf = P.pair_flip ? 1u : 0u, nz = 1u + pf;
     const W full = static_cast<W>(P.full);
-    const uint32_t seen = (SMALL ? 2 * n : 64u) - pf;      // bits of z that tell
-    const uint64_t ext = static_cast<uint64_t>(w) | static_cast<uint64_t>(w) << (SMALL ? n : n & 63u);
+    uint32_t turn = 0;       // bit i of the turned word is bit i + turn (mod n) of the word
+    if constexpr (TURN) {
+        // (the last bit of a constant word that is looked at stays its own)
+        const W edges = static_cast<W>((w ^ (w >> 1)) | static_cast<W>(1) << (n - 2));
+        turn = static_cast<uint32_t>(__builtin_ctzll(static_cast<uint64_t>(edges))) + 1;
+        w = ((w >> turn) | (w << (n - turn))) & full;
+    }
+    uint64_t ext = static_cast<uint64_t>(w);
+    if constexpr (!TURN) ext |= static_cast<uint64_t>(w) << (SMALL ? n : n & 63u);
+    const uint32_t seen = (SMALL ? 2 * n : TURN ? n : 64u) - pf;      // bits of z that tell
     const uint64_t z = ~(pf ? ext ^ (ext >> 1) : ext) & (~0ull >> (64 - seen));
     const uint64_t z2 = z & (z >> 1), z4 = z2 & (z2 >> 2), z8 = z4 & (z4 >> 4);
     uint64_t cur = z;
@@ -283,6 +214,11 @@ __device__ __forceinline__ bool ring_fold(const PlanDev &P, W w, bool mirror, ui
             len += l;
         }
     };
+    if constexpr (TURN) {
+        const uint64_t z16 = z8 & (z8 >> 8);
+        lift(z16 & (z16 >> 16), 32);
+        lift(z16, 16);
+    }
     lift(z8, 8);
     lift(z4, 4);
     lift(z2, 2);
@@ -290,13 +226,19 @@ __device__ __forceinline__ bool ring_fold(const PlanDev &P, W w, bool mirror, ui
     if (z == 0) {                                          // no two equal neighbours
         cur = P.full;
         len = 0;
-    } else if (len == 16) {
+    } else if (!TURN && len == 16) {
         while (len < n && (cur & (z >> len)) != 0) {
             cur &= z >> len;
             ++len;
         }
     }
-    if (len + n > seen || w == 0 || w == full) return false;
+    if (w == 0 || w == full) {
+        if constexpr (!COUNT) {
+            fold_image<TRACK, COUNT>(P, w, [&] { return code0; }, best, info);
+            if (pf) fold_image<TRACK, COUNT>(P, static_cast<W>(w ^ full), [&] { return code0 + 1; }, best, info);
+        }
+        return !COUNT;
+    }
     const uint32_t run = len + pf;
     W starts = static_cast<W>(cur) & full;
     while (starts) {
@@ -311,111 +253,47 @@ __device__ __forceinline__ bool ring_fold(const PlanDev &P, W w, bool mirror, ui
             const W wf = f ? w ^ full : w;
             y = ((wf >> i) | (wf << (n - i))) & full;
         }
+        const uint32_t at = !TURN || i + turn < n ? i + turn : i + turn - n;      // the run's start in the word
         fold_image<TRACK, COUNT>(P, static_cast<W>(y >> run), [&] {
-            const uint32_t k = 2 * n - i - run;
+            const uint32_t k = 2 * n - at - run;
             return code0 + (k >= n ? k - n : k) * nz + f;
         }, best, info);
         if (mirror) {
-            fold_image<TRACK, COUNT>(P, bit_reverse<W>(y, n), [&] { return mcode0 + i * nz + f; }, best, info);
+            fold_image<TRACK, COUNT>(P, bit_reverse<W>(y, n), [&] { return mcode0 + at * nz + f; }, best, info);
         }
     }
     return true;
 }
 
 // The orbit minimum of a ring word by ring_fold over the cosets (the plain
-// reversal folded into the identity's); false as in ring_fold.
-template <typename W, bool TRACK, bool COUNT>
+// reversal folded into the identity's); false: a constant word with COUNT.
+template <typename W, bool TRACK, bool COUNT, bool TURN>
 __device__ __forceinline__ bool ring_orbit_min(const PlanDev &P, W s, W &best, OrbitInfo &info) {
     const uint32_t nz = P.pair_flip ? 2u : 1u, per = P.n_sites * nz;
     if (P.n_cosets == 2 && P.cosets[1].kind == kCosetReverse && P.cosets[1].flip == 0)
-        return ring_fold<W, TRACK, COUNT>(P, s, true, 0, per, best, info);
+        return ring_fold<W, TRACK, COUNT, TURN>(P, s, true, 0, per, best, info);
     for (uint32_t p0 = 0; p0 < P.n_cosets; ++p0) {
         const uint32_t p = uni(p0);
         const W u = p == 0 ? s : apply_coset<W>(P.cosets[p], s, P);
-        if (!ring_fold<W, TRACK, COUNT>(P, u, false, p * per, 0, best, info)) return false;
+        if (!ring_fold<W, TRACK, COUNT, TURN>(P, u, false, p * per, 0, best, info)) return false;
     }
     return true;
 }
 
-// Orbit minimum; with TRACK also the code of the first element reaching it.
+// Orbit minimum; with TRACK also the code of an element reaching it.
 template <typename W, int KIND, bool TRACK>
 __device__ __forceinline__ W orbit_min(const PlanDev &P, W s, uint32_t &code) {
-    W best = s;
-    uint32_t arg = 0;
-    if constexpr (KIND == kOrbitGeneric) {
-        if (P.n_elements == 1) {
-            code = 0;
-            return s;
-        }
-    }
-    if constexpr (KIND == kOrbitRing32 || KIND == kOrbitRing64) {
+    if constexpr (KIND == kOrbitRing32 || KIND == kOrbitRing64 || KIND == kOrbitRing64T) {
         OrbitInfo info;
         W least = static_cast<W>(~static_cast<W>(0));
-        if (ring_orbit_min<W, TRACK, false>(P, s, least, info)) {
-            code = info.code;
-            return least;
-        }
-    }
-    if constexpr (KIND == kOrbitRing64) {
-        const uint64_t full = P.full;
-        const uint32_t n = P.n_sites;
-        const uint32_t nz = P.pair_flip ? 2u : 1u;
-        const uint64_t w = static_cast<uint64_t>(s);
-        uint64_t b64 = w;        // s itself is the identity image (code 0)
-        if (P.n_cosets == 2 && P.cosets[1].kind == kCosetReverse && P.cosets[1].flip == 0) {
-            // dihedral group (x spin flip): the reversed word's runs mirror
-            // w's, and with the flip only the longer of the zero and one runs
-            // can put the minimum's leading zeros on top
-            uint32_t Lz, Lo = 0;
-            const uint64_t sz = ring64_runs(w, n, full, Lz);
-            uint64_t so = 0;
-            if (P.pair_flip) so = ring64_runs(w ^ full, n, full, Lo);
-            const uint64_t rw = __builtin_bitreverse64(w) >> (64u - n);
-            if (Lz >= Lo) {
-                ring64_eval<TRACK>(w, sz, Lz, n, full, 0, nz, b64, arg);
-                ring64_eval<TRACK>(rw, ring64_mirror(sz, Lz, n, full), Lz, n, full, n * nz, nz, b64, arg);
-            }
-            if (P.pair_flip && Lo >= Lz) {
-                ring64_eval<TRACK>(w ^ full, so, Lo, n, full, 1, nz, b64, arg);
-                ring64_eval<TRACK>(rw ^ full, ring64_mirror(so, Lo, n, full), Lo, n, full, n * nz + 1, nz, b64,
-                                   arg);
-            }
-        } else {
-            for (uint32_t p0 = 0; p0 < P.n_cosets; ++p0) {
-                const uint32_t p = uni(p0);
-                const uint64_t u = static_cast<uint64_t>(apply_coset<W>(P.cosets[p], s, P));
-                uint32_t L;
-                uint64_t st = ring64_runs(u, n, full, L);
-                ring64_eval<TRACK>(u, st, L, n, full, p * n * nz, nz, b64, arg);
-                if (P.pair_flip) {
-                    st = ring64_runs(u ^ full, n, full, L);
-                    ring64_eval<TRACK>(u ^ full, st, L, n, full, p * n * nz + 1, nz, b64, arg);
-                }
-            }
-        }
-        best = static_cast<W>(b64);
-    } else if constexpr (!TRACK && KIND == kOrbitRing32) {
-        // plain min, two images per rotation with spin inversion
-        const W full = static_cast<W>(P.full);
-        const uint32_t n = P.n_sites;
-        for (uint32_t p0 = 0; p0 < P.n_cosets; ++p0) {
-            const CosetRep c = P.cosets[uni(p0)];
-            const W u = apply_coset<W>(c, s, P);
-            const uint64_t uu = static_cast<uint64_t>(u) | (static_cast<uint64_t>(u) << n);
-            const uint32_t lo = static_cast<uint32_t>(uu), hi = static_cast<uint32_t>(uu >> 32);
-            if (P.pair_flip) {
-                for (uint32_t t = 0; t < n; ++t) {
-                    const W v = static_cast<W>(__builtin_amdgcn_alignbit(hi, lo, t)) & full;
-                    best = min(best, min(v, static_cast<W>(v ^ full)));
-                }
-            } else {
-                for (uint32_t t = 0; t < n; ++t) {
-                    const W v = static_cast<W>(__builtin_amdgcn_alignbit(hi, lo, t)) & full;
-                    best = min(best, v);
-                }
-            }
-        }
+        (void)ring_orbit_min<W, TRACK, false, KIND == kOrbitRing64T>(P, s, least, info);
+        code = info.code;
+        return least;
     } else {
+        code = 0;
+        if (P.n_elements == 1) return s;
+        W best = s;
+        uint32_t arg = 0;
         for_each_image<W, KIND>(P, s, [&](W v, uint32_t c) {
             if constexpr (TRACK) {
                 if (v < best) { best = v; arg = c; }
@@ -424,9 +302,9 @@ __device__ __forceinline__ W orbit_min(const PlanDev &P, W s, uint32_t &code) {
             }
             return true;
         });
+        code = arg;
+        return best;
     }
-    code = arg;
-    return best;
 }
 
 // Byte offset of the 4-byte table entry of the top two rows of tau_{0,b}(u),
