@@ -313,6 +313,7 @@ struct ls_operator {
     std::vector<ls_term_dev> host_terms;
     std::vector<ls_step_dev> host_steps;
     ls_step_dev *d_steps = nullptr;     // in d_terms' block; null: the rows walk their own lists
+    bool steps_together = false;        // enough of them act for the rows of a wavefront to take them together
     // torus search: the permutation part of every base image applied to every
     // off-diagonal flip mask, [n_base][n_off]
     std::vector<uint64_t> host_cflip;

@@ -279,7 +279,7 @@ Variant variant_of(const ls_operator *op) {
         v.kind = ring_turns(gp, op->basis->weight) ? kOrbitRing64T : kOrbitRing64;
     } else if (torus) {
         v.kind = kOrbitTorus;
-        v.together = op->d_steps != nullptr;
+        v.together = op->d_steps != nullptr && op->steps_together;
         if (square_torus(gp) && (gp.lx == 6 || gp.lx == 4)) {
             v.lx = gp.lx;
             v.ly = gp.ly;

@@ -163,15 +163,31 @@ void compile_terms(const ls_basis *b, uint32_t n_terms, const ls_term *terms, ls
     op->n_off = static_cast<uint32_t>(ts.size()) - op->n_diag;
 
     // steps of the element loop, for the forms in which the lanes take them
-    // without looking for the row's terms (run_rows_steps, row groups).  On
-    // average over states a step of an exchange acts on half of the rows, a
-    // step of a single term on a quarter or less; where fewer than 0.4 act,
-    // the idle lanes cost more than the look, and the rows walk their lists
+    // without looking for the row's terms (run_rows_steps, row groups).  At
+    // half filling a step of an exchange acts on half of the states, a step of
+    // a single term on a quarter or less, at other weights on fewer.  Below 0.4
+    // the idle lanes of a wavefront cost a torus product more than the look
+    // (5x8, 8 up, 0.33: 2.72 ms in steps, 2.02 in lists; 6x6, 9 up, 0.39: 2.06
+    // and 1.92; 6x6, 18 up, 0.51: 20.0 and 25.7); row groups, which look per
+    // lane, gain from steps down to about 0.3 (4x8, 8 up, 0.39: 407 us in
+    // steps, 688 in lists; 6x6, 6 up, 0.29: 168 and 161; 6x10, 5 up, 0.16: 909
+    // and 477)
     op->host_steps.clear();
+    // the part of the sector's states with the selected sites at given values
+    auto selected = [&](const ls_term_dev &t) -> double {
+        const int sites = __builtin_popcountll(t.sel), up = __builtin_popcountll(t.val);
+        if (b->weight < 0) return std::ldexp(1.0, -sites);
+        double p = 1.0;
+        for (int i = 0; i < sites; ++i) {
+            const int left = i < up ? b->weight - i : static_cast<int>(n) - b->weight - (i - up);
+            p *= std::max(0, left) / static_cast<double>(n - static_cast<uint32_t>(i));
+        }
+        return p;
+    };
     double acting = 0.0;
     for (uint32_t k = 0; k < op->n_off; ++k) {
         const ls_term_dev &t = op->host_terms[op->n_diag + k];
-        acting += std::ldexp(1.0, -__builtin_popcountll(t.sel));
+        acting += selected(t);
         if (!op->host_steps.empty()) {
             ls_step_dev &s = op->host_steps.back();
             if (s.val == s.val2 && s.sel == t.sel && s.flip == t.flip && s.sign == t.sign && s.re == t.re &&
@@ -182,7 +198,9 @@ void compile_terms(const ls_basis *b, uint32_t n_terms, const ls_term *terms, ls
         }
         op->host_steps.push_back(ls_step_dev{t.re, t.im, t.sel, t.val, t.val, t.flip, t.sign, k, 0});
     }
-    if (acting < 0.4 * static_cast<double>(op->host_steps.size())) op->host_steps.clear();
+    const double steps = static_cast<double>(op->host_steps.size());
+    if (acting < 0.3 * steps) op->host_steps.clear();
+    op->steps_together = acting >= 0.4 * steps;
 
     // p(r ^ f) = p(r) ^ pi_p(f) for a base image p = (pi_p, flip): the images
     // of each flip mask let the kernel reuse p(r) for a whole row
