@@ -276,7 +276,7 @@ __global__ void __launch_bounds__(kBlock) k_index_fill(SearchDev S, IndexBlock *
         key = S.reps[j];
         if ((key >> S.low_bits()) != blk) break;
     }
-    if (one) bits |= (stab & S.stab_mask()) << kBlockStab;
+    if (one) bits |= (stab & ((1ull << S.stab_bits()) - 1)) << kBlockStab;
     uint64_t line = home_line(S, first);
     for (;;) {
         IndexBlock &B = table[block_at(S, line, first)];
@@ -298,7 +298,7 @@ __global__ void k_drop_key(SearchDev S, IndexBlock *table, uint64_t *dropped, ui
         IndexBlock &B = table[block_at(S, line, key)];
         if (holds_group(S, B, group_of(S, key))) {
             dropped[++dropped[0]] = key;
-            B.bits &= ~(static_cast<uint64_t>(S.stab_mask()) << kBlockStab);
+            B.bits &= ~(((1ull << S.stab_bits()) - 1) << kBlockStab);
             B.bits |= 1ull << kBlockDropped;
             return;
         }
@@ -883,7 +883,8 @@ void build_basis(ls_basis *b, hipStream_t st) {
             for (uint64_t c = lines; c > 1; c >>= 1) --S.hash_shift;
             // wide groups leave the entries no room for stabilizer sizes
             const bool wide = (kmax >> (low_bits + group_bits)) > kMaxGroup;
-            S.index_format = low_bits | group_bits << 8 | ((wide ? kBlockTagWide : kBlockTag) - 32) << 16 | (wide ? 1u << 24 : 0u);
+            S.index_format = low_bits | group_bits << 8 | ((wide ? kBlockTagWide : kBlockTag) - 32) << 16 |
+                             (wide ? 0 : kBlockStabBits) << 24;
             // a key's number in its block: its low bits, or their rank among
             // those of their popcount
             uint8_t rank[128] = {}, next[8] = {};

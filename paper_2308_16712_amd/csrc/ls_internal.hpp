@@ -222,7 +222,7 @@ struct alignas(16) IndexBlock {
 };
 constexpr uint32_t kBlockKeys = 36, kBlockDropped = 36, kBlockStab = 37;
 constexpr uint32_t kBlockTag = 50, kBlockTagWide = 37;
-constexpr uint32_t kBlockStabMask = (1u << (kBlockTag - kBlockStab)) - 1;
+constexpr uint32_t kBlockStabBits = kBlockTag - kBlockStab;
 constexpr uint32_t kGroupBits = 3;                        // blocks of a wide line: 2^3
 constexpr uint64_t kMaxGroup = (1ULL << (32 + 64 - kBlockTag)) - 2;   // above: wide
 constexpr uint32_t kMaxDropped = 1023;                    // keys the test hook can drop
@@ -237,8 +237,8 @@ struct SearchDev {
     uint32_t n_bkt;             // entries of the bucket table (staged mode)
     // hash mode: bits of a key inside its block (bits 0..7), bits of a block's
     // number in its group (8..15), where an entry's high half has the group's
-    // bits 32 and up (16..23), and whether the entries hold no stabilizer sizes
-    // (24); one word, for the registers
+    // bits 32 and up (16..23), and the bits of the entries' stabilizer sizes
+    // (24..31, or 0); one word, for the registers
     uint32_t index_format;
     uint64_t dim;
     uint64_t kmin, kmax;
@@ -254,7 +254,7 @@ struct SearchDev {
     __host__ __device__ uint32_t low_bits() const { return index_format & 0xFFu; }
     __host__ __device__ uint32_t group_bits() const { return (index_format >> 8) & 0xFFu; }
     __host__ __device__ uint32_t tag_shift() const { return (index_format >> 16) & 0xFFu; }
-    __host__ __device__ uint32_t stab_mask() const { return (index_format >> 24) ? 0u : kBlockStabMask; }
+    __host__ __device__ uint32_t stab_bits() const { return index_format >> 24; }
 };
 
 }  // namespace ls

@@ -335,7 +335,9 @@ __device__ __forceinline__ void lookup_miss(const MatvecJob &a, W rep) {
 }
 
 // stateToIndex of a neighbour with its stabilizer size, in the job's layout.
-template <bool STAGED>
+// (Tori and rings of 33 sites and more have translations: no rank, no identity,
+// nor the scalar registers they would take.)
+template <int KIND, bool STAGED = false>
 __device__ __forceinline__ int64_t lookup_stab(const MatvecJob &a, const LdsTables &L, uint64_t key, uint32_t &st) {
     if constexpr (STAGED) {
         if (a.search.mode == kLookupStaged) {
@@ -344,7 +346,7 @@ __device__ __forceinline__ int64_t lookup_stab(const MatvecJob &a, const LdsTabl
             return j;
         }
     }
-    return lookup_index_stab(a.search, key, a.stab, st);
+    return lookup_index_stab<KIND == kOrbitGeneric || KIND == kOrbitRing32>(a.search, key, a.stab, st);
 }
 
 // Rows as run_rows, for the searches that are cheap next to the memory
@@ -421,7 +423,7 @@ __device__ __forceinline__ void run_rows_ahead(const MatvecJob &a, const LdsTabl
             if (hash) {
                 j = resolve_block(S, p_rep, p_line, p_e, p_q, st_j);
             } else {
-                j = lookup_stab<STAGED>(a, L, p_rep, st_j);
+                j = lookup_stab<KIND, STAGED>(a, L, p_rep, st_j);
             }
             if (j >= 0) {
                 const T c = element_value<CHI, CPLX>(sterm[p_t], r, stab_factor<KIND>(a.plan, L, rs, st_j), a.plan, p_code);
@@ -492,7 +494,7 @@ __device__ __forceinline__ void run_rows_steps(const MatvecJob &a, const LdsTabl
             const W rep = torus_orbit_min<W, CHI != kChiTrivial, false, LX, LY, NZ>(
                 a.plan, pr, cflip + steps[s].term, a.n_terms - a.n_diag, L.lut, L.arg, L.col, info);
             uint32_t st_j = 0;
-            const int64_t j = lookup_stab<STAGED>(a, L, static_cast<uint64_t>(rep), st_j);
+            const int64_t j = lookup_stab<KIND, STAGED>(a, L, static_cast<uint64_t>(rep), st_j);
             if (j < 0) {
                 lookup_miss<W, KIND, CHI>(a, rep);
                 continue;
@@ -572,7 +574,7 @@ __device__ __forceinline__ void run_rows(const MatvecJob &a, const LdsTables &L,
         const W rep = neighbour_rep<W, KIND, TRACK, LX, LY, NZ>(a, L, r, pr, t, code);
         ++t;
         uint32_t st_j = 0;
-        const int64_t j = lookup_stab<STAGED>(a, L, static_cast<uint64_t>(rep), st_j);
+        const int64_t j = lookup_stab<KIND, STAGED>(a, L, static_cast<uint64_t>(rep), st_j);
         if (j < 0) {
             lookup_miss<W, KIND, CHI>(a, rep);
             continue;
@@ -653,7 +655,7 @@ __device__ __forceinline__ void run_rows_group(const MatvecJob &a, const LdsTabl
                 uint32_t code;
                 const W rep = neighbour_rep<W, KIND, TRACK, LX, LY, NZ>(a, L, r, pr, t, code);
                 uint32_t st_j = 0;
-                const int64_t j = lookup_index_stab(a.search, static_cast<uint64_t>(rep), a.stab, st_j);
+                const int64_t j = lookup_stab<KIND>(a, L, static_cast<uint64_t>(rep), st_j);
                 if (j >= 0) {
                     c = element_value<CHI, CPLX>(sterm[t], r, stab_factor<KIND>(a.plan, L, rs, st_j), a.plan, code);
                     xv = x[static_cast<uint64_t>(j) * a.ld + a.col];
@@ -725,7 +727,7 @@ __device__ __forceinline__ void run_rows_group_steps(const MatvecJob &a, const L
                     rep = orbit_min<W, KIND, TRACK>(a.plan, static_cast<W>(r ^ S.flip), code);
                 }
                 uint32_t st_j = 0;
-                const int64_t j = lookup_index_stab(a.search, static_cast<uint64_t>(rep), a.stab, st_j);
+                const int64_t j = lookup_stab<KIND>(a, L, static_cast<uint64_t>(rep), st_j);
                 if (j >= 0) {
                     c = element_value<CHI, CPLX>(S.re, S.im, S.sign, r, stab_factor<KIND>(a.plan, L, rs, st_j), a.plan,
                                                  code);
@@ -816,7 +818,7 @@ __device__ __forceinline__ void push_rows(const MatvecJob &a, const LdsTables &L
             uint32_t code;
             const W rep = neighbour_rep<W, KIND, TRACK, LX, LY, NZ>(a, L, r, pr, t, code);
             uint32_t st_j = 0;
-            const int64_t j = lookup_index_stab(a.search, static_cast<uint64_t>(rep), a.stab, st_j);
+            const int64_t j = lookup_stab<KIND>(a, L, static_cast<uint64_t>(rep), st_j);
             if (j < 0) {
                 lookup_miss<W, KIND, CHI>(a, rep);
                 continue;

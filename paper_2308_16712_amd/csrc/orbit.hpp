@@ -547,7 +547,7 @@ __device__ __forceinline__ int64_t resolve_block(const SearchDev &S, uint64_t ke
     const uint64_t upto = members << (63u - q);
     if (static_cast<int64_t>(upto) >= 0) return -1;
     const uint32_t idx = e.z + static_cast<uint32_t>(__builtin_popcountll(upto)) - 1u;
-    stab = (e.y >> (kBlockStab - 32)) & S.stab_mask();
+    stab = __builtin_amdgcn_ubfe(e.y, kBlockStab - 32, S.stab_bits());   // (no bits: 0)
     int64_t found = static_cast<int64_t>(idx);
     if (stab == 0) {
         if ((e.y >> (kBlockDropped - 32)) & 1u)
@@ -574,7 +574,8 @@ __device__ __forceinline__ int64_t search_bucket(const uint64_t *reps, uint32_t 
 }
 
 // stateToIndex: hash index, or bucket of the key's high bits then binary
-// search, or the colex rank (U(1) without lattice symmetry).
+// search, or (PLAIN: groups of one element) the colex rank or the state itself.
+template <bool PLAIN = true>
 __device__ __forceinline__ int64_t lookup_index(const SearchDev &S, uint64_t key) {
     if (S.mode == kLookupHash) {
         // a block's numbering holds for keys of the sector's weight only
@@ -582,11 +583,13 @@ __device__ __forceinline__ int64_t lookup_index(const SearchDev &S, uint64_t key
         uint32_t st;
         return lookup_hash(S, key, st);
     }
-    if (S.mode == kLookupIdentity)
-        return (S.n_sites == 64 || (key >> S.n_sites) == 0) ? static_cast<int64_t>(key) : -1;
-    if (S.mode == kLookupRank) {
-        if ((S.n_sites < 64 && (key >> S.n_sites) != 0) || __builtin_popcountll(key) != S.weight) return -1;
-        return static_cast<int64_t>(colex_rank(key, S.n_sites, static_cast<uint32_t>(S.weight), S.rank));
+    if constexpr (PLAIN) {
+        if (S.mode == kLookupIdentity)
+            return (S.n_sites == 64 || (key >> S.n_sites) == 0) ? static_cast<int64_t>(key) : -1;
+        if (S.mode == kLookupRank) {
+            if ((S.n_sites < 64 && (key >> S.n_sites) != 0) || __builtin_popcountll(key) != S.weight) return -1;
+            return static_cast<int64_t>(colex_rank(key, S.n_sites, static_cast<uint32_t>(S.weight), S.rank));
+        }
     }
     if (key < S.kmin || key > S.kmax) return -1;
     const uint64_t b = (key - S.kmin) >> S.shift;
@@ -604,13 +607,14 @@ __device__ __forceinline__ int64_t lookup_staged(const SearchDev &S, const uint3
 
 // Index and stabilizer size of a key of the sector's weight (terms conserve
 // it; the hash index holds both in one entry).
+template <bool PLAIN = true>
 __device__ __forceinline__ int64_t lookup_index_stab(const SearchDev &S, uint64_t key, const uint16_t *stab_arr,
                                                      uint32_t &stab) {
     if (S.mode == kLookupHash) {
         if (key > S.kmax) return -1;
         return lookup_hash(S, key, stab);
     }
-    const int64_t j = lookup_index(S, key);
+    const int64_t j = lookup_index<PLAIN>(S, key);
     if (j >= 0) stab = stab_arr[j];
     return j;
 }

@@ -118,7 +118,7 @@ __global__ void __launch_bounds__(block_of(KIND)) k_store(StoreArgs s) {
         uint32_t code;
         const W rep = neighbour_rep<W, KIND, TRACK, LX, LY, NZ>(a, L, r, pr, t, code);
         uint32_t st_j = 0;
-        const int64_t j = lookup_index_stab(a.search, static_cast<uint64_t>(rep), a.stab, st_j);
+        const int64_t j = lookup_stab<KIND>(a, L, static_cast<uint64_t>(rep), st_j);
         const uint64_t slot = base + static_cast<uint64_t>(k) * kSlice;
         ++k;
         if (j < 0) {           // the slot keeps kNoCol
