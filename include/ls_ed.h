@@ -142,11 +142,12 @@ ls_status ls_sector_count(const ls_sector_desc *desc, uint64_t rank_begin, uint6
  * allocate device memory (tight loops that must not call hipMalloc,
  * harnesses that forbid it).  Same arguments, results and errors as
  * ls_sector_count.  The compiled group's device tables and the 8-byte
- * accumulator live in a static device array of 256 KiB that each GPU the
- * library runs on holds until the process ends (groups whose tables need
- * more -- binomial table, coset representatives at 96 bytes each,
- * characters at 16 bytes per element, the torus pair table -- are refused
- * with LS_EINVAL; groups with lattice translations need a few KB).  No
+ * accumulator live in a static device array of 545 KiB that each GPU the
+ * library runs on holds until the process ends: 256 KiB for the binomial
+ * table, the coset representatives at 96 bytes each and the characters at
+ * 16 bytes per element (groups that need more are refused with LS_EINVAL;
+ * groups with lattice translations need a few KB), and after them the
+ * tables of the enumeration, which every group fits.  No
  * hipMalloc, hipFree or other device allocation is made.  Every call on a
  * GPU shares that GPU's array and overwrites what the last call left:
  * calls from one process are serialised by a lock inside the library;

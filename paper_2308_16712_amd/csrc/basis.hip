@@ -522,7 +522,7 @@ namespace {
 // Host images of the device tables of a compiled group, shared by
 // upload_plan (device allocations) and the allocation-free count (static
 // scratch): binomial table [65][65], coset representatives, characters by
-// code, chi == 1 bitset, pair table (tori).
+// code, chi == 1 bitset.
 struct PlanTables {
     std::vector<uint64_t> binom;
 };
@@ -630,7 +630,7 @@ void upload_plan(ls_basis *b, hipStream_t st) {
     pd.chi = b->d_chi;
     pd.chi_one = b->d_chi_one;
     pd.skip = b->d_skip;
-    if (gp.torus) {
+    if (gp.row_tables) {
         const std::vector<unsigned char> t = torus_tables(gp);
         b->d_torus = dev_alloc_n<unsigned char>(t.size(), st);
         LS_HIP_CHECK(hipMemcpyAsync(b->d_torus, t.data(), t.size(), hipMemcpyHostToDevice, st));
@@ -723,8 +723,8 @@ uint64_t count_members(ls_basis *b, uint64_t begin, uint64_t end, hipStream_t st
 //
 // The same count for callers that cannot allocate device memory: the
 // compiled group's tables and the accumulator live in `scratch`, a
-// file-scope device array of kCountScratchBytes that each GPU holds for the
-// life of the process.  Host code never passes the array's name to a
+// file-scope device array (kCountScratchBytes, and the walk's tables after
+// them) that each GPU holds for the life of the process.  Host code never passes the array's name to a
 // kernel or a copy (on the host it is only a stand-in symbol): the device
 // address of each GPU's copy is taken once with hipGetSymbolAddress, with
 // that GPU current, and used everywhere.  Calls are serialised by a
@@ -764,18 +764,20 @@ uint64_t count_members_noalloc(const GroupPlan &gp, int32_t weight, uint64_t beg
     const uint64_t total = candidates_of(gp, weight);
     if (n_candidates) *n_candidates = total;
     end = std::min(end, total);
-    // layout: accumulator | binomials | cosets | characters | chi == 1 bits | pair table
+    // layout: accumulator | binomials | cosets | characters | chi == 1 bits
     const PlanTables t = plan_tables();
     const size_t o_binom = 256;
     const size_t o_cos = align_up(o_binom + t.binom.size() * sizeof(uint64_t), 256);
     const size_t o_chi = align_up(o_cos + gp.cosets.size() * sizeof(CosetRep), 256);
     const size_t o_one = align_up(o_chi + gp.chi.size() / 2 * sizeof(double2), 256);
-    const size_t o_lut = align_up(o_one + gp.chi_one.size() * sizeof(uint32_t), 256);
-    const size_t need = o_lut + (gp.torus ? gp.pair_lut.size() * sizeof(uint32_t) : 0);
+    const size_t need = align_up(o_one + gp.chi_one.size() * sizeof(uint32_t), 256);
     if (need > kCountScratchBytes)
         throw Error{LS_EINVAL, "the compiled group needs " + std::to_string(need) + " bytes of device tables, above the " +
                                    std::to_string(kCountScratchBytes) +
                                    "-byte scratch of the allocation-free count (use ls_sector_count)"};
+    const std::vector<unsigned char> rows = gp.row_tables ? torus_tables(gp) : std::vector<unsigned char>();
+    if (gp.skip.size() > kSkipBytes || rows.size() > kTorusBytes)
+        throw Error{LS_EINTERNAL, "the walk's tables pass their scratch"};
     if (begin >= end) return 0;
     std::lock_guard<std::mutex> lk(g_scratch_mu);
     int dev = 0;
@@ -795,12 +797,9 @@ uint64_t count_members_noalloc(const GroupPlan &gp, int32_t weight, uint64_t beg
     pd.chi = reinterpret_cast<const double2 *>(base + o_chi);
     pd.chi_one = reinterpret_cast<const uint32_t *>(base + o_one);
     pd.skip = base + kCountScratchBytes;
-    if (gp.torus) {
-        const std::vector<unsigned char> t = torus_tables(gp);
-        unsigned char *at = base + kCountScratchBytes + kSkipBytes;
-        put(kCountScratchBytes + kSkipBytes, t.data(), t.size());
-        LS_HIP_CHECK(hipStreamSynchronize(st));
-        set_torus_tables(gp, at, pd);
+    if (!rows.empty()) {
+        put(kCountScratchBytes + kSkipBytes, rows.data(), rows.size());
+        set_torus_tables(gp, base + kCountScratchBytes + kSkipBytes, pd);
     }
     unsigned long long *acc = reinterpret_cast<unsigned long long *>(base);
     const uint64_t *binom = reinterpret_cast<const uint64_t *>(base + o_binom);

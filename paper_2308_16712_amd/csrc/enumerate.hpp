@@ -226,7 +226,7 @@ __device__ __forceinline__ void walk_ring(const PlanDev &P, W s, const CandRange
     }
 }
 
-// Tori with a pair table (lx <= 6, ly >= 2): the top two rows of the smallest
+// Tori with a pair table (lx = 3..6, ly >= 2): the top two rows of the smallest
 // image are the smallest pair of rows over every base image, y-shift, flip
 // and row operation, and the pair table gives the smallest value of a pair.
 // An iteration takes one base image of the lane's candidate: ly table reads
@@ -318,7 +318,7 @@ inline bool ring_walk(const GroupPlan &p) {
 // The walk of a group's enumeration.
 enum WalkKind : int { kWalkImages = 0, kWalkRing = 1, kWalkTorus = 2 };
 inline int walk_kind(const GroupPlan &p) {
-    return ring_walk(p) ? kWalkRing : p.torus ? kWalkTorus : kWalkImages;
+    return ring_walk(p) ? kWalkRing : p.row_tables ? kWalkTorus : kWalkImages;
 }
 
 }  // namespace ls

@@ -114,7 +114,8 @@ struct GroupPlan {
     // Enumeration: for image p * |T| + t and bit d, the lowest of d and the
     // positions the image moves to bit d or above, [n_elements / |Z|][N].
     std::vector<uint8_t> skip;
-    // Pruned torus search (lx <= 6, ly >= 2).  The row operations among the
+    // Tables of row pairs (lx = 3..6, ly >= 2) for the enumeration (row_tables)
+    // and, where it pays, the pruned torus search (torus).  The row operations among the
     // cosets (m = 0 identity, 1 x -> lx-1-x, 2 y -> ly-1-y, 3 both; row_ops)
     // act on a pair of neighbouring rows as on the whole word, so one table
     // read covers them all: for every pair q = (top << lx | second) the
@@ -122,7 +123,7 @@ struct GroupPlan {
     // (key), as key(q) | key(q with all bits flipped) << 16; pair_arg has bit
     // m * 8 + a for every operation m and x-shift a that give the key.
     // The other cosets are row operations after one of the base cosets.
-    bool torus = false;
+    bool row_tables = false, torus = false;
     std::vector<uint32_t> pair_lut, pair_arg;
     uint32_t op_flips = 0;          // row operations that come with a spin flip
     std::vector<uint32_t> base_coset;   // base images: indices into cosets

@@ -382,10 +382,12 @@ __device__ __forceinline__ W torus_orbit_min(const PlanDev &P, const W *pr, Flip
         if (f) v ^= full;
         uint32_t am = arg[static_cast<uint32_t>(v >> tb)];
         const T t = static_cast<T>(v) & tmask;
-        T tr = 0;        // the rows' bits reversed
+        T tr = 0;        // the rows' bits reversed (bases that are all the cosets: no operation reverses)
+        if (LX || nb != P.n_cosets) {
 #pragma unroll
-        for (uint32_t x = 0; x < 6; ++x)
-            if (x < L) tr |= ((t >> x) & col0) << (L - 1 - x);
+            for (uint32_t x = 0; x < 6; ++x)
+                if (x < L) tr |= ((t >> x) & col0) << (L - 1 - x);
+        }
         while (am) {
             const uint32_t j = static_cast<uint32_t>(__builtin_ctz(am));
             am &= am - 1;
