@@ -423,8 +423,7 @@ GroupPlan compile_group(const ls_sector_desc &d) {
         // 0.77.  (2x14, full point group and inversion: 2.00 and 0.80 ms, and
         // the enumeration by images is as fast: no tables two sites wide.)
         P.row_tables = true;
-        P.torus = P.base_coset.size() * P.ly <= 64 &&   // a bit for every base image and y-shift
-                  (P.lx == 6 || P.cosets.size() * nt >= 64);
+        P.torus = P.lx == 6 || P.cosets.size() * nt >= 64;
         auto rot = [&](uint32_t v, uint32_t a) { return a == 0 ? v : (((v << a) | (v >> (L - a))) & rm); };
         auto rev = [&](uint32_t v) {
             uint32_t r = 0;

@@ -270,9 +270,15 @@ Variant variant_of(const ls_operator *op) {
     v.word64 = gp.n_sites > 32 ? 1 : 0;
     v.cplx = op->is_complex;
     v.chi = op->is_complex ? kChiComplex : gp.chi_mode;
+    // Terms, flip images and both tables within 64 KB; or, with up to eight
+    // base images, as many terms as with 64 bytes of flip images each and one
+    // table (groups of a launch then take up to 80 KB, two to a CU as else).
+    // More terms run the generic search (6x10, 5 up, 360 terms: batched 1.28
+    // ms there, 1.97 by the tables).
+    const uint32_t n_terms = op->n_diag + op->n_off, bases = static_cast<uint32_t>(gp.base_coset.size());
     const bool torus = gp.torus && op->d_cflip != nullptr &&
-                       lds_bytes(kOrbitTorus, op->n_diag + op->n_off, op->n_off,
-                                 static_cast<uint32_t>(gp.base_coset.size())) + kTorusTableBytes <= kMaxLds;
+                       (lds_bytes(kOrbitTorus, n_terms, op->n_off, bases) + 2 * kPairTableBytes <= kMaxLds ||
+                        lds_bytes(kOrbitTorus, n_terms, op->n_off, kTorusCosetSlots) + kPairTableBytes <= kMaxLds);
     if (!v.word64 && gp.ly == 1 && gp.lx == gp.n_sites) {
         v.kind = kOrbitRing32;
     } else if (v.word64 && gp.ly == 1 && gp.lx == gp.n_sites && gp.n_sites < 64) {

@@ -144,7 +144,6 @@ __host__ __device__ inline size_t lds_bytes(int kind, uint32_t n_terms, uint32_t
 // read that one from memory, once or twice an element: small workgroups would
 // hold fewer waves for it, and a batch needs the room for staged buckets.
 constexpr size_t kPairTableBytes = kPairTableEntries * sizeof(uint32_t);
-constexpr size_t kTorusTableBytes = 2 * kPairTableBytes;
 
 // Kernels that read the element normalisation from the stabilizer-ratio
 // table (5.6 KB of static LDS): the single launches of the ring and generic

@@ -28,7 +28,7 @@ __device__ __forceinline__ ConstPtr<T> as_const(const T *p) {
 enum OrbitKind : int {
     kOrbitGeneric = 0,   // runtime lx, ly (ring, torus, or no translations)
     kOrbitRing32 = 1,    // N <= 32 ring: all rotations from one funnel shift each
-    kOrbitTorus = 2,     // lx <= 6, ly >= 2 torus: pruned by the pair table (torus_orbit_min)
+    kOrbitTorus = 2,     // lx = 3..6, ly >= 2 torus: pruned by the pair table (torus_orbit_min)
     kOrbitRing64 = 3,    // 32 < N < 64 ring whose words' longest runs show in 64 bits when doubled
     kOrbitRing64T = 4,   // other 32 < N < 64 rings: the words are turned (ring_fold)
 };
@@ -320,7 +320,7 @@ __device__ __forceinline__ uint32_t pair_offset(W u, uint32_t b, uint32_t L, uin
     return ((static_cast<uint32_t>(u) & rm) << (L + 2)) | (x4(L * (ly - 1)) & (rm << 2));
 }
 
-// Pruned orbit minimum on an lx-by-ly torus (lx <= 6, ly >= 2).
+// Pruned orbit minimum on an lx-by-ly torus (lx = 3..6, ly >= 2).
 //
 // The group is row operations (x-shifts, the reversal of the rows' bits, the
 // reversal of the rows' order) after y-shifts of a few base images (the
@@ -450,27 +450,39 @@ __device__ __forceinline__ W torus_orbit_min(const PlanDev &P, const W *pr, Flip
                 mn = __builtin_elementwise_min(mn, __builtin_bit_cast(u16x2, entry(u, uni(b))));
         }
         best = nz == 2 ? min(static_cast<uint32_t>(mn.x), static_cast<uint32_t>(mn.y)) : static_cast<uint32_t>(mn.x);
-        uint64_t hp = 0, hf = 0;     // bit i * Ly + b: plain, flipped
+        // bit i * Ly + b: plain, flipped; without flips the second word has the
+        // odd base images (bases * Ly * |Z| is at most 128)
+        uint64_t hp = 0, hf = 0;
 #pragma unroll
         for (uint32_t i = 0; i < kTorusMaxBases; ++i) {
             if (i >= nb) continue;
             const W u = pr[i] ^ static_cast<W>(cf[i * cstride]);
-            for (uint32_t b = 0; b < Ly; ++b) {
-                const uint32_t e = entry(u, uni(b));
-                hp |= ((e & 0xFFFFu) == best ? 1ull : 0ull) << (i * Ly + b);
-                hf |= (nz == 2 && (e >> 16) == best ? 1ull : 0ull) << (i * Ly + b);
+            uint64_t m0 = 0, m1 = 0;
+            for (uint32_t b0 = 0; b0 < Ly; ++b0) {
+                const uint32_t b = uni(b0), e = entry(u, b);
+                m0 |= ((e & 0xFFFFu) == best ? 1ull : 0ull) << b;
+                m1 |= (nz == 2 && (e >> 16) == best ? 1ull : 0ull) << b;
+            }
+            if (nz == 2) {
+                hp |= m0 << (i * Ly);
+                hf |= m1 << (i * Ly);
+            } else if (i & 1u) {
+                hf |= m0 << ((i >> 1) * Ly);
+            } else {
+                hp |= m0 << ((i >> 1) * Ly);
             }
         }
         while (hp | hf) {
-            const uint32_t f = hp ? 0u : 1u;
+            const uint32_t second = hp ? 0u : 1u;
             uint64_t &h = hp ? hp : hf;
-            const uint32_t k = static_cast<uint32_t>(__builtin_ctzll(h));
+            uint32_t i = 0, b = static_cast<uint32_t>(__builtin_ctzll(h));
             h &= h - 1;
-            uint32_t i = 0, b = k;
             while (b >= Ly) {
                 b -= Ly;
                 ++i;
             }
+            if (nz == 1) i = 2 * i + second;
+            const uint32_t f = nz == 2 ? second : 0u;
             W u = pr[0];
 #pragma unroll
             for (uint32_t q = 1; q < kTorusMaxBases; ++q) u = (q < nb && i == q) ? pr[q] : u;
