@@ -312,10 +312,10 @@ struct NoFlips {
 };
 
 // Representative, character and norm of each state, from the products'
-// searches.  As many elements take s to its representative as fix s, so the
-// number of images that equal the minimum is the stabilizer size, and the
-// projector annihilates the orbit when two of them have different characters
-// (`mixed`).  Walking all images took 864 us for 4.2e6 states of a 6x6 sector
+// searches or a walk of all images (launch_state_info).  As many elements take s
+// to its representative as fix s, so a search's number of images that equal the
+// minimum is the stabilizer size, and the projector annihilates the orbit when
+// two of them have different characters (`mixed`).  Walking all images took 864 us for 4.2e6 states of a 6x6 sector
 // (576 elements).  Tori: the tables lie in LDS and the workgroups stay for many
 // states.
 template <int KIND>
@@ -361,11 +361,19 @@ __global__ void __launch_bounds__(state_block<KIND>())
                 found = ring_orbit_min<W, true, true, KIND == kOrbitRing64T>(P, s, best, info);
             }
             if (!found) {
-                best = static_cast<W>(~static_cast<W>(0));
-                info = OrbitInfo{};
+                // every image, the stabilizer from those that are s itself
                 constexpr int WALK = KIND == kOrbitRing32 ? kOrbitRing32 : kOrbitGeneric;
+                info = OrbitInfo{};
+                best = s;
                 for_each_image<W, WALK>(P, s, [&](W v, uint32_t code) {
-                    fold_image<true, true>(P, v, [&] { return code; }, best, info);
+                    if (v < best) {
+                        best = v;
+                        info.code = code;
+                    }
+                    if (v == s) {
+                        ++info.count;
+                        info.mixed = info.mixed || !chi_is_one(P, code);
+                    }
                     return true;
                 });
             }
@@ -552,6 +560,7 @@ void fill_plan_dev(const GroupPlan &gp, PlanDev &pd) {
     pd.bases = nullptr;
     pd.n_base = static_cast<uint32_t>(gp.base_coset.size());
     pd.op_flips = gp.op_flips;
+    pd.chi_trivial = gp.chi_mode == kChiTrivial ? 1 : 0;
     pd.skip = nullptr;
     for (int a = 0; a < 8; ++a) pd.col_ge[a] = gp.col_ge[a];
     pd.n_stab_cls = 0;
@@ -960,15 +969,24 @@ void launch_state_info(const ls_basis *b, uint64_t n, const uint64_t *states, ui
     if (n == 0) return;
     const GroupPlan &gp = b->plan;
     const bool ring = gp.ly == 1 && gp.lx == gp.n_sites && gp.n_sites < 64;
+    // The torus search looks at every image that ties with the smallest in two
+    // rows, which with few spins a row are many; a walk of all images is as fast
+    // for few of them and in small sectors, whose states have many symmetries
+    // (1e6 states, search and walk: 6x6, 18 up, 288 images: 50 and 268 us; 6x5,
+    // 11 up, 120 images: 70 and 81; 4x7, 14 up, 112: 111 and 102; 6x8, 7 up: 156
+    // and 129; 6x10, 5 up: 238 and 159; 4x4: 234 and 179).
+    const uint32_t images = gp.n_elements / (gp.pair_flip ? 2 : 1), w = static_cast<uint32_t>(b->weight);
+    const bool search = gp.torus && gp.n_sites > 16 && images >= 120 &&
+                        (b->weight < 0 || 5 * std::min(w, gp.n_sites - w) >= 6 * gp.ly);
     if (gp.n_sites <= 32) {
         if (ring) run_state_info<uint32_t, kOrbitRing32>(b, n, states, reps, chi, norm, st);
-        else if (gp.torus) run_state_info<uint32_t, kOrbitTorus>(b, n, states, reps, chi, norm, st);
+        else if (search) run_state_info<uint32_t, kOrbitTorus>(b, n, states, reps, chi, norm, st);
         else run_state_info<uint32_t, kOrbitGeneric>(b, n, states, reps, chi, norm, st);
     } else if (ring) {
         run_state_info<uint64_t, kOrbitRing64T>(b, n, states, reps, chi, norm, st);
-    } else if (gp.torus && square_torus(gp) && gp.lx == 6) {
+    } else if (search && square_torus(gp) && gp.lx == 6) {
         run_state_info<uint64_t, kOrbitTorus, 6, 6, 2>(b, n, states, reps, chi, norm, st);
-    } else if (gp.torus) {
+    } else if (search) {
         run_state_info<uint64_t, kOrbitTorus>(b, n, states, reps, chi, norm, st);
     } else {
         run_state_info<uint64_t, kOrbitGeneric>(b, n, states, reps, chi, norm, st);

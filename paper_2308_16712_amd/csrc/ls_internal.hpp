@@ -169,7 +169,7 @@ struct PlanDev {
     // the divisor s of |G|, stab_ratio[a * n_stab_cls + b] the correctly
     // rounded sqrt(d_b / d_a) of classes a and b.
     uint32_t n_stab_cls;
-    uint32_t pad_;
+    uint32_t chi_trivial;       // every character is 1
     const uint8_t *stab_cls;    // device [kStabMapBytes]
     const double *stab_ratio;   // device [n_stab_cls][n_stab_cls]
 };

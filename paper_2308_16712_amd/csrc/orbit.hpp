@@ -147,21 +147,25 @@ struct OrbitInfo {
 
 // Notes the image v of the element with code `code` (given as a function): the
 // smallest so far, and with COUNT how many are equal to it, the smallest of
-// their codes, and whether their characters differ.
+// their codes, and whether their characters differ (of trivial characters
+// only how many).
 template <bool TRACK, bool COUNT, typename W, typename Code>
 __device__ __forceinline__ void fold_image(const PlanDev &P, W v, Code &&code, W &best, OrbitInfo &info) {
+    const bool chars = TRACK && !(COUNT && P.chi_trivial);
     if constexpr (COUNT) {
         if (v == best && info.count) {
-            const uint32_t c = code();
-            const double2 c0 = P.chi[info.code], c1 = P.chi[c];
             ++info.count;
-            info.mixed = info.mixed || fabs(c0.x - c1.x) + fabs(c0.y - c1.y) > 1e-6;
-            info.code = min(info.code, c);
+            if (chars) {
+                const uint32_t c = code();
+                const double2 c0 = P.chi[info.code], c1 = P.chi[c];
+                info.mixed = info.mixed || fabs(c0.x - c1.x) + fabs(c0.y - c1.y) > 1e-6;
+                info.code = min(info.code, c);
+            }
         }
     }
     if (v < best || (COUNT && info.count == 0)) {
         best = v;
-        if constexpr (TRACK) info.code = code();
+        if (chars) info.code = code();
         if constexpr (COUNT) {
             info.count = 1;
             info.mixed = false;
