@@ -12,8 +12,9 @@
 //   scan    an exclusive scan of the chunk counts gives chunk offsets;
 //   pass 2  a workgroup scan of the lanes' counts gives each lane's offset;
 //           the lane walks its run again and writes its members and their
-//           stabilizer sizes.  No atomics; the output is sorted by
-//           construction.
+//           stabilizer sizes, or steps through the candidates that pass 1
+//           marked (marked_build), and the stabilizers follow in a pass of
+//           their own.  No atomics; the output is sorted by construction.
 // The "condition" kept by the filter: s is the minimum of its orbit, and P
 // does not annihilate it (every stabilizer element has character 1).
 
@@ -30,6 +31,7 @@ namespace ls {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr uint64_t kMarkCandidates = 1ull << 33;       // most candidates of one (1 GiB of marks)
 
 __device__ uint64_t unrank_colex(uint64_t rank, uint32_t n, int32_t w, const uint64_t *tab) {
     uint64_t s = 0;
@@ -82,6 +84,7 @@ struct EnumArgs {
     uint32_t n_sites;
     int32_t weight;
     uint32_t *lane_counts;    // [lanes]
+    uint64_t *marks;          // [lanes], marked builds: the members among up to 64 candidates
     uint32_t *counts;         // [blocks]
     const uint64_t *offsets;  // [blocks], pass 2
     uint64_t *reps;           // pass 2
@@ -138,6 +141,61 @@ __global__ void __launch_bounds__(kBlock) k_enum_mark(EnumArgs a) {
     a.lane_counts[lane] = c;
     const uint32_t t = block_sum(c, sh);
     if (threadIdx.x == 0) a.counts[blockIdx.x] = t;
+}
+
+// Pass 1 of a marked build (up to 64 candidates a lane): one bit a candidate, so
+// that pass 2 need not walk again.
+template <typename W, int WALK>
+__global__ void __launch_bounds__(kBlock) k_enum_mark_bits(EnumArgs a) {
+    __shared__ uint64_t ends[kBlock + 1];
+    __shared__ uint32_t sh[kBlock];
+    const uint64_t lane = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x, start = lane * a.per_lane;
+    uint64_t mask = 0;
+    walk_lane<W, WALK>(a, ends, [&](W s, uint32_t) {
+        uint64_t rank = static_cast<uint64_t>(s);
+        if (a.weight >= 0) {
+            rank = 0;
+            uint32_t k = 0;
+            for (uint64_t left = static_cast<uint64_t>(s); left != 0; left &= left - 1)
+                rank += binom(a.binom, static_cast<uint32_t>(__builtin_ctzll(left)), ++k);
+        }
+        mask |= 1ull << (rank - start);
+    });
+    if (start < a.total) a.marks[lane] = mask;
+    const uint32_t c = block_sum(static_cast<uint32_t>(__builtin_popcountll(mask)), sh);
+    if (threadIdx.x == 0) a.counts[blockIdx.x] = c;
+}
+
+// Pass 2 of a marked build: a lane steps through its candidates up to the last
+// member.
+template <typename W>
+__global__ void __launch_bounds__(kBlock) k_enum_write_bits(EnumArgs a) {
+    __shared__ uint32_t sh[kBlock];
+    const uint64_t lane = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x, start = lane * a.per_lane;
+    uint64_t mask = start < a.total ? a.marks[lane] : 0ull;
+    const uint32_t local = block_exclusive_scan(static_cast<uint32_t>(__builtin_popcountll(mask)), sh);
+    if (mask == 0) return;
+    uint64_t pos = a.offsets[blockIdx.x] + local;
+    for (W s = candidate<W>(a, start);;) {
+        if (mask & 1) a.reps[pos++] = static_cast<uint64_t>(s);
+        mask >>= 1;
+        if (mask == 0) break;
+        s = a.weight >= 0 ? next_combination<W>(s) : static_cast<W>(s + 1);
+    }
+}
+
+// Stabilizer sizes of a marked build's members.
+template <typename W>
+__global__ void __launch_bounds__(kBlock) k_stab(PlanDev P, const uint64_t *reps, uint64_t d, uint16_t *stab) {
+    const uint64_t i = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    if (i >= d) return;
+    const W r = static_cast<W>(reps[i]);
+    uint32_t c = 0;
+    for_each_image<W, kOrbitGeneric>(P, r, [&](W v, uint32_t) {
+        c += v == r ? 1u : 0u;
+        return true;
+    });
+    stab[i] = static_cast<uint16_t>(c);
 }
 
 // Count only: block totals are added into *acc (integer atomic adds: the
@@ -428,29 +486,43 @@ uint32_t cand_per_lane(uint64_t candidates, int walk) {
     return static_cast<uint32_t>(std::min<uint64_t>(most, std::max<uint64_t>(4, candidates >> 20)));
 }
 
+// Whether the build marks the members, for pass 2 to step through the
+// candidates, or walks twice.  Members cost a walk every image, so a second
+// walk costs most where they are many: 30-site ring in scrambled order, 60
+// images, 1.6e8 candidates: 6.4 ms walked twice, 2.9 marked; 4x9, 144 images: 5.1
+// and 2.9; 6x6, 12 up, 288 images, 1.3e9 candidates: 6.2 and 4.8; 6x6, 18 up, 9e9:
+// 11.2 and 15.2.  Rings walk their members by a few runs (32 sites: 3 ms).
+bool marked_build(int walk, uint64_t total) { return walk != kWalkRing && total <= kMarkCandidates; }
+
 // Sorted representatives and their stabilizer sizes.
 template <typename W, int WALK>
 void enumerate_impl(ls_basis *b, hipStream_t st, uint64_t total) {
+    const bool marked = marked_build(WALK, total);
     EnumArgs a{};
     a.plan = b->plan_dev;
     a.binom = b->d_binom;
     a.begin = 0;
     a.total = total;
-    a.per_lane = cand_per_lane(total, WALK);
+    a.per_lane = marked ? std::min(64u, cand_per_lane(total, WALK)) : cand_per_lane(total, WALK);
     a.n_sites = b->plan.n_sites;
     a.weight = b->weight;
     const uint64_t lanes = (total + a.per_lane - 1) / a.per_lane;
     const uint64_t blocks = grid_for(lanes);
-    StreamBuf lanes_b(std::max<uint64_t>(blocks, 1) * kBlock * sizeof(uint32_t), st);
+    // a count or 64 marks of every lane
+    StreamBuf lanes_b(std::max<uint64_t>(blocks, 1) * kBlock * (marked ? sizeof(uint64_t) : sizeof(uint32_t)), st);
     StreamBuf counts_b(std::max<uint64_t>(blocks, 1) * sizeof(uint32_t), st);
     StreamBuf offsets_b(std::max<uint64_t>(blocks, 1) * sizeof(uint64_t), st);
     StreamBuf total_b(sizeof(uint64_t), st);
     a.lane_counts = lanes_b.as<uint32_t>();
+    a.marks = lanes_b.as<uint64_t>();
     a.counts = counts_b.as<uint32_t>();
     a.offsets = offsets_b.as<uint64_t>();
     uint64_t dim = 0;
     if (blocks > 0) {
-        hipLaunchKernelGGL((k_enum_mark<W, WALK>), dim3(blocks), dim3(kBlock), 0, st, a);
+        if constexpr (WALK != kWalkRing) {
+            if (marked) hipLaunchKernelGGL((k_enum_mark_bits<W, WALK>), dim3(blocks), dim3(kBlock), 0, st, a);
+        }
+        if (!marked) hipLaunchKernelGGL((k_enum_mark<W, WALK>), dim3(blocks), dim3(kBlock), 0, st, a);
         LS_HIP_CHECK(hipGetLastError());
         hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, st, a.counts, blocks, offsets_b.as<uint64_t>(),
                            total_b.as<uint64_t>());
@@ -463,7 +535,11 @@ void enumerate_impl(ls_basis *b, hipStream_t st, uint64_t total) {
     b->d_stab = dev_alloc_n<uint16_t>(std::max<uint64_t>(dim, 1), st);
     a.reps = b->d_reps;
     a.stab = b->d_stab;
-    if (dim > 0) {
+    if (dim > 0 && marked) {
+        hipLaunchKernelGGL((k_enum_write_bits<W>), dim3(blocks), dim3(kBlock), 0, st, a);
+        hipLaunchKernelGGL((k_stab<W>), dim3(grid_for(dim)), dim3(kBlock), 0, st, b->plan_dev, b->d_reps, dim, b->d_stab);
+        LS_HIP_CHECK(hipGetLastError());
+    } else if (dim > 0) {
         hipLaunchKernelGGL((k_enum_write<W, WALK>), dim3(blocks), dim3(kBlock), 0, st, a);
         LS_HIP_CHECK(hipGetLastError());
     }

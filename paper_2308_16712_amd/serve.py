@@ -87,12 +87,13 @@ def _search_bytes(dim: int) -> int:
 
 
 def _walk_bytes(cand: int) -> int:
-    """Scratch of the enumeration: a count per lane (128 candidates, fewer in
-    small sectors; rings have up to 512), and a count and an offset per block
-    of 256 lanes."""
-    lanes = -(-cand // min(128, max(4, cand >> 20)))
-    blocks = -(-lanes // 256)
-    return blocks * (256 * 4 + 12)
+    """Scratch of the enumeration, a count and an offset per block of 256 lanes
+    and per lane either 8 bytes of marks (up to 64 candidates; up to 2^33 in
+    all) or a 4-byte count (128 candidates, fewer in small sectors; rings have
+    up to 512)."""
+    most, each = (64, 8) if cand <= 1 << 33 else (128, 4)
+    lanes = -(-cand // min(most, max(4, cand >> 20)))
+    return -(-lanes // 256) * (256 * each + 12)
 
 
 def footprint_bytes(sector, max_iter: int) -> int:

@@ -37,4 +37,7 @@ def test_build_scratch_is_reserved():
     for cand in (1, 1000, 1 << 20, (1 << 27) - 1, 9075135300):
         lanes = -(-cand // min(128, max(4, cand >> 20)))
         assert serve._walk_bytes(cand) >= lanes * 4 + -(-lanes // 256) * 12
+        if cand <= 1 << 33:      # marked: 8 bytes for up to 64
+            marked = -(-cand // min(64, max(4, cand >> 20)))
+            assert serve._walk_bytes(cand) >= marked * 8 + -(-marked // 256) * 12
     assert serve._walk_bytes(9075135300) < 9075135300 // 24
