@@ -193,7 +193,7 @@ void upload_jobs(Group &g, hipStream_t st) {
                                 st));
 }
 
-using TuneKey = std::tuple<int, int, int, uint32_t, uint32_t, int, int, int, int>;
+using TuneKey = std::tuple<int, int, int, uint32_t, uint32_t, int, int, int, int, int>;
 std::mutex g_tune_mu;
 std::map<TuneKey, std::pair<uint32_t, uint32_t>> g_tune_cache;   // -> (rpl, workgroups per CU)
 // (dim, kmin, kmax, LDS free) -> (mode, bits, own, chosen, best staged ns per lookup)
@@ -207,7 +207,7 @@ TuneKey tune_key(const Group &g) {
     while ((1ull << lg) < rows) ++lg;
     int lj = 0;
     while ((1u << lj) < g.jobs.size()) ++lj;
-    return TuneKey{g.v.word64, g.v.kind, g.v.chi, g.v.lx, g.v.ly, g.v.cplx ? 1 : 0, g.nr, lg, lj};
+    return TuneKey{g.v.word64, g.v.kind, g.v.chi, g.v.lx, g.v.ly, g.v.cplx ? 1 : 0, g.v.together ? 1 : 0, g.nr, lg, lj};
 }
 
 float time_group(Group &g, hipStream_t st) {
