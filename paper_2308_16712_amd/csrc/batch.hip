@@ -37,8 +37,24 @@ struct Tile {
 // around the tile loop, so it runs in 512-thread workgroups.
 constexpr int batch_block(int kind, bool cplx) { return (kind == kOrbitTorus && cplx) ? 512 : block_of(kind); }
 
+// Waves per SIMD the register allocator must allow, for the variants that end
+// one or two registers above 80 (72 with eight real columns) without it and
+// lose a wave: 64 rings of one column 115 ms with six, 128 with five.
+constexpr int batch_waves(bool word64, int kind, int chi, bool cplx, int nr) {
+    if (kind == kOrbitRing32) {
+        if (cplx ? nr <= 2 : chi == kChiReal && (nr == 2 || nr == 4)) return 6;
+        if (chi == kChiTrivial && nr == 8) return 7;
+    }
+    if (kind == kOrbitGeneric) {
+        if (word64 && chi == kChiTrivial && nr <= 4) return 6;
+        if (!word64 && chi == kChiTrivial && nr == 8) return 7;
+    }
+    return 1;
+}
+
 template <typename W, int KIND, int CHI, bool CPLX, int NR, uint32_t LX, uint32_t LY, uint32_t NZ, bool TOGETHER>
 __global__ void __launch_bounds__(batch_block(KIND, CPLX))
+    __attribute__((amdgpu_waves_per_eu(batch_waves(sizeof(W) == 8, KIND, CHI, CPLX, NR))))
     k_matvec_batch(const MatvecJob *jobs, const Tile *tiles, uint32_t n_tiles, uint32_t *counter, uint32_t rpl,
                    uint32_t tile_rows) {
     constexpr int BLOCK = batch_block(KIND, CPLX);
