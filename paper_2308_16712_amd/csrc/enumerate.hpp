@@ -12,8 +12,8 @@
 // order, where most members are, m is small; above, one test rules out
 // millions of candidates (the prefix pruning of necklace generation, here
 // for any group).  Bound by the VALU, and by lanes waiting for the busiest of
-// their wavefront.  Counting 3.4e10 candidates of the 40-spin chain: 253 ms
-// testing each, 20 ms with the jumps; the 6x6 sector's build 82 to 36 ms.
+// their wavefront.  Counting 3.4e10 candidates of the 40-spin chain: 351 ms
+// testing each, 20 ms with the jumps; the 6x6 sector's build 82 ms then, 11 now.
 #pragma once
 
 #include "orbit.hpp"

@@ -543,7 +543,7 @@ __device__ __forceinline__ void run_rows(const MatvecJob &a, const LdsTables &L,
     RowStab<uses_ratio_table(KIND, STAGED)> rs{};
     T acc[NR];
     uint32_t t = a.n_diag;
-    W pr[kTorusCosetSlots] = {};   // p(r) for every coset (torus search)
+    W pr[kTorusCosetSlots] = {};   // p(r) for every base image (torus search)
 
     auto begin_row = [&]() {
         r = a.search.reps[row];
