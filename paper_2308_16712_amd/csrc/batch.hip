@@ -212,8 +212,8 @@ void upload_jobs(Group &g, hipStream_t st) {
 using TuneKey = std::tuple<int, int, int, uint32_t, uint32_t, int, int, int, int, int>;
 std::mutex g_tune_mu;
 std::map<TuneKey, std::pair<uint32_t, uint32_t>> g_tune_cache;   // -> (rpl, workgroups per CU)
-// (dim, kmin, kmax, LDS free) -> (mode, bits, own, chosen, best staged ns per lookup)
-std::map<std::tuple<uint64_t, uint64_t, uint64_t, uint64_t>, std::tuple<uint32_t, uint32_t, double, double, double>>
+// (dim, kmin, kmax, LDS free, the basis's own mode) -> (mode, bits, own, chosen, best staged ns per lookup)
+std::map<std::tuple<uint64_t, uint64_t, uint64_t, uint64_t, uint32_t>, std::tuple<uint32_t, uint32_t, double, double, double>>
     g_search_cache;
 
 TuneKey tune_key(const Group &g) {
@@ -349,7 +349,8 @@ bool staged_fits(uint32_t nbits, size_t lds_free) {
 // staged in LDS (when they fit beside the jobs' own LDS tables: lds_free
 // bytes); or the layout ls_batch_set_search forced.  The batch owns the
 // tables it builds; the basis is not modified.  Tuning results are cached
-// per process by (dim, kmin, kmax, lds_free).
+// per process by (dim, kmin, kmax, lds_free) and the basis's own layout: a
+// choice of the hash index means nothing to a basis built without one.
 SearchChoice tuned_search(ls_batch *B, const ls_basis *b, size_t lds_free, hipStream_t st) {
     SearchChoice C;
     C.S = b->search_dev;
@@ -366,7 +367,7 @@ SearchChoice tuned_search(ls_batch *B, const ls_basis *b, size_t lds_free, hipSt
         return C;
     }
     if (b->dim < 4096) return C;
-    const auto key = std::make_tuple(b->dim, own.kmin, own.kmax, static_cast<uint64_t>(lds_free));
+    const auto key = std::make_tuple(b->dim, own.kmin, own.kmax, static_cast<uint64_t>(lds_free), own.mode);
     auto table = [&](uint32_t mode, uint32_t nbits, uint32_t **out) { return bucket_layout(b, mode, nbits, out, st); };
     std::tuple<uint32_t, uint32_t, double, double, double> pick;   // mode, bits, own, chosen, staged (ns/key)
     bool cached = false;
