@@ -257,8 +257,9 @@ ls_status ls_operator_count(const ls_operator *op, uint64_t *n_offdiag, void *st
 /* The orbit search (the representative of each generated state, Section
  * 5.2's condition applied to a neighbour) that the products of op run:
  * kind 0 the general walk over coset representatives, 1 rings of at most 32
- * sites (rotations of a doubled word), 2 tori (pair-table pruned search),
- * 3 rings of 33 to 63 sites (longest-zero-run candidates); fixed_shape 1
+ * sites and 3 rings of 33 to 63 sites (the longest runs of equal spins), 2
+ * tori of 3 to 6 columns (pair-table pruned search; below 6 columns only with
+ * at least 64 images besides spin inversion); fixed_shape 1
  * when a torus search runs with a compile-time layout (6x6 or 4x4 with the
  * full point group and spin inversion).  For an operator with stored
  * elements (ls_operator_store) it is the search the store ran; its products
@@ -270,7 +271,7 @@ ls_status ls_operator_search_kind(const ls_operator *op, uint32_t *kind, uint32_
  * row's elements are generated from its representative, looked up, and
  * accumulated; no atomics, since H is Hermitian).  Each row is summed in
  * term order, diagonal first, whatever the launch shape: a single column of
- * a small sector (below 2^18 rows on tori, 2^16 otherwise) gives each row
+ * a small sector (below 2^18 rows with the torus search, 2^16 otherwise) gives each row
  * several lanes that generate its elements in parallel and add them in that
  * order, so the results are the same bits as the one-lane form.
  *   nrhs   1..64 right-hand sides.
